@@ -66,6 +66,31 @@ def test_tile_edges(csrk, monkeypatch, M, K, D, N, p, kind, bf16, ones):
     check(F, *oracle.fusedmm(M, K, D, N, rp, ci, v, A, B, C), "fusedmm " + what)
 
 
+@pytest.mark.parametrize("M,K,D,N", [(1920, 1000, 40, 77), (4096, 1024, 24, 512), (5632, 700, 20, 200)])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("first,step", [(-1, 1), (-2, 1), (0, 1), (-1, 17), (-18, 17)])
+def test_one_swap_at_each_cut(csrk, monkeypatch, M, K, D, N, bf16, first, step):
+    # Sorted rows but for one in every 128, whose entries number `first` and `first + step` from a multiple of 64 columns are
+    # exchanged: across, before and behind every place where a range of K may begin.  Nothing else sends the rows of those
+    # workgroups to the entry-by-entry path.  K is cut in all three shapes, and the second one (the third in bfloat16) has
+    # the wide blocks that work a tile further ahead.
+    monkeypatch.setenv("CSRK_MFMA", "2")
+    rng = np.random.default_rng(M + step - first)
+    rp, ci = pattern(rng, M, K, 0.2, "even")
+    for block in range(M // 128):
+        r = block * 128 + int(rng.integers(128))
+        at = rp[r] + np.searchsorted(ci[rp[r]:rp[r + 1]], 64 * (1 + block % ((K - 1) // 64))) + first
+        i, j = np.clip([at, at + step], rp[r], rp[r + 1] - 1)
+        ci[i], ci[j] = ci[j], ci[i]
+    v = rng.uniform(-1, 1, len(ci)).astype(np.float32)
+    A, B, C = (rng.normal(size=s).astype(np.float32) for s in ((M, D), (K, D), (K, N)))
+    (dA, A), (dB, B), (dC, C) = map(dev_bf16 if bf16 else lambda x: (dev(x), x), (A, B, C))
+    O, P, F = results(csrk, M, K, D, N, rp, ci, v, dA, dB, dC, bf16)
+    check(O, *oracle.spmm(M, K, N, rp, ci, v, C), "spmm")
+    check(P, *oracle.sddmm(M, K, D, rp, ci, v, A, B), "sddmm")
+    check(F, *oracle.fusedmm(M, K, D, N, rp, ci, v, A, B, C), "fusedmm")
+
+
 @pytest.mark.parametrize("bad", [np.inf, np.nan, 3.4e38, 1e-41])
 @pytest.mark.parametrize("where", ["v", "A", "B", "C"])
 def test_values_without_pieces(csrk, monkeypatch, bad, where):
