@@ -116,8 +116,9 @@ def test_values_without_pieces(csrk, monkeypatch, bad, where):
         np.testing.assert_allclose(a[fine], b[fine], rtol=1e-4, atol=1e-5 * scale)
 
 
+@pytest.mark.parametrize("in_place", [False, True])
 @pytest.mark.parametrize("D", [24, 100])
-def test_scores_out_of_range(csrk, monkeypatch, D):
+def test_scores_out_of_range(csrk, monkeypatch, D, in_place):
     # finite operands whose dot products leave the range of floats: infinities of their sign, as in the vector kernels (the
     # products of the smaller pieces overflow to either sign), beside products that stay inside
     M, K = 200, 300
@@ -130,6 +131,31 @@ def test_scores_out_of_range(csrk, monkeypatch, D):
     got = []
     for mode in ("2", "3"):
         monkeypatch.setenv("CSRK_MFMA", mode)
-        got.append(csrk.sddmm_csr(M, K, D, dev(rp), dev(ci), dev(v), dev(A), dev(B)).cpu().numpy())
+        d_v = dev(v)
+        got.append(csrk.sddmm_csr(M, K, D, dev(rp), dev(ci), d_v, dev(A), dev(B), P=d_v if in_place and mode == "2" else None).cpu().numpy())
     assert np.isneginf(got[1]).any() and np.isfinite(got[1]).any()
     np.testing.assert_allclose(got[0], got[1], rtol=1e-5)
+
+
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+@pytest.mark.parametrize("where", ["A", "B"])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_bf16_scores_out_of_range(csrk, monkeypatch, bad, where, in_place):
+    M, K, D = 200, 300, 40
+    rng = np.random.default_rng(5)
+    rp, ci = pattern(rng, M, K, 0.3, "even")
+    v = rng.uniform(0.5, 1, len(ci)).astype(np.float32)
+    A, B = rng.normal(size=(M, D)).astype(np.float32), rng.normal(size=(K, D)).astype(np.float32)
+    (dA, A), (dB, B) = dev_bf16(A), dev_bf16(B)
+    (A if where == "A" else B)[7, 3] = bad
+    (dA if where == "A" else dB)[7, 3] = bad
+    got = []
+    for mode in ("2", "3"):
+        monkeypatch.setenv("CSRK_MFMA", mode)
+        d_v = dev(v)
+        got.append(csrk.sddmm_csr_bf16(M, K, D, dev(rp), dev(ci), d_v, dA, dB, P=d_v if in_place and mode == "2" else None).cpu().numpy())
+    fine = np.isfinite(got[1])
+    assert fine.any() and not fine.all()
+    np.testing.assert_array_equal(got[0][~fine], got[1][~fine])
+    _, terms = oracle.sddmm(M, K, D, rp, ci, v, np.nan_to_num(A, posinf=0), np.nan_to_num(B, posinf=0))
+    assert (np.abs(got[0][fine] - got[1][fine]) <= 2e-5 * terms[fine]).all()
