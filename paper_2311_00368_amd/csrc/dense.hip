@@ -163,6 +163,7 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
     a.Cp = base + l.c;
     a.O = out;
     a.partial = reinterpret_cast<float *>(base + l.partial);
+    a.lost_is_nan = s.op == kDenseSddmm;
     a.prep_flags = reinterpret_cast<int32_t *>(base + l.flags);
     a.cuts = reinterpret_cast<int32_t *>(base + l.cuts);
 
