@@ -22,24 +22,23 @@ size_t padded(size_t bytes) { return (bytes + 255) / 256 * 256; }
 size_t up32(int x) { return ((size_t)x + 31) / 32 * 32; }
 
 int prepare_blocks(size_t units) {
-    // one unit of 8 values per thread: a call's latency counts here (two: 1-2 us more).  Every workgroup of the product looks
-    // through the blocks' flags, so there are not more than a few for each of its threads.
+    // one unit of 8 values per thread: a call's latency counts here (two: 1-2 us more)
     const size_t blocks = (units + 255) / 256;
     return (int)(blocks > 1024 ? 1024 : blocks);
 }
 
 // where everything lies in the scratch area
 struct Layout {
-    size_t c, b, a, flags, cuts, partial, bytes;
+    size_t c, b, a, todo, met, special, redo, cuts, partial, bytes;
     int n_tiles, c_blocks, b_blocks, a_blocks;
     Layout(const DenseShape &s, const DenseConfig &cfg) {
         const size_t pieces = s.bf16 ? 2 : 6;       // bytes of a prepared value
         const int bn = cfg.ct * 16;
         n_tiles = s.op == kDenseSddmm ? 0 : (s.N + bn - 1) / bn * cfg.ct;
-        const size_t d = (size_t)cfg.ds * 32, k = up32(s.K);
+        const size_t d = (size_t)cfg.ds * 32, k = up32(s.K), octs = cfg.ds == 3 ? 16 : cfg.ds * 4;
         c_blocks = prepare_blocks(k / 8 * n_tiles * 16);
-        b_blocks = prepare_blocks(k * d / 8);
-        a_blocks = prepare_blocks(up32(s.M) * d / 8);
+        b_blocks = prepare_blocks(k * octs);
+        a_blocks = prepare_blocks(up32(s.M) * octs);
         size_t at = 0;
         auto take = [&](size_t n) {
             const size_t was = at;
@@ -50,7 +49,10 @@ struct Layout {
         // (whole tiles of SDDMM's columns)
         b = take((k + kSddmmMaxKt - 32) * d * pieces);
         a = take(up32(s.M) * d * pieces);
-        flags = take((size_t)(c_blocks + b_blocks + a_blocks) * 4);
+        todo = take(8);
+        met = take(s.op == kDenseFused ? (size_t)b_blocks * 4 : 0);
+        special = take(s.op == kDenseFused ? k : 0);
+        redo = take(s.op != kDenseSddmm ? (size_t)cfg.segs * (n_tiles / cfg.ct) * s.M * 2 : 0);
         cuts = take(cfg.segs > 1 ? (size_t)(cfg.segs - 1) * s.M * 4 : 0);
         partial = take(cfg.segs > 1 && s.op != kDenseSddmm ? (size_t)cfg.segs * s.M * s.N * 4 : 0);
         bytes = at;
@@ -148,6 +150,7 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
     a.segs = c.segs;
     a.seg_k = c.seg_k;
     a.n_tiles = l.n_tiles;
+    a.bn = c.ct * 16;
     a.d_steps = c.ds;
     a.c_blocks = l.c_blocks;
     a.b_blocks = l.b_blocks;
@@ -163,8 +166,12 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
     a.Cp = base + l.c;
     a.O = out;
     a.partial = reinterpret_cast<float *>(base + l.partial);
-    a.lost_is_nan = s.op == kDenseSddmm;
-    a.prep_flags = reinterpret_cast<int32_t *>(base + l.flags);
+    if (s.op == kDenseFused) {
+        a.special = reinterpret_cast<uint8_t *>(base + l.special);
+        a.special_met = reinterpret_cast<int32_t *>(base + l.met);
+    }
+    if (s.op != kDenseSddmm) a.todo = reinterpret_cast<int32_t *>(base + l.todo);
+    a.redo = reinterpret_cast<uint16_t *>(base + l.redo);
     a.cuts = reinterpret_cast<int32_t *>(base + l.cuts);
 
     const DenseKernel k = s.op == kDenseSpmm    ? (s.bf16 ? spmm_kernel<1>(c.ct) : spmm_kernel<3>(c.ct))
@@ -187,13 +194,18 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
     if (s.bf16) hipLaunchKernelGGL(dense_prepare_kernel<bf16_t>, dim3(prepare), dim3(256), 0, stream, a);
     else hipLaunchKernelGGL(dense_prepare_kernel<float>, dim3(prepare), dim3(256), 0, stream, a);
     hipLaunchKernelGGL(k.fn, dim3((unsigned)a.row_blocks * a.col_blocks * a.segs), dim3(kDenseThreads), k.lds_bytes, stream, a);
-    if (a.segs > 1 && s.op != kDenseSddmm) {
-        const size_t units = (size_t)a.M * a.N / 4;
-        const unsigned blocks = (unsigned)(units < 2048 * 256 ? (units + 255) / 256 + 1 : 2048);
-        if (a.N % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & 15u) == 0)
-            hipLaunchKernelGGL(dense_combine_kernel<true>, dim3(blocks), dim3(256), 0, stream, a);
-        else
-            hipLaunchKernelGGL(dense_combine_kernel<false>, dim3(blocks), dim3(256), 0, stream, a);
+    if (s.op != kDenseSddmm) {
+        const int unit = s.bf16 ? 8 : 4;
+        uintptr_t at = reinterpret_cast<uintptr_t>(out) | reinterpret_cast<uintptr_t>(C);
+        if (s.op == kDenseFused) at |= reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B);
+        const bool vec = a.N % unit == 0 && a.D % unit == 0 && (at & 15u) == 0;
+        const DenseKernel f = dense_finish_kernel(s.bf16, s.op == kDenseFused, vec, c.ct);
+        if (!f.fn) return hipErrorInvalidValue;
+        // not many more workgroups than the chip holds at a time (2048 of FusedMM's: 6.8 instead of 5.8 us for the sums of
+        // 16384 x 4096, 128 columns, in 2 ranges), and with long rows to do again some to choose from
+        const int rows = a.segs > 1 && a.N < 1024 ? 1024 / a.N : 1;
+        const int blocks = (a.M + rows - 1) / rows, most = s.op == kDenseFused ? 1536 : 1280;
+        hipLaunchKernelGGL(f.fn, dim3(blocks < most ? blocks : most), dim3(256), 0, stream, a);
     }
     return hipGetLastError();
 }

@@ -40,5 +40,7 @@ struct DenseKernel {
 };
 DenseKernel dense_fused_kernel_f32(int ct, int ds);
 DenseKernel dense_fused_kernel_bf16(int ct, int ds);
+// `vec`: 128-bit accesses of all dense operands and the output
+DenseKernel dense_finish_kernel(bool bf16, bool fused, bool vec, int ct);
 
 }  // namespace csrk
