@@ -242,3 +242,39 @@ def test_time_of_what_is_left(csrk, monkeypatch, M, K, D, N, op, kind):
         monkeypatch.setenv("CSRK_MFMA", mode)
         us.append(best_time(call))
     assert us[0] < 2.5 * us[1] + 30, us
+
+
+@pytest.mark.parametrize("op,where", [("spmm", "v"), ("spmm", "C"), ("sddmm", "v"), ("sddmm", "A"), ("sddmm", "B"),
+                                      ("fusedmm", "v"), ("fusedmm", "A"), ("fusedmm", "B"), ("fusedmm", "C")])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("factor", [1e-35, 1e15])
+def test_small_and_large_values(csrk, monkeypatch, op, where, bf16, factor):
+    # normal floats far from 1, underflowed probabilities and the like, stay on the matrix cores: results as good as any, and no
+    # slower than the vector kernels (all entries one by one it was 1.5 to 3 times)
+    M, K, D, N = 4096, 2048, 100, 128
+    rng = np.random.default_rng(M)
+    rp, ci = pattern(rng, M, K, 0.3, "even")
+    x = {"v": rng.uniform(0.5, 1, len(ci)), "A": rng.normal(size=(M, D)), "B": rng.normal(size=(K, D)), "C": rng.normal(size=(K, N))}
+    x = {k: a.astype(np.float32) for k, a in x.items()}
+    x[where] *= np.float32(factor)
+    d = {k: (dev_bf16 if bf16 and k != "v" else lambda a: (dev(a), a))(a) for k, a in x.items()}
+    s, (A, B, C), w = (dev(rp), dev(ci), d["v"][0]), (d[k][0] for k in "ABC"), {k: d[k][1] for k in d}
+    suffix = "_bf16" if bf16 else ""
+    call, want = {
+        "spmm": (lambda: getattr(csrk, "spmm_csr" + suffix)(M, K, N, *s, C), lambda r: oracle.spmm(M, K, N, rp, ci, w["v"], w["C"], rows=r)),
+        "sddmm": (lambda: getattr(csrk, "sddmm_csr" + suffix)(M, K, D, *s, A, B), lambda r: oracle.sddmm(M, K, D, rp, ci, w["v"], w["A"], w["B"], rows=r)),
+        "fusedmm": (lambda: getattr(csrk, "fusedmm_csr" + suffix)(M, K, D, N, *s, A, B, C),
+                    lambda r: oracle.fusedmm(M, K, D, N, rp, ci, w["v"], w["A"], w["B"], w["C"], rows=r))}[op]
+    us = []
+    for mode in ("3", "2"):
+        monkeypatch.setenv("CSRK_MFMA", mode)
+        got = call()
+        us.append(best_time(call))
+    rows = np.arange(0, M, 13)
+    want, terms = want(rows)
+    got = got.cpu().numpy().astype(np.float64)
+    got = got[rows] if op != "sddmm" else got[~np.isnan(want)]
+    if op == "sddmm":
+        want, terms = want[~np.isnan(want)], terms[~np.isnan(terms)]
+    assert (np.abs(got - want) <= 2e-6 * terms).all()
+    assert us[1] < 1.2 * us[0] + 10, us
