@@ -71,7 +71,7 @@ __global__ __launch_bounds__(kBlockThreads) void dense_finish(DenseArgs a) {
     const int M = a.M, N = a.N;
     const int lane = lane_id(), wave = uniform(threadIdx.x >> 6);
 
-    // elements [from, to) of O as the sums of the ranges' outputs, in the order of the ranges
+    // elements [from, to) of O as the sums of the ranges' outputs, two and two
     using T = std::conditional_t<VEC == 1, float, f32x4>;
     constexpr int kUnit = sizeof(T) / 4;
     auto add_ranges = [&](size_t from, size_t to, size_t thread, size_t threads) CSRK_INLINE {
@@ -84,14 +84,11 @@ __global__ __launch_bounds__(kBlockThreads) void dense_finish(DenseArgs a) {
             for (int i = 0; i < 2; ++i)
 #pragma unroll
                 for (int s = 0; s < kDenseMaxSegs; ++s)
-                    if (s < a.segs) x[i][s] = p[s * total + at[i]];
+                    x[i][s] = s < a.segs ? p[s * total + at[i]] : T{};
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                T sum = x[i][0];
-#pragma unroll
-                for (int s = 1; s < kDenseMaxSegs; ++s)
-                    if (s < a.segs) sum += x[i][s];
-                reinterpret_cast<T *>(a.O)[at[i]] = sum;
+                static_assert(kDenseMaxSegs == 8);
+                reinterpret_cast<T *>(a.O)[at[i]] = ((x[i][0] + x[i][1]) + (x[i][2] + x[i][3])) + ((x[i][4] + x[i][5]) + (x[i][6] + x[i][7]));
             }
         }
     };

@@ -278,3 +278,40 @@ def test_small_and_large_values(csrk, monkeypatch, op, where, bf16, factor):
         want, terms = want[~np.isnan(want)], terms[~np.isnan(terms)]
     assert (np.abs(got - want) <= 2e-6 * terms).all()
     assert us[1] < 1.2 * us[0] + 10, us
+
+
+@pytest.mark.parametrize("op,M,K,D,N", [("spmm", 16114, 3635, 0, 64), ("spmm", 5003, 2999, 0, 77), ("spmm", 8192, 4096, 0, 256),
+                                        ("sddmm", 4096, 2048, 128, 0), ("sddmm", 3001, 1999, 64, 0), ("sddmm", 2048, 2048, 24, 0),
+                                        ("fusedmm", 15872, 3072, 32, 48), ("fusedmm", 6000, 2048, 128, 128), ("fusedmm", 2048, 4096, 64, 512)])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("sign", ["both", "one"])
+def test_error_is_the_vector_kernels(csrk, monkeypatch, op, M, K, D, N, bf16, sign):
+    # The 2-norm of the error against FP64, compared with the vector kernels'.  Data of one sign shows what is always rounded
+    # one way (up to 2.05 times the vector kernels' error with one truncating accumulator).  Random draws of these ranges had
+    # ratios of up to 1.00 for data of both signs, and of up to 1.13 with one, where both are close to the error of
+    # rounding the result once.
+    gen = torch.Generator(device="cuda").manual_seed(M + N)
+    rand = lambda *n: torch.rand(n, device="cuda", generator=gen) * (1 if sign == "one" else 2) - (0 if sign == "one" else 1)
+    keep = torch.rand((M, K), device="cuda", generator=gen) < 0.2
+    at = keep.nonzero()
+    rp = torch.zeros(M + 1, dtype=torch.int32, device="cuda")
+    rp[1:] = torch.cumsum(keep.sum(1), 0).to(torch.int32)
+    ci, v = at[:, 1].to(torch.int32).contiguous(), rand(len(at))
+    A, B, C = rand(M, max(D, 1)), rand(K, max(D, 1)), rand(K, max(N, 1))
+    if bf16:
+        A, B, C = A.bfloat16(), B.bfloat16(), C.bfloat16()
+    f = getattr(csrk, {"spmm": "spmm_csr", "sddmm": "sddmm_csr", "fusedmm": "fusedmm_csr"}[op] + ("_bf16" if bf16 else ""))
+    args = {"spmm": (M, K, N, rp, ci, v, C), "sddmm": (M, K, D, rp, ci, v, A, B), "fusedmm": (M, K, D, N, rp, ci, v, A, B, C)}[op]
+    got = []
+    for mode in ("2", "3"):
+        monkeypatch.setenv("CSRK_MFMA", mode)
+        got.append(f(*args).double())
+    s = v.double()
+    if D:
+        s = s * (A.double() @ B.double().t().contiguous())[at[:, 0], at[:, 1]]
+    if N:
+        dense = torch.zeros((M, K), dtype=torch.float64, device="cuda")
+        dense[at[:, 0], at[:, 1]] = s
+        s = dense @ C.double()
+    matrix, vector = ((g - s).norm().item() / s.norm().item() for g in got)
+    assert matrix <= (1.02 if sign == "both" else 1.2) * vector, (matrix, vector)
