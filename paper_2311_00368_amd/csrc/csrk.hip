@@ -1352,18 +1352,17 @@ Choice choose_fused(const DeviceState &d, const csrk_plan_s *plan, int M, int K,
 struct VectorCost {
     double call, work, entries, cells;
 };
-double vector_us(const DenseShape &s, long long nnz) {
+double vector_us(const DenseShape &s, long long nnz, bool wide) {
     static constexpr VectorCost f32_spmm[] = {{4.6, 0, 5.2, 0.15}, {5.4, 95, 0, 0.64}, {7.0, 0, 20.9, 0.88}, {9.7, 0, 28.3, 2.3}};
     static constexpr VectorCost f32_fused[] = {{5.6, 200, 0.4, 0.08}, {6.1, 98, 4.5, 0.73}, {6.3, 108, 8.0, 1.23}, {8.2, 16.5, 29.1, 3.5}};
     static constexpr VectorCost bf16_spmm[] = {{4.9, 0, 7.5, 0.16}, {5.2, 94, 2.5, 0.28}, {4.8, 121, 3.5, 0.24}, {4.8, 121, 3.5, 0.24}};
     static constexpr VectorCost bf16_fused[] = {{6.2, 90, 7.5, 0.15}, {6.4, 85, 5.8, 0.33}, {6.1, 100, 6.3, 0.48}, {6.1, 100, 6.3, 0.48}};
-    // widths without 128-bit accesses: f32 / bf16 of SPMM, SDDMM, FusedMM
+    // widths or operands without 128-bit accesses (`wide`: there are some): f32 / bf16 of SPMM, SDDMM, FusedMM
     static constexpr VectorCost odd[3][2] = {{{11.2, 381, 16, 0}, {12.2, 373, 13.8, 0}},
                                              {{10.4, 209, 47.1, 0.06}, {14.6, 240, 40.9, 0.13}},
                                              {{16.3, 354, 4.8, 0.62}, {16.2, 286, 15.5, 0}}};
-    const int unit = s.bf16 ? 8 : 4;
     const int w = s.N <= 32 ? 0 : s.N <= 128 ? 1 : s.N <= 256 ? 2 : 3;
-    const VectorCost c = s.N % unit != 0 || s.D % unit != 0 ? odd[s.op][s.bf16]
+    const VectorCost c = !wide                             ? odd[s.op][s.bf16]
                          : s.op == kDenseSpmm              ? (s.bf16 ? bf16_spmm : f32_spmm)[w]
                          : s.op == kDenseFused             ? (s.bf16 ? bf16_fused : f32_fused)[w]
                          : s.bf16                          ? (s.D <= 64 ? VectorCost{4.8, 12.3, 7.35, 0.03} : VectorCost{4.6, 10.6, 12.5, 0.14})
@@ -1372,8 +1371,9 @@ double vector_us(const DenseShape &s, long long nnz) {
 }
 
 // The matrix-core kernels are taken where they are expected to be the faster ones by a tenth (SDDMM: by a third).  Over
-// 2600 other random calls of the ranges above, uneven rows among them, that made the average call 1.28 times as fast
-// (always the better of the two: 1.34), and 10 calls slower by more than 3 %.
+// 4000 other random calls of the ranges above, uneven rows among them, that made the average call 1.34 times as fast
+// (always the better of the two: 1.46), and 22 calls slower by more than 3 % (at worst 0.77 times as fast).  Over 4000 calls
+// of M 16-200000, K 32-65536, up to 2048 columns and 0.4-95 % it was 1.14 times (1.37), 4 slower (at worst 0.64).
 // FP32 SDDMM with dot products of up to 64 elements and aligned rows stays with the vector kernels: it is bound by S and P,
 // which the tiled kernel streams, and the matrix-core kernel was 0.4-1.1 times as fast there (32768 x 8192, 10 %, 32: 292
 // against 149 us).  With bfloat16 operands, which the vector kernel has to widen, it is the better one where the chip is
@@ -1387,7 +1387,14 @@ double short_bf16_sddmm_us(const DenseShape &s, const DenseConfig &c, int cus, d
     return -3.5 + rounds * (11.0 + c.seg_k / 32 * tile) + (c.ds == 1 ? 0.9 : 1.4) * 1e-6 * nnz;
 }
 
-bool dense_wanted(const DeviceState &d, const csrk_plan_s *plan, const DenseShape &s, long long nnz, DenseConfig *c) {
+uintptr_t addresses(std::initializer_list<const void *> pointers) {
+    uintptr_t a = 0;
+    for (const void *p : pointers) a |= reinterpret_cast<uintptr_t>(p);
+    return a;
+}
+
+// `operands`: the addresses of the dense operands and of O, or'ed together
+bool dense_wanted(const DeviceState &d, const csrk_plan_s *plan, const DenseShape &s, uintptr_t operands, long long nnz, DenseConfig *c) {
     const int mode = env_int("CSRK_MFMA", 1);       // 1 auto, 2 force where the kernels can run, 3 off
     if (mode == 3 || nnz < 0 || nnz >= (1ll << 30)) return false;
     // (tests that force or forbid one of the other families mean those)
@@ -1395,18 +1402,19 @@ bool dense_wanted(const DeviceState &d, const csrk_plan_s *plan, const DenseShap
         return false;
     if (plan && !plan->sorted) return false;
     const int unit = s.bf16 ? 8 : 4;
+    const bool wide = s.N % unit == 0 && s.D % unit == 0 && (operands & 15u) == 0;
     if (mode == 1) {
-        if (s.op == kDenseSddmm && !s.bf16 && s.D <= 64 && s.D % unit == 0) return false;
-        if (vector_us(s, nnz) < 11.0) return false;     // (less than any configuration is expected to take)
+        if (s.op == kDenseSddmm && !s.bf16 && s.D <= 64 && wide) return false;
+        if (vector_us(s, nnz, wide) < 11.0) return false;     // (less than any configuration is expected to take)
     }
     if (!dense_config(s, d.cus, c)) return false;
     if (d.fixed && c->bytes > d.head_floats * sizeof(float)) return false;
     if (mode == 2) return true;
     const double density = (double)nnz / ((double)s.M * (double)s.K);
-    if (s.op == kDenseSddmm && s.bf16 && s.D <= 64 && s.D % unit == 0)
-        return short_bf16_sddmm_us(s, *c, d.cus, (double)nnz, density) * 1.2 < vector_us(s, nnz);
-    const double us = c->us * (s.op == kDenseSddmm ? (0.9 + 0.9 * density) * (s.D % unit == 0 ? 1.25 : 1.0) : 0.82 + 0.5 * density);
-    return us * 1.1 < vector_us(s, nnz);
+    if (s.op == kDenseSddmm && s.bf16 && s.D <= 64 && wide)
+        return short_bf16_sddmm_us(s, *c, d.cus, (double)nnz, density) * 1.2 < vector_us(s, nnz, wide);
+    const double us = c->us * (s.op == kDenseSddmm ? (0.9 + 0.9 * density) * (wide ? 1.25 : 1.0) : 0.82 + 0.5 * density);
+    return us * 1.1 < vector_us(s, nnz, wide);
 }
 
 csrk_status dense_call(DeviceState &d, const DenseShape &s, const DenseConfig &c, const int32_t *rowptr, const int32_t *colidx,
@@ -1489,7 +1497,7 @@ static csrk_status spmm_run(const csrk_plan_s *plan, const ScratchSource &scratc
     CallRecord rec(1, stream);
     const DenseShape shape{kDenseSpmm, false, M, K, N, 0};
     DenseConfig dense;
-    if (dense_wanted(*d, plan, shape, nnz, &dense)) {
+    if (dense_wanted(*d, plan, shape, addresses({B, O}), nnz, &dense)) {
         rec.begin();
         return dense_call(*d, shape, dense, rowptr, colidx, vals, nullptr, nullptr, B, O, stream);
     }
@@ -1599,7 +1607,7 @@ static csrk_status sddmm_run(const csrk_plan_s *plan, const ScratchSource &scrat
     CallRecord rec(2, stream);
     const DenseShape shape{kDenseSddmm, false, M, K, 0, D};
     DenseConfig dense;
-    if (dense_wanted(*d, plan, shape, nnz, &dense)) {
+    if (dense_wanted(*d, plan, shape, addresses({A, B}), nnz, &dense)) {
         rec.begin();
         return dense_call(*d, shape, dense, rowptr, colidx, vals, A, B, nullptr, P, stream);
     }
@@ -1682,7 +1690,7 @@ static csrk_status fusedmm_run(const csrk_plan_s *plan, const ScratchSource &scr
     CallRecord rec(3, stream);
     const DenseShape shape{kDenseFused, false, M, K, N, D};
     DenseConfig dense;
-    if (dense_wanted(*d, plan, shape, nnz, &dense)) {
+    if (dense_wanted(*d, plan, shape, addresses({A, B, C, O}), nnz, &dense)) {
         rec.begin();
         return dense_call(*d, shape, dense, rowptr, colidx, vals, A, B, C, O, stream);
     }
@@ -2076,7 +2084,7 @@ static csrk_status spmm_bf16_run(long long nnz, int M, int K, int N, const int32
     CallRecord rec(11, stream);
     const DenseShape shape{kDenseSpmm, true, M, K, N, 0};
     DenseConfig dense;
-    if (dense_wanted(*d, nullptr, shape, nnz, &dense)) {
+    if (dense_wanted(*d, nullptr, shape, addresses({B, O}), nnz, &dense)) {
         rec.begin();
         return dense_call(*d, shape, dense, rowptr, colidx, vals, nullptr, nullptr, B, O, stream);
     }
@@ -2145,7 +2153,7 @@ static csrk_status sddmm_bf16_run(long long nnz, int M, int K, int D, const int3
     CallRecord rec(12, stream);
     const DenseShape shape{kDenseSddmm, true, M, K, 0, D};
     DenseConfig dense;
-    if (dense_wanted(*d, nullptr, shape, nnz, &dense)) {
+    if (dense_wanted(*d, nullptr, shape, addresses({A, B}), nnz, &dense)) {
         rec.begin();
         return dense_call(*d, shape, dense, rowptr, colidx, vals, A, B, nullptr, P, stream);
     }
@@ -2200,7 +2208,7 @@ static csrk_status fusedmm_bf16_run(long long nnz, int M, int K, int D, int N, c
     CallRecord rec(13, stream);
     const DenseShape shape{kDenseFused, true, M, K, N, D};
     DenseConfig dense;
-    if (dense_wanted(*d, nullptr, shape, nnz, &dense)) {
+    if (dense_wanted(*d, nullptr, shape, addresses({A, B, C, O}), nnz, &dense)) {
         rec.begin();
         return dense_call(*d, shape, dense, rowptr, colidx, vals, A, B, C, O, stream);
     }

@@ -315,3 +315,20 @@ def test_error_is_the_vector_kernels(csrk, monkeypatch, op, M, K, D, N, bf16, si
         s = dense @ C.double()
     matrix, vector = ((g - s).norm().item() / s.norm().item() for g in got)
     assert matrix <= (1.02 if sign == "both" else 1.2) * vector, (matrix, vector)
+
+
+@pytest.mark.parametrize("op,M,K,D,N", [("sddmm", 2048, 2048, 64, 0), ("spmm", 3072, 2048, 0, 64), ("fusedmm", 2048, 2048, 32, 64)])
+def test_choice_with_unaligned_operands(csrk, monkeypatch, op, M, K, D, N):
+    # without 128-bit accesses the vector kernels are slow: such calls go to the matrix cores (which of the two kernels it was
+    # shows in the last bits)
+    rng = np.random.default_rng(M)
+    rp, ci = pattern(rng, M, K, 0.3, "even")
+    s = dev(rp), dev(ci), dev(rng.uniform(-1, 1, len(ci)).astype(np.float32))
+    A, B, C = (dev(np.append(np.float32(0), rng.normal(size=n).astype(np.float32)))[1:].view(*n) for n in ((M, D), (K, D), (K, N)))
+    call = {"spmm": lambda: csrk.spmm_csr(M, K, N, *s, C), "sddmm": lambda: csrk.sddmm_csr(M, K, D, *s, A, B),
+            "fusedmm": lambda: csrk.fusedmm_csr(M, K, D, N, *s, A, B, C)}[op]
+    got = {}
+    for mode in "123":
+        monkeypatch.setenv("CSRK_MFMA", mode)
+        got[mode] = call()
+    assert torch.equal(got["1"], got["2"]) and not torch.equal(got["1"], got["3"])
