@@ -36,7 +36,8 @@
  *    floats), plus a few flag words; SDDMM needs the flag words only.  Where the
  *    matrix-core kernels are chosen (S dense enough and its number of entries known:
  *    planned calls, csrk_call), the dense operands in pieces: 6 bytes per element of A,
- *    B and C (2 for bfloat16), lengths rounded up to 32.  Three ways to provide it:
+ *    B and C (2 for bfloat16), lengths rounded up to 32, partial outputs likewise, and
+ *    2 bytes for each row, range and block of up to 256 columns.  Three ways to provide it:
  *      * spmm_csr / sddmm_csr / fusedmm_csr (and their planned and bfloat16 forms) use
  *        an area the library keeps per device.  It is allocated (hipMalloc, which
  *        synchronises) the first time it is needed, replaced when it has to grow (after
@@ -260,7 +261,9 @@ csrk_status csrk_plan_create(int M, int K, const int32_t *rowptr, const int32_t 
                              hipStream_t stream, csrk_plan **out);
 /*
  * Gives the plan a workspace of its own, large enough for spmm_csr_plan and fusedmm_csr_plan
- * with outputs of up to max_N columns (and for sddmm_csr_plan): allocates it here
+ * with outputs of up to max_N columns (and for sddmm_csr_plan), whichever kernels they take
+ * and with dot products of up to 128 elements (16384 x 16384, 512 columns: some 0.1 GB, most of
+ * it for the matrix-core kernels' operands in pieces): allocates it here
  * (hipMalloc; if the plan already had a smaller one, the device is synchronised and that one
  * freed), freed by csrk_plan_destroy.  Planned calls that fit into it use it instead of the
  * library's per-device area and then allocate nothing, never synchronise, take no lock and

@@ -8,12 +8,14 @@ of a function from here raises: there is no fallback path.
 
 The compute calls are made by the extension module `_torch_calls` (csrc/torch_calls.cpp)
 when their arguments are as they should be; what it turns down is done here step by
-step, with messages.
+step, with messages - and so is every call, at some 10 us more of host time, where the
+module is not built or belongs to another version of torch.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional, Tuple
 
 import torch
@@ -23,9 +25,11 @@ LIB_PATH = os.path.join(_HERE, "libcsrk.so")
 
 CSRK_OK = 0
 
-EXT_PATH = os.path.join(_HERE, "_torch_calls.so")
-
 _lib = None
+
+
+def _turned_down(*args):
+    return None
 
 
 def _call(*args):
@@ -46,14 +50,13 @@ class CsrkError(RuntimeError):
 
 
 def load(build_if_missing: bool = True):
-    """Load libcsrk.so and the extension module (building them first only if a file is absent)."""
+    """Load libcsrk.so (building it first only if the file is absent) and, if there is one, the extension module."""
     global _lib, _call, _call_plan
     if _lib is not None:
         return _lib
-    missing = [f for f in (LIB_PATH, EXT_PATH) if not os.path.exists(f)]
-    if missing:
+    if not os.path.exists(LIB_PATH):
         if not build_if_missing:
-            raise FileNotFoundError(f"{missing[0]} not built: run `python -m paper_2311_00368_amd.build`")
+            raise FileNotFoundError(f"{LIB_PATH} not built: run `python -m paper_2311_00368_amd.build`")
         from . import build as _build
         _build.build()
     lib = ctypes.CDLL(LIB_PATH)
@@ -97,8 +100,12 @@ def load(build_if_missing: bool = True):
         f.restype = ctypes.c_int
     lib.csrk_last_error.restype = ctypes.c_char_p
     lib.csrk_version.restype = ctypes.c_char_p
-    from . import _torch_calls
-    _call, _call_plan = _torch_calls.call, _torch_calls.call_plan
+    try:
+        from . import _torch_calls
+        _call, _call_plan = _torch_calls.call, _torch_calls.call_plan
+    except ImportError as e:        # not built, or for another torch: the same calls step by step
+        warnings.warn(f"calls go through ctypes, which takes longer: {e}; run `python -m paper_2311_00368_amd.build`")
+        _call = _call_plan = _turned_down
     _lib = lib
     return lib
 
