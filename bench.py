@@ -12,19 +12,22 @@ workload is the 16384 x 16384, 20 %-dense configuration the benchmark spec's target is
                + 2*nnz*(D+N) (FusedMM)
   ops          per operation, from one HIP-event pair around all kernels of a call: GFLOP/s (mean, median, best), the
                fractions of the published FP32 peak and HBM bandwidth (algorithmic bytes, and the bytes counted by
-               rocprofv3 in a recorded run of the same kernel: hbm_counter_*) and of the three machine
-               rates measured in this run (frac_*_measured), the rate at which gathered dense rows reach the ALUs
-               (nnz * width * 4 bytes / time), one cold run (caches flushed by writing a 1 GiB buffer) and the wall
-               time of the very first call (workspace allocation included)
+               rocprofv3 in a recorded run of the same kernels: hbm_counter_*) and of the machine
+               rates measured in this run (frac_*_measured), one cold run (caches flushed by writing a 1 GiB buffer) and
+               the wall time of the very first call (workspace allocation included).  `kernels` says whether the matrix-core
+               kernels or the vector kernels ran: of the first the rate of the bfloat16 products that they work through
+               (six for an FP32 one, over every cell of S) and its share of the published peak, of the second the rate at
+               which gathered dense rows reach the ALUs (nnz * width * 4 bytes / time)
   measured_peaks  the library's micro-benchmarks (csrk_microbench), run in this process before the timed region:
                device copy (GB/s), independent FP32 multiply-adds acc += x * y without packed FP32 (TFLOP/s), and
                conflict-free 128-bit LDS reads with 16 wavefronts per CU (TB/s)
-  roofline     the dominant kernel against MI355X's FP32 vector peak (157.3 TFLOP/s); `traffic` and
-               `traffic_source`: HBM bytes per launch from a recorded rocprofv3 --pmc run (profiles/), since
-               counters cannot be read from inside the process; `frac_of_lds_ceiling`: against the rate the
-               measured LDS read bandwidth allows (one 4-byte LDS operand per multiply-add)
-  phases       where the wavefronts of the dominant kernel spend their cycles (csrk_tile_phases: the measuring
-               build of the same kernel, shares of the summed phase counters)
+  roofline     the dominant operation against what bounds its kernels: the matrix cores' published bfloat16 peak (2.5
+               PFLOP/s dense), or for vector kernels the FP32 vector peak (157.3 TFLOP/s); `traffic` and
+               `traffic_source`: HBM bytes per call from a recorded rocprofv3 --pmc run (profiles/), since
+               counters cannot be read from inside the process; `frac_of_lds_ceiling` (vector kernels): against the rate
+               the measured LDS read bandwidth allows (one 4-byte LDS operand per multiply-add)
+  phases       where the wavefronts of the 512-column LDS-tiled kernels spend their cycles, for operations that these do
+               (csrk_tile_phases: the measuring build of the same kernel, shares of the summed phase counters)
   sddmm_at_scale  SDDMM at the benchmark size with D = 64 and D = 128
   cpu_baseline the FP64 CPU oracle timed on a sample of the rows of the same workload
   planned      the same three calls through a plan (pattern analysed once, outside the timing), timed after
@@ -44,6 +47,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
+BF16_MATRIX_PEAK_TFLOPS = 2500.0  # MI355X, published, dense
+PRODUCTS = 6                      # bfloat16 products that the matrix-core kernels make of an FP32 one
 FP32_VECTOR_PEAK_TFLOPS = 157.3   # MI355X, published: 256 CUs x 2.4 GHz x 256 flop/clk/CU
 HBM_PEAK_GBS = 8000.0             # MI355X, published
 # The rates this build's instruction mix can reach (plain multiply-adds, since packed FP32 is switched off; 128-bit LDS
@@ -54,7 +59,7 @@ KIND = {1: "spmm", 2: "sddmm", 3: "fusedmm"}
 
 
 def hbm_traffic_from_profiles(workload: str, kernel_key: str):
-    """HBM bytes per launch of the dominant kernel as measured by rocprofv3 --pmc (FETCH_SIZE / WRITE_SIZE, scaled
+    """HBM bytes per call of an operation as measured by rocprofv3 --pmc (FETCH_SIZE / WRITE_SIZE, scaled
     by a copy kernel) in a RECORDED run: counters cannot be read from inside this process, so the figure comes from
     the committed summary profiles/hbm_traffic_<workload>.json.  Returns (bytes or None, where it came from)."""
     path = os.path.join(ROOT, "profiles", f"hbm_traffic_{workload}.json")
@@ -84,7 +89,7 @@ def main():
     ap.set_defaults(plan=True)
     ap.add_argument("--bf16", action="store_true",
                     help="also time the bfloat16-operand entry points on the same workload, beside the FP32 general "
-                         "path they share their kernels with (adds a `bf16_operands` object to the line)")
+                         "path (adds a `bf16_operands` object to the line)")
     ap.add_argument("--no-microbench", action="store_true",
                     help="skip the library's machine-rate micro-benchmarks (`measured_peaks` and the frac_*_measured fields)")
     ap.add_argument("--no-phases", action="store_true",
@@ -198,6 +203,22 @@ def main():
     binding.csrk_profile_enable(0)
 
     ms_per_step = (t1 - t0) * 1e3 / args.steps
+    # which kernels did the calls: the last bits differ if it was not the vector kernels
+    outputs = {"spmm": lambda: O, "sddmm": lambda: P, "fusedmm": lambda: Of}
+    on_matrix_cores = {}
+    mfma_switch = os.environ.get("CSRK_MFMA")
+    for name, fn in ops:
+        fn()
+        first = outputs[name]().clone()
+        os.environ["CSRK_MFMA"] = "3"
+        fn()
+        on_matrix_cores[name] = not torch.equal(first, outputs[name]())
+        if mfma_switch is None:
+            del os.environ["CSRK_MFMA"]
+        else:
+            os.environ["CSRK_MFMA"] = mfma_switch
+    widths = {name: sum(v_ for k_, v_ in w.ops[name].items() if k_ in ("N", "D")) for name, _ in ops}
+    matrix_flops = {name: PRODUCTS * 2.0 * w.M * w.K * widths[name] for name, _ in ops}
     # one cold run per operation: a 1 GiB fill pushes the operands out of L2 and the 256 MB memory-side cache
     cold_ms = {}
     flush = torch.empty(1 << 28, dtype=torch.float32, device="cuda")
@@ -228,31 +249,48 @@ def main():
             "hbm_algorithmic_bytes": int(hbm_bytes[name]),
             "hbm_GBps": round(hbm_bytes[name] / avg / 1e6, 1),
             "frac_hbm_peak": round(hbm_bytes[name] / avg / 1e6 / HBM_PEAK_GBS, 4),
-            "gathered_TBps": round(gather_bytes[name] / avg / 1e9, 2),
+            "kernels": "matrix cores" if on_matrix_cores[name] else "vector",
         }
+        if on_matrix_cores[name]:
+            op_report[name]["matrix_core_TFLOPs"] = round(matrix_flops[name] / avg / 1e9, 1)
+            op_report[name]["frac_bf16_peak"] = round(matrix_flops[name] / avg / 1e9 / BF16_MATRIX_PEAK_TFLOPS, 4)
+        else:
+            op_report[name]["gathered_TBps"] = round(gather_bytes[name] / avg / 1e9, 2)
         counted, _ = hbm_traffic_from_profiles(args.workload, name)
-        if counted:         # FETCH_SIZE + WRITE_SIZE of a recorded rocprofv3 --pmc run of the same kernel
+        if counted:         # FETCH_SIZE + WRITE_SIZE of a recorded rocprofv3 --pmc run of the same kernels
             op_report[name]["hbm_counter_bytes"] = int(counted)
             op_report[name]["hbm_counter_GBps"] = round(counted / avg / 1e6, 1)
             op_report[name]["frac_hbm_peak_counter"] = round(counted / avg / 1e6 / HBM_PEAK_GBS, 4)
         if peaks:
-            op_report[name]["frac_fma_measured"] = round(tf / peaks["fma_f32_TFLOPs"], 4)
             op_report[name]["frac_hbm_copy_measured"] = round(hbm_bytes[name] / avg / 1e6 / peaks["hbm_copy_GBps"], 4)
-            op_report[name]["frac_lds_read_measured"] = round(gather_bytes[name] / avg / 1e9 / peaks["lds_read_b128_TBps"], 4)
+            if not on_matrix_cores[name]:
+                op_report[name]["frac_fma_measured"] = round(tf / peaks["fma_f32_TFLOPs"], 4)
+                op_report[name]["frac_lds_read_measured"] = round(gather_bytes[name] / avg / 1e9 / peaks["lds_read_b128_TBps"], 4)
     # dominant kernel = the one the step spends most time in
     dom = max(per_op, key=lambda k: float(np.mean(per_op[k])))
     dom_ms = float(np.mean(per_op[dom]))
     achieved = flops[dom] / dom_ms / 1e9      # TFLOP/s
     traffic, traffic_source = hbm_traffic_from_profiles(args.workload, dom)
-    roofline = {
-        "kernel": dom, "bound": "alu", "achieved": round(achieved, 3), "peak": FP32_VECTOR_PEAK_TFLOPS,
-        "unit": "TFLOP/s", "frac": round(achieved / FP32_VECTOR_PEAK_TFLOPS, 4),
-        "traffic": traffic, "traffic_source": traffic_source,
-        "flops_per_launch": flops[dom], "avg_launch_ms": round(dom_ms, 4),
-        "ceiling_note": "peak is the published FP32 vector rate; every multiply-add of the method needs its own 4 "
-                        "bytes of a gathered dense row from LDS, so the kernel's own ceiling is the LDS read rate "
-                        "(measured_peaks.lds_read_b128_TBps / 4 bytes x 2 flops), well below the ALU peak",
-    }
+    if on_matrix_cores[dom]:
+        rate = matrix_flops[dom] / dom_ms / 1e9
+        roofline = {
+            "kernel": dom, "bound": "mfma", "achieved": round(rate, 1), "peak": BF16_MATRIX_PEAK_TFLOPS,
+            "unit": "TFLOP/s", "frac": round(rate / BF16_MATRIX_PEAK_TFLOPS, 4),
+            "useful_TFLOPs": round(achieved, 3),
+            "ceiling_note": "rate of the bfloat16 products that the matrix cores work through: six for an FP32 product, over every "
+                            "cell of S (stored or not); useful_TFLOPs counts 2 flops per stored entry and column; the peak "
+                            "is the published dense one at 2.4 GHz, the clock under this load is 2.0 GHz (power)",
+        }
+    else:
+        roofline = {
+            "kernel": dom, "bound": "alu", "achieved": round(achieved, 3), "peak": FP32_VECTOR_PEAK_TFLOPS,
+            "unit": "TFLOP/s", "frac": round(achieved / FP32_VECTOR_PEAK_TFLOPS, 4),
+            "ceiling_note": "peak is the published FP32 vector rate; every multiply-add of the vector kernels needs its own 4 "
+                            "bytes of a gathered dense row from LDS, so their own ceiling is the LDS read rate "
+                            "(measured_peaks.lds_read_b128_TBps / 4 bytes x 2 flops), well below the ALU peak",
+        }
+    roofline.update({"traffic": traffic, "traffic_source": traffic_source, "flops_per_launch": flops[dom],
+                     "avg_launch_ms": round(dom_ms, 4)})
 
     result = {
         "metric": "GFLOP/s (2*nnz*N) for SPMM + SDDMM + FusedMM, one pass each",
@@ -272,18 +310,23 @@ def main():
     }
     if peaks:
         result["measured_peaks"] = peaks
-        result["roofline"]["frac_of_lds_ceiling"] = round(achieved / (peaks["lds_read_b128_TBps"] / 4.0 * 2.0), 4)
+        if not on_matrix_cores[dom]:
+            result["roofline"]["frac_of_lds_ceiling"] = round(achieved / (peaks["lds_read_b128_TBps"] / 4.0 * 2.0), 4)
 
     if not args.no_phases and "fusedmm" in w.ops and w.ops["fusedmm"]["N"] == 512 and w.ops["fusedmm"]["D"] == 64 \
             and w.M % 64 == 0:
-        # where a wavefront's cycles go in the two 512-column tiled kernels (measuring builds, one run each)
+        # where a wavefront's cycles go in the two 512-column tiled kernels (measuring builds, one run each), where these
+        # do the call
         ph = {}
         for opname, opcode in (("spmm", binding.CSRK_OP_SPMM), ("fusedmm", binding.CSRK_OP_FUSEDMM)):
+            if on_matrix_cores.get(opname, True):
+                continue
             cyc, tiles, _ = binding.csrk_tile_phases(opcode, w.M, w.K, 64, 512, rp, ci, v, Af, Bf, Cf, Of)
             total = sum(cyc)
             ph[opname] = {"tiles_per_wavefront": tiles, "cycles_per_wavefront": round(total),
                           "share": {n: round(c / total, 4) for n, c in zip(binding.PHASE_NAMES, cyc) if c > 0}}
-        result["phases"] = ph
+        if ph:
+            result["phases"] = ph
 
     if not args.no_sddmm_at_scale:
         # SDDMM alone at this size with both dot lengths of the workloads (the paper times SDDMM on its own too)
@@ -372,9 +415,9 @@ def main():
                                      "analysis and the stand-by launches behind a tiled kernel"}
 
     if args.bf16:
-        # the paper's stated future work: dense operands in bfloat16, FP32 arithmetic.  Same workload; the
-        # bfloat16 calls run the general kernels, so the like-for-like FP32 figure is the general path
-        # (CSRK_KTILE=3, CSRK_ROWS as chosen) - the default FP32 figures above are the LDS-tiled kernels'.
+        # the paper's stated future work: dense operands in bfloat16, FP32 arithmetic.  Same workload; beside them the
+        # FP32 general path (CSRK_KTILE=3, which also keeps the matrix-core kernels out), whose kernels they share where
+        # they do not run on the matrix cores.
         def to_dev_bf16(a):
             bits, _ = inputs.to_bf16(a)
             return torch.from_numpy(bits.view(np.int16)).cuda().view(torch.bfloat16)
@@ -419,7 +462,7 @@ def main():
         else:
             os.environ["CSRK_KTILE"] = saved
         result["bf16_operands"] = {"bf16": r16, "fp32_general_path": r32,
-                                   "note": "whole calls; bf16 entry points and the FP32 general path share their kernels"}
+                                   "note": "whole calls; the bf16 ones on the matrix cores where the library chooses these"}
 
     if not args.no_cpu_baseline:
         import oracle
