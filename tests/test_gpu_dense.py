@@ -332,3 +332,45 @@ def test_choice_with_unaligned_operands(csrk, monkeypatch, op, M, K, D, N):
         monkeypatch.setenv("CSRK_MFMA", mode)
         got[mode] = call()
     assert torch.equal(got["1"], got["2"]) and not torch.equal(got["1"], got["3"])
+
+
+@pytest.mark.parametrize("M,K,D,N", [(400, 900, 64, 48), (33000, 200, 40, 33)])
+def test_graph_replays_with_other_values(csrk, monkeypatch, M, K, D, N):
+    # one captured call of each operation, replayed on operands that have nothing special in them, then something to be done
+    # again, then nothing again: what a call leaves in its workspace says nothing to the next one
+    monkeypatch.setenv("CSRK_MFMA", "2")
+    rng = np.random.default_rng(M)
+    rp, ci = pattern(rng, M, K, 0.3, "unsorted" if M < 1000 else "even")
+    s = dev(rp), dev(ci), dev(rng.uniform(-1, 1, len(ci)).astype(np.float32))
+    A, B, C = (dev(rng.normal(size=n).astype(np.float32)) for n in ((M, D), (K, D), (K, N)))
+    ws = [torch.empty(csrk.csrk_workspace_bytes(op, M, K, N, D), dtype=torch.uint8, device="cuda") for op in (1, 2, 3)]
+    out = [torch.empty(n, dtype=torch.float32, device="cuda") for n in ((M, N), (len(ci),), (M, N))]
+
+    def calls(O, P, F):
+        csrk.spmm_csr_ws(M, K, N, *s, C, ws[0], O)
+        csrk.sddmm_csr_ws(M, K, D, *s, A, B, ws[1], P)
+        csrk.fusedmm_csr_ws(M, K, D, N, *s, A, B, C, ws[2], F)
+
+    calls(*out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        calls(*out)
+    for special in (None, (B, 3), None, (C, 5), (A, 7), None):
+        if special:
+            x, at = special
+            kept = x.view(-1)[at * x.shape[1]].clone()
+            x.view(-1)[at * x.shape[1]] = float("nan")
+        graph.replay()
+        torch.cuda.synchronize()
+        replayed = [x.clone() for x in out]
+        eager = [torch.empty_like(x) for x in out]
+        calls(*eager)
+        torch.cuda.synchronize()
+        for a, b in zip(replayed, eager):
+            assert torch.equal(a.nan_to_num(nan=1e30), b.nan_to_num(nan=1e30))
+        if special:
+            assert torch.isnan(replayed[2]).any()
+            x.view(-1)[at * x.shape[1]] = kept
+        else:
+            assert not any(torch.isnan(a).any() for a in replayed)
