@@ -95,7 +95,8 @@ csrk_status spmm_csr(int M, int K, int N,
  * P may alias vals (P == vals: the values are overwritten in place, as in the
  * paper's Algorithm 1); such a call keeps to the kernels that need no second
  * pass over vals - the LDS-tiled kernel only through sddmm_csr_plan, whose plan
- * vouches for the column order.  Partly overlapping P and vals are not allowed.
+ * vouches for the column order, and the matrix-core kernel, which computes no entry
+ * twice.  Partly overlapping P and vals are not allowed.
  */
 csrk_status sddmm_csr(int M, int K, int D,
                       const int32_t *rowptr, const int32_t *colidx, const float *vals,

@@ -55,12 +55,15 @@ __device__ __forceinline__ void special_segment(const DenseArgs &a, int row, int
 
 // VEC: elements per access of the dense operands (1, or 128 bits); a column block has up to LG * VEC columns (VEC == 1: it
 // is done 64 columns at a time).  A workgroup's time for a long row is that of its loads one after the other, so few lanes
-// take an entry and many entries are under way: 8 lanes of 16 elements for a dot product, 8 floats of a lane for the sums.
+// take an entry and many entries are under way: 8 elements of a lane for a dot product, 8 floats of a lane for the sums.  (16
+// elements of FP32 rows of more than 64 took 165 registers, and 652 instead of 577 us where no row of FusedMM 16384 x 4096,
+// 20 %, 128/128 is ordered.)
 template <typename E, bool FUSED, int VEC, int LG>
 __global__ __launch_bounds__(kBlockThreads) void dense_finish(DenseArgs a) {
     constexpr int PL = 16 / VEC;                            // lanes for a 16-column piece
     constexpr int BL = VEC == 1 ? 16 : VEC == 4 ? LG / 2 : LG, BT = LG / BL;    // ... for a block, and tiles of theirs
-    constexpr int DL = VEC == 1 ? 16 : 8, DT = 128 / (DL * VEC);    // ... for a dot product of up to 128 elements
+    constexpr int DL = 16, DT = 128 / (DL * VEC);           // ... for a dot product of up to 128 elements, and tiles of theirs
+    constexpr int SL = VEC == 1 ? 16 : 8, ST = 64 / (SL * VEC);     // ... of up to 64
     __shared__ union {
         RowParts<VEC, LG, 1> whole;
         RowParts<VEC, BL, BT> block;
@@ -115,9 +118,10 @@ __global__ __launch_bounds__(kBlockThreads) void dense_finish(DenseArgs a) {
             constexpr int LN = decltype(lanes)::value, TN = decltype(tiles)::value;
             float acc[TN][VEC] = {};
             if constexpr (FUSED) {
-                const int d = lane % DL * VEC;
-                if (a.D <= 64) fused_segment<VEC, DL, DT / 2, VEC, LN, TN>(row, s0, s1, a.colidx, a.vals, A, B, C, a.D, N, d, n, slots[wave], acc);
-                else fused_segment<VEC, DL, DT, VEC, LN, TN>(row, s0, s1, a.colidx, a.vals, A, B, C, a.D, N, d, n, slots[wave], acc);
+                if (a.D <= 64)
+                    fused_segment<VEC, SL, ST, VEC, LN, TN>(row, s0, s1, a.colidx, a.vals, A, B, C, a.D, N, lane % SL * VEC, n, slots[wave], acc);
+                else
+                    fused_segment<VEC, DL, DT, VEC, LN, TN>(row, s0, s1, a.colidx, a.vals, A, B, C, a.D, N, lane % DL * VEC, n, slots[wave], acc);
             } else
                 spmm_segment<VEC, LN, TN>(s0, s1, a.colidx, a.vals, C, N, n, acc);
             fold_groups<VEC, LN, TN>(acc);
