@@ -3,7 +3,7 @@
 
 #include <atomic>
 
-#include "kernels_dense.hpp"
+#include "kernels_dense_wide.hpp"
 
 namespace csrk {
 namespace {
@@ -13,6 +13,14 @@ constexpr int kMaxWidth = 2048, kMaxDot = 128, kMaxK = 1 << 20;
 constexpr size_t kView = 0xe0000000ull;
 constexpr int kMaxRows = 1 << 26;
 constexpr long long kMaxGroups = 1 << 22;
+
+// Ranges of K from this length on are done in half-precision pieces where blocks of 192 or 256 columns of FP32 are the best
+// choice (narrower blocks add up their sums on the way and are the more exact).  Shorter ranges would not be: the error in the
+// 2-norm against FP64, six products of bfloat16 / three of halves, is 4.2e-7 / 3.6e-7 at 16384^2, 20 %, 512 columns, 1.8e-7 /
+// 1.6e-7 at 16384 x 8192, 10 %, but 1.36e-7 / 1.41e-7 at 8192^2, log-normal rows, 256 columns, in ranges of 2048, and putting
+// the sums away (8 times 4 us or so) would weigh more.  A tile takes 1.5 us with 16 pieces and 1.4 with 12.
+constexpr int kHalvesK = 8192;
+constexpr double kHalvesTileUs = 1.5;
 
 // SDDMM's tiles: 128 columns where they and B's fit LDS, for the entries of a row in a tile fill the 16 lanes better
 constexpr int sddmm_kt(int ds) { return ds == 1 ? 128 : 64; }
@@ -29,10 +37,11 @@ int prepare_blocks(size_t units) {
 
 // where everything lies in the scratch area
 struct Layout {
-    size_t c, b, a, todo, met, special, redo, cuts, partial, bytes;
+    size_t c, b, a, todo, exponents, met, special, tiny, redo, zeros, cuts, partial, bytes;
     int n_tiles, c_blocks, b_blocks, a_blocks;
     Layout(const DenseShape &s, const DenseConfig &cfg) {
-        const size_t pieces = s.bf16 ? 2 : 6;       // bytes of a prepared value
+        const bool halves = cfg.halves;
+        const size_t pieces = s.bf16 ? 2 : halves ? 4 : 6;      // bytes of a prepared value
         const int bn = cfg.ct * 16;
         n_tiles = s.op == kDenseSddmm ? 0 : (s.N + bn - 1) / bn * cfg.ct;
         const size_t d = (size_t)cfg.ds * 32, k = up32(s.K), octs = cfg.ds == 3 ? 16 : cfg.ds * 4;
@@ -49,10 +58,13 @@ struct Layout {
         // (whole tiles of SDDMM's columns)
         b = take((k + kSddmmMaxKt - 32) * d * pieces);
         a = take(up32(s.M) * d * pieces);
-        todo = take(8);
+        todo = take(16);
+        exponents = take(halves ? 8 : 0);
+        tiny = take(halves ? (size_t)c_blocks * 4 : 0);
         met = take(s.op == kDenseFused ? (size_t)b_blocks * 4 : 0);
         special = take(s.op == kDenseFused ? k : 0);
         redo = take(s.op != kDenseSddmm ? (size_t)cfg.segs * (n_tiles / cfg.ct) * s.M * 2 : 0);
+        zeros = take(halves ? (size_t)cfg.segs * (n_tiles / cfg.ct) * s.M * 2 : 0);
         cuts = take(cfg.segs > 1 ? (size_t)(cfg.segs - 1) * s.M * 4 : 0);
         partial = take(cfg.segs > 1 && s.op != kDenseSddmm ? (size_t)cfg.segs * s.M * s.N * 4 : 0);
         bytes = at;
@@ -65,6 +77,12 @@ DenseKernel spmm_kernel(int ct) {
     if (ct == CT) return {dense_kernel<CT, 0, P>, DenseCfg<CT, 0, P>::kBytes};
     CSRK_DENSE_CT(CSRK_DENSE_CASE)
 #undef CSRK_DENSE_CASE
+    return {nullptr, 0};
+}
+
+DenseKernel wide_kernel(int ct) {
+    if (ct == 12) return {dense_wide_kernel<12>, WideCfg<12>::kBytes};
+    if (ct == 16) return {dense_wide_kernel<16>, WideCfg<16>::kBytes};
     return {nullptr, 0};
 }
 
@@ -129,6 +147,11 @@ bool dense_config(const DenseShape &s, int cus, DenseConfig *out) {
         }
     }
     if (best.ct == 0) return false;
+    if (s.op == kDenseSpmm && !s.bf16 && best.ct > 8 && best.seg_k >= kHalvesK) {
+        const long long rounds = (row_blocks * ((s.N + best.ct * 16 - 1) / (best.ct * 16)) * best.segs + cus - 1) / cus;
+        best.halves = true;
+        best.us -= (double)rounds * (best.seg_k / 32 * (tile_us(s, best.ct, 0) - kHalvesTileUs) - 24.0);
+    }
     const Layout l(s, best);
     best.bytes = l.bytes;
     best.us += (double)l.partial / 2.0e6;           // the operands' preparation
@@ -172,26 +195,33 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
     }
     if (s.op != kDenseSddmm) a.todo = reinterpret_cast<int32_t *>(base + l.todo);
     a.redo = reinterpret_cast<uint16_t *>(base + l.redo);
+    if (c.halves) {
+        a.exponents = reinterpret_cast<int32_t *>(base + l.exponents);
+        a.tiny_met = reinterpret_cast<int32_t *>(base + l.tiny);
+        a.zeros = reinterpret_cast<uint16_t *>(base + l.zeros);
+    }
     a.cuts = reinterpret_cast<int32_t *>(base + l.cuts);
 
-    const DenseKernel k = s.op == kDenseSpmm    ? (s.bf16 ? spmm_kernel<1>(c.ct) : spmm_kernel<3>(c.ct))
+    const DenseKernel k = c.halves              ? wide_kernel(c.ct)
+                          : s.op == kDenseSpmm  ? (s.bf16 ? spmm_kernel<1>(c.ct) : spmm_kernel<3>(c.ct))
                           : s.op == kDenseSddmm ? (s.bf16 ? sddmm_kernel<1>(c.ds) : sddmm_kernel<3>(c.ds))
                                                 : (s.bf16 ? dense_fused_kernel_bf16(c.ct, c.ds) : dense_fused_kernel_f32(c.ct, c.ds));
     if (!k.fn) return hipErrorInvalidValue;
     {
         // once per kernel and device (harmless if two threads do it)
-        static std::atomic<uint64_t> done[3][2][17][5];
+        static std::atomic<uint64_t> done[3][3][17][5];
         int dev = 0;
         if (hipError_t e = hipGetDevice(&dev)) return e;
-        std::atomic<uint64_t> &seen = done[s.op][s.bf16][c.ct][c.ds];
+        std::atomic<uint64_t> &seen = done[s.op][s.bf16 ? 1 : c.halves ? 2 : 0][c.ct][c.ds];
         const uint64_t bit = 1ull << (dev & 63);
         if (!(seen.load(std::memory_order_acquire) & bit)) {
             if (hipError_t e = hipFuncSetAttribute((const void *)k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, k.lds_bytes)) return e;
             seen.fetch_or(bit, std::memory_order_release);
         }
     }
-    const int prepare = a.c_blocks + a.b_blocks + a.a_blocks + (a.segs > 1 ? (a.M + kDenseCutRows - 1) / kDenseCutRows : 0);
+    const int prepare = a.c_blocks + a.b_blocks + a.a_blocks + (a.segs > 1 ? (a.M + kDenseCutRows - 1) / kDenseCutRows : 0) + (c.halves ? 1 : 0);
     if (s.bf16) hipLaunchKernelGGL(dense_prepare_kernel<bf16_t>, dim3(prepare), dim3(256), 0, stream, a);
+    else if (c.halves) hipLaunchKernelGGL((dense_prepare_kernel<float, true>), dim3(prepare), dim3(256), 0, stream, a);
     else hipLaunchKernelGGL(dense_prepare_kernel<float>, dim3(prepare), dim3(256), 0, stream, a);
     hipLaunchKernelGGL(k.fn, dim3((unsigned)a.row_blocks * a.col_blocks * a.segs), dim3(kDenseThreads), k.lds_bytes, stream, a);
     if (s.op != kDenseSddmm) {
@@ -199,7 +229,7 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
         uintptr_t at = reinterpret_cast<uintptr_t>(out) | reinterpret_cast<uintptr_t>(C);
         if (s.op == kDenseFused) at |= reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B);
         const bool vec = a.N % unit == 0 && a.D % unit == 0 && (at & 15u) == 0;
-        const DenseKernel f = dense_finish_kernel(s.bf16, s.op == kDenseFused, vec, c.ct);
+        const DenseKernel f = dense_finish_kernel(s.bf16, s.op == kDenseFused, vec, c.ct, c.halves);
         if (!f.fn) return hipErrorInvalidValue;
         // not many more workgroups than the chip holds at a time (2048 of FusedMM's: 6.8 instead of 5.8 us for the sums of
         // 16384 x 4096, 128 columns, in 2 ranges), and with long rows to do again some to choose from

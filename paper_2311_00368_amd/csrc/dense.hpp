@@ -22,6 +22,7 @@ struct DenseConfig {
     int ct;                 // 16-column pieces of the output per workgroup
     int ds;                 // 32-element steps of the dot products
     int segs, seg_k;        // K in `segs` ranges of `seg_k` columns
+    bool halves;            // FP32 in half-precision pieces (kernels_dense_wide.hpp)
     double us;              // what the call is expected to take
     size_t bytes;           // of scratch
 };
@@ -41,6 +42,6 @@ struct DenseKernel {
 DenseKernel dense_fused_kernel_f32(int ct, int ds);
 DenseKernel dense_fused_kernel_bf16(int ct, int ds);
 // `vec`: 128-bit accesses of all dense operands and the output
-DenseKernel dense_finish_kernel(bool bf16, bool fused, bool vec, int ct);
+DenseKernel dense_finish_kernel(bool bf16, bool fused, bool vec, int ct, bool halves);
 
 }  // namespace csrk

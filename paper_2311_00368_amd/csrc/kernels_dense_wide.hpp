@@ -1,0 +1,312 @@
+// Matrix-core SPMM for wide outputs: FP32 in two half-precision pieces, 32 rows of S per wavefront.
+//
+// A float of 24 bits is h + l to 23 bits and a sign, h and l of 11 bits each (Ootomo and Yokota, "Recovering single precision
+// accuracy from Tensor Cores while surpassing the FP32 theoretical peak performance", 2022, whose scaling of the smaller piece
+// by 2^11 is used here): three products s_h c_h, s_h c_l + s_l c_h instead of the six of three bfloat16 pieces, two thirds of
+// the bytes of C in LDS, and half a dozen instructions less for every cell of S, since S's values are split where they are
+// scattered and not where they are read.  What that costs:
+//
+// - Range.  Half precision has exponents from 2^-14 (2^-24) to 2^15, so S's values and C are multiplied by powers of two that
+//   bring the largest of 1024 sampled values of each to [2^8, 2^9).  Magnitudes of 2^16 and more become infinities, which show
+//   in every result that they are part of; values below 2^-12 lose bits, 2^-36 of them at most.  So a result is computed again,
+//   by the finishing kernel, where it is not finite or where its magnitude (scaled) is below 1, which neither values of the
+//   sampled size nor sums of their products are but for one in 10^5 or fewer (one product of two uniform values: 10^-4); and results that are exactly zero where C
+//   or the row of S has values that the larger piece loses altogether (rows without entries aside).
+// - Rounding of sums.  Products of bfloat16 pieces have 16 bits and mostly add up exactly inside an instruction; these have 22,
+//   and long sums are 1.75 times as far from FP64.  So the sums are put away in memory on the way, three times where rows are
+//   long (error at 16384^2, 20 %: 0.86 times that of the six products in one accumulator, which is rounded the less the fewer
+//   entries a tile has) and seven times elsewhere (16384 x 8192, 10 %: 0.91, with three 1.19).
+//
+// A workgroup is 8 wavefronts, 128 rows and CT * 16 columns: a pair of wavefronts shares 32 rows, each has half of the columns
+// (two rows' fragments for every read of C's pieces: 2 reads per 6 products; with 16 rows, 2 per 3, the reads bound the kernel).
+// Every wavefront scatters 16 rows' entries into the tile that its pair reads.  C's tiles go to LDS directly, three buffers, two
+// tiles ahead; S's tiles are scattered two tiles ahead in two buffers; one barrier per tile.
+//
+// Measured on MI355X, six products of bfloat16 pieces / this: SPMM 16384^2, 20 %, N = 512 1194 / 760 us, 16384 x 8192, 10 %, 512
+// 662 / 436, 32768 x 8192, 20 %, 192 590 / 390.  Bound by latency: of the 3000 cycles of a tile the matrix cores are busy for
+// half; the wavefronts that come second on their SIMD take 770 + 1065 cycles for the products, 670 for S, 200 to ask for
+// loads, 215 for the fragments (the first ones wait for them at the barrier).  What gave nothing: S between the matrix
+// instructions (780-940 us), four of the wavefronts with S before the products and four behind (756), entries of two halves of
+// the range in turn, so that loads are under way for two tiles (908), priorities, 128 columns and 4 wavefronts per SIMD (880).
+#pragma once
+#include "kernels_dense.hpp"
+
+namespace csrk {
+
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ f32x4 mfma(f16x8 a, f16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
+
+// scaled results below this are computed again
+constexpr float kWideSmall = 1.f;
+// mean entries of a row in a range from which on the sums are put away three times on the way and not seven
+constexpr int kWideLongRow = 2400;
+
+template <int CT>
+struct WideCfg {
+    static constexpr int BN = CT * 16, PW = CT / 2;     // columns of a block, 16-column pieces of a wavefront
+    static constexpr int kS = kDenseBM * kSRow;         // bytes of a tile of S
+    static constexpr int kC = CT * 2048;                // ... and of C
+    static constexpr int kIssue = kC / (kDenseThreads * 16);
+    static constexpr int kOffS = 3 * kC;
+    static constexpr int kOffCount = kOffS + 2 * kS;
+    static constexpr int kOffMarks = kOffCount + kDenseWaves * 4;
+    static constexpr int kBytes = kOffMarks + 2 * kDenseBM * 4;
+    static_assert(CT % 4 == 0 && kBytes <= 160 * 1024, "LDS of a gfx950 CU");
+};
+
+template <int CT>
+__global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs a) {
+    using L = WideCfg<CT>;
+    constexpr int PW = L::PW;
+    extern __shared__ __attribute__((aligned(16))) char dlds[];
+    const int M = a.M, K = a.K, N = a.N;
+    const int lane = lane_id();
+    const int wave = uniform(threadIdx.x >> 6);
+    const DenseJob job = dense_job(a);
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)dlds;
+
+    // part i of C's tile to LDS (tiles past the last one read as zeros: the uniform part of the address stops at the view's end)
+    const unsigned c_step = (unsigned)a.n_tiles * 2048u, c_end = (unsigned)((K + kDenseK - 1) / kDenseK) * c_step;
+    const DenseView cview = dense_view(a.Cp, c_end);
+    const unsigned c_off = (unsigned)job.cb * L::kC + threadIdx.x * 16u;
+    auto issue_c = [&](int k0, int buf, int i) CSRK_INLINE {
+        const unsigned tile = (unsigned)(k0 / kDenseK) * c_step, at = (tile < c_end ? tile : c_end) + i * kDenseThreads * 16;
+        const unsigned to = lds0 + buf * L::kC + wave * 1024u + i * kDenseThreads * 16;
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                     :: "s"(to), "v"(c_off), "s"(cview.rsrc), "s"(at) : "memory");
+    };
+#pragma unroll
+    for (int i = 0; i < 2 * L::kIssue; ++i) issue_c(job.kb + i / L::kIssue * kDenseK, i / L::kIssue, i % L::kIssue);
+
+    Entries<true> e;
+    int several;                // rows with more than one entry
+    {
+        const unsigned bytes = dense_entry_bytes(a, job);
+        e.cols = dense_view(job.ci, bytes);
+        e.vals = dense_view(a.vals ? (const void *)(a.vals + job.e0) : (const void *)job.ci, a.vals ? bytes : 0u);
+        e.scale = power_of_two(uniform(a.exponents[0]));
+        e.one = a.vals ? 0.f : e.scale;
+        e.q4 = (lane & 3) * 4;
+        e.ke = job.ke;
+        e.bad = 0;
+        const int2 range = dense_row_range(a, job, wave * kDenseRows + (lane >> 2));
+        e.pos = range.x;
+        e.end = range.y;
+        several = (int)__popcll(__ballot(range.y - range.x > 1)) / 4;
+        e.load();
+    }
+    char *const swave = dlds + L::kOffS + wave * kSWave;
+    const unsigned row_at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)(swave + (lane >> 2) * kSRow);
+    const unsigned dump = kDenseK * 4u + (lane & 3) * 4u;
+    char *const zero_at = swave + (lane >> 3) * kSRow + (lane & 7) * 16;
+    auto bring = [&](int k0, int buf) CSRK_INLINE {
+        const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 2; ++i) *reinterpret_cast<f32x4 *>(zero_at + buf * L::kS + i * 8 * kSRow) = z;
+        e.row_at = row_at + buf * L::kS;
+        e.dump = e.row_at + dump;
+        e.template place<true>(k0, false);
+    };
+
+    // 32 rows of S as fragments: [rows / 16][larger and smaller pieces]
+    const int pair = wave >> 1, half = wave & 1;
+    const char *const sfrag = dlds + L::kOffS + (pair * 32 + (lane & 15)) * kSRow + (lane >> 4) * 16;
+    f16x8 s[2][2];
+    auto fetch = [&](int buf) CSRK_INLINE {
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            u32x4 x[2], h, l;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) x[i] = *reinterpret_cast<const u32x4 *>(sfrag + buf * L::kS + r * 16 * kSRow + i * 64);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                h[i] = lower_halves(x[i >> 1][(i & 1) * 2], x[i >> 1][(i & 1) * 2 + 1]);
+                l[i] = upper_halves(x[i >> 1][(i & 1) * 2], x[i >> 1][(i & 1) * 2 + 1]);
+            }
+            s[r][0] = __builtin_bit_cast(f16x8, h);
+            s[r][1] = __builtin_bit_cast(f16x8, l);
+        }
+    };
+    const char *const cfrag = dlds + half * (PW * 2048) + lane * 16;
+    auto piece = [&](int buf, int t, f16x8 (&b)[2]) CSRK_INLINE {
+#pragma unroll
+        for (int p = 0; p < 2; ++p) b[p] = *reinterpret_cast<const f16x8 *>(cfrag + buf * L::kC + (t * 2 + p) * 1024);
+    };
+    f32x4 acc[2][PW], low[2][PW];       // the products of the larger pieces, the others times 2^11
+    auto clear = [&]() CSRK_INLINE {
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int t = 0; t < PW; ++t) acc[r][t] = low[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    clear();
+
+    // which pieces of which rows are to be computed again, and which have zeros; every workgroup's last word
+    unsigned *const marks = reinterpret_cast<unsigned *>(dlds + L::kOffMarks), *const zeros = marks + kDenseBM;
+    if (threadIdx.x < kDenseBM) marks[threadIdx.x] = zeros[threadIdx.x] = 0;
+    auto say = [&](unsigned again, unsigned zero) CSRK_INLINE {
+        const int t = threadIdx.x, row = job.row0 + t;
+        if (t < kDenseBM && row < M) {
+            if (zero != 0) {            // (rows without entries have nothing but)
+                const int2 range = dense_row_range(a, job, t);
+                if (range.x >= range.y) zero = 0;
+            }
+            const size_t at = ((size_t)job.seg * a.col_blocks + job.cb) * M + row;
+            a.redo[at] = (uint16_t)again;
+            a.zeros[at] = (uint16_t)zero;
+            // (plain stores of the same word: see kernels_dense.hpp)
+            if (again != 0) a.todo[0] = 1;
+            if (zero != 0) a.todo[2] = 1;
+        }
+        for (int i = blockIdx.x * kDenseThreads + t; i < a.c_blocks; i += gridDim.x * kDenseThreads)
+            if (a.tiny_met[i] != 0) a.todo[3] = 1;
+    };
+
+    // The results, scaled: what is put away in memory, and what has been.
+    float *const out = (a.segs > 1 ? a.partial + (size_t)job.seg * M * N : a.O) + (size_t)job.row0 * N;
+    const unsigned ld_b = (unsigned)N * 4u;
+    const DenseView oview = dense_view(out, (unsigned)(M - job.row0 < kDenseBM ? M - job.row0 : kDenseBM) * ld_b);
+    // lane l holds column l & 15 of each 16-column piece, rows 4 (l / 16) + i; rows past M and columns past N fall outside the view
+    auto column_at = [&](int t) CSRK_INLINE {
+        const int l = lane_id_again(), col = job.cb * L::BN + (half * PW + t) * 16 + (l & 15);
+        return col < N ? (unsigned)(l >> 4) * 4u * ld_b + (unsigned)col * 4u : 0xf0000000u;
+    };
+    auto row_offset = [&](int r, int i) CSRK_INLINE { return (unsigned)(pair * 32 + r * 16 + i) * ld_b; };
+    auto result = [&](int r, int t, int i) CSRK_INLINE { return fmaf(low[r][t][i], 1.f / kHalfLow, acc[r][t][i]); };
+    auto add_earlier = [&]() CSRK_INLINE {
+#pragma unroll
+        for (int g = 0; g < PW; g += 2) {
+            float y[2][2][4];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const unsigned o = column_at(g + t);
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        y[r][t][i] = float_of(__builtin_amdgcn_raw_buffer_load_b32(oview.rsrc, o, row_offset(r, i), 0));
+            }
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        acc[r][g + t][i] = y[r][t][i] + result(r, g + t, i);
+                        low[r][g + t][i] = 0.f;
+                    }
+        }
+    };
+
+    bring(job.kb, 0);
+    e.rest(job.kb);
+    bring(job.kb + kDenseK, 1);
+    e.rest(job.kb + kDenseK);
+    i32x4 *const counts = reinterpret_cast<i32x4 *>(dlds + L::kOffCount);
+    {
+        unsigned long long rows = e.bad | e.bad >> 1;
+        rows = (rows | rows >> 2) & 0x1111111111111111ull;
+        if (lane == 0) reinterpret_cast<int *>(counts)[wave] = 2 * (int)__popcll(rows) - several;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    {
+        // (half of the rows with more than one entry out of order: see kernels_dense.hpp)
+        const i32x4 n = counts[0] + counts[1];
+        if (uniform(n[0] + n[1] + n[2] + n[3]) > 0) return say(0xffffu, 0u);
+    }
+    fetch(0);
+    __syncthreads();
+    int cbuf = 0, put_away = 0;
+    // tiles until the sums are put away (neighbouring workgroups at different times: all at once, 872 instead of 834 us)
+    const int parts = (long long)uniform(a.rowptr[M]) >= (long long)kWideLongRow * a.segs * M ? 4 : 8;
+    const int part = ((job.ke - job.kb + kDenseK - 1) / kDenseK + parts - 1) / parts;
+    int until = part - part * (job.row0 / kDenseBM % 8) / 8;
+    for (int k0 = job.kb, t = 0; k0 < job.ke; k0 += kDenseK, t ^= 1) {
+        // multiplies tile k0, scatters the one after the next
+        f16x8 b[2][2];
+        piece(cbuf, 0, b[0]);
+        const int c2 = cbuf + 2 < 3 ? cbuf + 2 : cbuf - 1;
+#pragma unroll
+        for (int i = 0; i < PW; ++i) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (i + 1 < PW) piece(cbuf, i + 1, b[(i + 1) & 1]);
+            const f16x8(&c)[2] = b[i & 1];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) acc[r][i] = mfma(s[r][0], c[0], acc[r][i]);
+#pragma unroll
+            for (int r = 0; r < 2; ++r) low[r][i] = mfma(s[r][1], c[0], low[r][i]);
+#pragma unroll
+            for (int r = 0; r < 2; ++r) low[r][i] = mfma(s[r][0], c[1], low[r][i]);
+            if (i == 1) {
+                bring(k0 + 2 * kDenseK, t);
+                e.rest(k0 + 2 * kDenseK);
+            }
+            if (i >= 1 && i <= L::kIssue) issue_c(k0 + 2 * kDenseK, c2, i - 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(t ^ 1);
+        if (--until == 0 && k0 + kDenseK < job.ke) {
+            if (put_away) add_earlier();
+            put_away = 1;
+            until = part;
+#pragma unroll
+            for (int ct = 0; ct < PW; ++ct) {
+                const unsigned o = column_at(ct);
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        __builtin_amdgcn_raw_buffer_store_b32(bits_of(result(r, ct, i)), oview.rsrc, o, row_offset(r, i), 0);
+            }
+            clear();
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
+        // all loads but the entries (2) and the parts of C's tile after the next one: the next one's are in LDS
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(L::kIssue + 2) : "memory");
+        __syncthreads();
+        cbuf = cbuf == 2 ? 0 : cbuf + 1;
+    }
+
+    if (put_away) add_earlier();
+    const int back = -(uniform(a.exponents[0]) + uniform(a.exponents[1]));
+    const int at = lane_id_again();
+    bool odd = false;           // a result that is not finite, small or zero
+    auto odd_bits = [&](float y) CSRK_INLINE { return (bits_of(y) << 1) - (bits_of(kWideSmall) << 1) >= (bits_of(kDenseHuge) - bits_of(kWideSmall)) << 1; };
+#pragma unroll
+    for (int t = 0; t < PW; ++t) {
+        const unsigned o = column_at(t);
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float y = result(r, t, i);
+                odd |= odd_bits(y);
+                __builtin_amdgcn_raw_buffer_store_b32(bits_of(ldexpf(y, back)), oview.rsrc, o, row_offset(r, i), 0);
+            }
+    }
+    const unsigned long long unused = __ballot(e.pos < e.end) | e.bad;
+    if (__builtin_expect(unused != 0, 0) && at < kDenseRows && ((unsigned)(unused >> at * 4) & 0xfu) != 0)
+        atomicOr(&marks[wave * kDenseRows + at], 0xffffu);
+    if (__builtin_expect(__any(odd), 0))
+#pragma unroll
+        for (int t = 0; t < PW; ++t)
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float y = result(r, t, i);
+                    const bool inside = column_at(t) != 0xf0000000u;
+                    const unsigned long long again = __ballot(inside && y != 0.f && odd_bits(y)), zero = __ballot(inside && y == 0.f);
+                    const int row = pair * 32 + r * 16 + (at >> 4) * 4 + i;
+                    if ((at & 15) == 0) {
+                        if ((again >> at & 0xffffu) != 0) atomicOr(&marks[row], 1u << (half * PW + t));
+                        if ((zero >> at & 0xffffu) != 0) atomicOr(&zeros[row], 1u << (half * PW + t));
+                    }
+                }
+    __syncthreads();
+    say(threadIdx.x < kDenseBM ? marks[threadIdx.x] : 0u, threadIdx.x < kDenseBM ? zeros[threadIdx.x] : 0u);
+}
+
+}  // namespace csrk

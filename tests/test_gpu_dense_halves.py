@@ -1,0 +1,108 @@
+"""SPMM of wide outputs over long ranges of K in half-precision pieces, forced (CSRK_MFMA=2): its tile edges, rows of every kind,
+and the values that two pieces or their range of exponents cannot hold."""
+import numpy as np
+import pytest
+
+import oracle
+from test_gpu_parity import csrk, dev  # noqa: F401  (csrk is a fixture)
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# Relative to the sum of the terms' magnitudes: two pieces leave 2^-24 of each operand and of their product, three times 6e-8;
+# the rows checked have up to 9000 terms, whose sums of random rounding errors stay below 1e-6 of it.
+TOL = 2e-6
+
+
+def matrix(rng, M, K):
+    """About 1 % of the cells; every 50th row has none, one, two, every one of the first half's or every cell."""
+    rows = []
+    for r in range(M):
+        kind = r % 250
+        if kind == 0: c = np.zeros(0, int)
+        elif kind == 50: c = rng.integers(K, size=1)
+        elif kind == 100: c = rng.choice(K, 2, replace=False)
+        elif kind == 150 and r < 1000: c = np.arange(K // 2)
+        elif kind == 200 and r < 1000: c = np.arange(K)
+        else: c = np.unique(rng.integers(K, size=K // 100))
+        rows.append(np.sort(c))
+    rp = np.concatenate([[0], np.cumsum([len(c) for c in rows])]).astype(np.int32)
+    return rp, np.concatenate(rows).astype(np.int32)
+
+
+@pytest.mark.parametrize("M,K,N", [(16300, 8200, 500), (16384, 8192, 512), (16320, 9000, 300), (32650, 8224, 180)])
+@pytest.mark.parametrize("kind", ["plain", "ones", "unsorted", "not finite", "small", "large", "mixed", "zeros"])
+def test_long_ranges(csrk, monkeypatch, M, K, N, kind):
+    monkeypatch.setenv("CSRK_MFMA", "2")
+    rng = np.random.default_rng(M + K + N)
+    rp, ci = matrix(rng, M, K)
+    v = rng.uniform(-1, 1, len(ci)).astype(np.float32)
+    C = rng.normal(size=(K, N)).astype(np.float32)
+    row_of = np.repeat(np.arange(M), np.diff(rp))
+    if kind == "ones":
+        v[:] = 1
+    elif kind == "unsorted":        # every third row, and one pair of neighbours in some others
+        for r in range(0, M, 3):
+            ci[rp[r]:rp[r + 1]] = rng.permutation(ci[rp[r]:rp[r + 1]])
+        for r in range(1, M, 300):
+            if rp[r + 1] - rp[r] > 40:
+                i = rp[r] + int(rng.integers(40))
+                ci[i], ci[i + 1] = ci[i + 1], ci[i]
+    elif kind == "not finite":
+        C[5, 3], C[K - 1, N - 1], v[len(v) // 2], v[len(v) // 3] = np.inf, np.nan, -np.inf, np.nan
+        C[K // 2, N // 2], v[len(v) // 5] = 3e38, 3e38
+    elif kind == "small":           # far below what half precision reaches: the operands are scaled
+        v *= np.float32(1e-20)
+        C *= np.float32(1e-15)
+    elif kind == "large":
+        v *= np.float32(1e15)
+        C *= np.float32(1e12)
+    elif kind == "mixed":           # rows of S and C that are far below, or above, the rest of theirs
+        v[row_of % 5 == 1] *= np.float32(1e-9)
+        v[row_of % 5 == 2] *= np.float32(1e-13)
+        v[row_of % 25 == 3] *= np.float32(1e7)
+        C[:, N // 3] *= np.float32(1e-10)
+        C[:, N // 4] *= np.float32(1e6)
+    elif kind == "zeros":           # columns of nothing but zeros, with a value that is lost in one of them, and rows of lost values
+        C[:, N // 2:] = 0
+        C[K // 3, N // 2 + 1] = 1e-25
+        v[row_of % 7 == 0] = 1e-30
+        v[row_of % 7 == 1] = 0
+    O = csrk.spmm_csr(M, K, N, dev(rp), dev(ci), None if kind == "ones" else dev(v), dev(C)).cpu().numpy()
+    rows = np.unique(np.concatenate([np.arange(0, 1000, 50), np.arange(0, M, 41), rng.integers(M, size=60), [M - 1],
+                                     np.arange(1, M, 1500), row_of[[len(v) // 2, len(v) // 3, len(v) // 5]]]))
+    want, terms = oracle.spmm(M, K, N, rp, ci, v, C, rows=rows)
+    got = O[rows]
+    fine = np.isfinite(want) & (terms < 3e38)
+    np.testing.assert_array_equal(np.isnan(got)[~fine & np.isnan(want)], True)
+    np.testing.assert_array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    # (results below the smallest normal float are rounded to a multiple of 2^-149)
+    bad = np.abs(got[fine] - want[fine]) > TOL * terms[fine] + 2.0 ** -148
+    assert not bad.any(), (kind, bad.mean(), np.abs(got[fine] - want[fine])[bad].max())
+    if kind == "zeros":
+        assert (np.abs(want[:, N // 2 + 1]) > 0).any()
+
+
+@pytest.mark.parametrize("M,K,N,p", [(16384, 8192, 512, 0.06), (16384, 8192, 512, 0.1), (16384, 9000, 384, 0.35)])
+@pytest.mark.parametrize("sign", ["both", "one"])
+def test_error_is_the_vector_kernels(csrk, monkeypatch, M, K, N, p, sign):
+    # the 2-norm of the error against FP64 on a sample of rows, no larger than the vector kernels' (measured: 0.2-0.5 times)
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    parts = [(torch.rand((2048, K), device="cuda", generator=gen) < p).nonzero() + torch.tensor([[r, 0]], device="cuda") for r in range(0, M, 2048)]
+    at = torch.cat(parts)
+    rp = torch.zeros(M + 1, dtype=torch.int32, device="cuda")
+    rp[1:] = torch.cumsum(torch.bincount(at[:, 0], minlength=M), 0).to(torch.int32)
+    ci = at[:, 1].to(torch.int32).contiguous()
+    v, C = torch.rand(len(ci), device="cuda", generator=gen), torch.randn((K, N), device="cuda", generator=gen)
+    v, C = (v - 0.5, C) if sign == "both" else (v, C.abs())
+    some = torch.zeros((M, 1), device="cuda", dtype=torch.bool)
+    some[::17] = True
+    picked = some[at[:, 0], 0]
+    S = torch.zeros((M // 17 + 1, K), dtype=torch.float64, device="cuda")
+    S[at[picked, 0] // 17, at[picked, 1]] = v[picked].double()
+    want = S @ C.double()
+    err = []
+    for mode in ("2", "3"):
+        monkeypatch.setenv("CSRK_MFMA", mode)
+        err.append(((csrk.spmm_csr(M, K, N, rp, ci, v, C)[::17].double() - want).norm() / want.norm()).item())
+    assert err[0] <= 1.02 * err[1], err
