@@ -269,6 +269,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
         cbuf = cbuf == 2 ? 0 : cbuf + 1;
     }
 
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // (LDS must not be written to behind the workgroup's end)
     if (put_away) add_earlier();
     const int back = -(uniform(a.exponents[0]) + uniform(a.exponents[1]));
     const int at = lane_id_again();
