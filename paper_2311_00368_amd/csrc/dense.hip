@@ -18,9 +18,10 @@ constexpr long long kMaxGroups = 1 << 22;
 // choice (narrower blocks add up their sums on the way and are the more exact).  Shorter ranges would not be: the error in the
 // 2-norm against FP64, six products of bfloat16 / three of halves, is 4.2e-7 / 3.6e-7 at 16384^2, 20 %, 512 columns, 1.8e-7 /
 // 1.6e-7 at 16384 x 8192, 10 %, but 1.36e-7 / 1.41e-7 at 8192^2, log-normal rows, 256 columns, in ranges of 2048, and putting
-// the sums away (8 times 4 us or so) would weigh more.  A tile takes 1.5 us with 16 pieces and 1.4 with 12.
+// the sums away (8 times 4 us or so) would weigh more.  FusedMM: 5.3e-7 / 3.7e-7 at 16384^2, 20 %, 512/64, 2.5e-7 / 1.8e-7 at
+// 16384 x 8192, 10 %, 512/32.  A tile takes 1.4-1.5 us, FusedMM's 2.1.
 constexpr int kHalvesK = 8192;
-constexpr double kHalvesTileUs = 1.5;
+constexpr double kHalvesTileUs = 1.5, kHalvesFusedTileUs = 2.1;
 
 // SDDMM's tiles: 128 columns where they and B's fit LDS, for the entries of a row in a tile fill the 16 lanes better
 constexpr int sddmm_kt(int ds) { return ds == 1 ? 128 : 64; }
@@ -41,7 +42,7 @@ struct Layout {
     int n_tiles, c_blocks, b_blocks, a_blocks;
     Layout(const DenseShape &s, const DenseConfig &cfg) {
         const bool halves = cfg.halves;
-        const size_t pieces = s.bf16 ? 2 : halves ? 4 : 6;      // bytes of a prepared value
+        const size_t pieces = s.bf16 ? 2 : 6;       // bytes of a prepared value
         const int bn = cfg.ct * 16;
         n_tiles = s.op == kDenseSddmm ? 0 : (s.N + bn - 1) / bn * cfg.ct;
         const size_t d = (size_t)cfg.ds * 32, k = up32(s.K), octs = cfg.ds == 3 ? 16 : cfg.ds * 4;
@@ -54,12 +55,12 @@ struct Layout {
             at += padded(n);
             return was;
         };
-        c = take(k * n_tiles * 16 * pieces);
+        c = take(k * n_tiles * 16 * (halves ? 4 : pieces));
         // (whole tiles of SDDMM's columns)
         b = take((k + kSddmmMaxKt - 32) * d * pieces);
         a = take(up32(s.M) * d * pieces);
         todo = take(16);
-        exponents = take(halves ? 8 : 0);
+        exponents = take(halves ? 16 : 0);
         tiny = take(halves ? (size_t)c_blocks * 4 : 0);
         met = take(s.op == kDenseFused ? (size_t)b_blocks * 4 : 0);
         special = take(s.op == kDenseFused ? k : 0);
@@ -80,9 +81,14 @@ DenseKernel spmm_kernel(int ct) {
     return {nullptr, 0};
 }
 
-DenseKernel wide_kernel(int ct) {
-    if (ct == 12) return {dense_wide_kernel<12>, WideCfg<12>::kBytes};
-    if (ct == 16) return {dense_wide_kernel<16>, WideCfg<16>::kBytes};
+DenseKernel wide_kernel(int ct, int ds) {
+#define CSRK_DENSE_CASE(DS) \
+    if (ct == 12 && ds == DS) return {dense_wide_kernel<12, DS>, WideCfg<12, DS>::kBytes}; \
+    if (ct == 16 && ds == DS) return {dense_wide_kernel<16, DS>, WideCfg<16, DS>::kBytes};
+    CSRK_DENSE_CASE(0)
+    CSRK_DENSE_CASE(1)
+    CSRK_DENSE_CASE(2)
+#undef CSRK_DENSE_CASE
     return {nullptr, 0};
 }
 
@@ -147,10 +153,10 @@ bool dense_config(const DenseShape &s, int cus, DenseConfig *out) {
         }
     }
     if (best.ct == 0) return false;
-    if (s.op == kDenseSpmm && !s.bf16 && best.ct > 8 && best.seg_k >= kHalvesK) {
+    if (s.op != kDenseSddmm && !s.bf16 && best.ct > 8 && best.seg_k >= kHalvesK) {
         const long long rounds = (row_blocks * ((s.N + best.ct * 16 - 1) / (best.ct * 16)) * best.segs + cus - 1) / cus;
         best.halves = true;
-        best.us -= (double)rounds * (best.seg_k / 32 * (tile_us(s, best.ct, 0) - kHalvesTileUs) - 24.0);
+        best.us -= (double)rounds * (best.seg_k / 32 * (tile_us(s, best.ct, best.ds) - (best.ds ? kHalvesFusedTileUs : kHalvesTileUs)) - 24.0);
     }
     const Layout l(s, best);
     best.bytes = l.bytes;
@@ -202,7 +208,7 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
     }
     a.cuts = reinterpret_cast<int32_t *>(base + l.cuts);
 
-    const DenseKernel k = c.halves              ? wide_kernel(c.ct)
+    const DenseKernel k = c.halves              ? wide_kernel(c.ct, c.ds)
                           : s.op == kDenseSpmm  ? (s.bf16 ? spmm_kernel<1>(c.ct) : spmm_kernel<3>(c.ct))
                           : s.op == kDenseSddmm ? (s.bf16 ? sddmm_kernel<1>(c.ds) : sddmm_kernel<3>(c.ds))
                                                 : (s.bf16 ? dense_fused_kernel_bf16(c.ct, c.ds) : dense_fused_kernel_f32(c.ct, c.ds));

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kBlockThreads) void dense_finish(DenseArgs a) {
         }
     };
     const bool special = FUSED && a.todo[1] != 0;
-    // pieces with zeros that may be none: values of C were lost, or it depends on the row's values
+    // pieces with zeros that may be none: values of C were lost, or it depends on the row's values (FusedMM has seen these)
     const bool zeros = HALVES && a.todo[2] != 0, lost = zeros && a.todo[3] != 0;
     if (__builtin_expect(!special && !zeros && a.todo[0] == 0, 1)) {
         if (a.segs > 1)
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(kBlockThreads) void dense_finish(DenseArgs a) {
                         if (share) add_row_parts<VEC, LG, 1>(lds.whole, wave, wave, kWavesPerBlock, true, orow, N, n, acc);
                         else store_row<VEC, LG, 1>(orow, N, n, acc);
                     }
-        const bool with_zeros = zeros && (lost || loses_value(begin, end));
+        const bool with_zeros = zeros && (lost || (!FUSED && loses_value(begin, end)));
         for (int cb = 0; cb < a.col_blocks; ++cb) {
             unsigned m = uniform(marks(row, cb));
             if (with_zeros) m |= uniform(marks_of(a.zeros, row, cb));

@@ -1,4 +1,4 @@
-// Matrix-core SPMM for wide outputs: FP32 in two half-precision pieces, 32 rows of S per wavefront.
+// Matrix-core SPMM and FusedMM for wide outputs: FP32 in two half-precision pieces, 32 rows of S per wavefront.
 //
 // A float of 24 bits is h + l to 23 bits and a sign, h and l of 11 bits each (Ootomo and Yokota, "Recovering single precision
 // accuracy from Tensor Cores while surpassing the FP32 theoretical peak performance", 2022, whose scaling of the smaller piece
@@ -22,8 +22,13 @@
 // Every wavefront scatters 16 rows' entries into the tile that its pair reads.  C's tiles go to LDS directly, three buffers, two
 // tiles ahead; S's tiles are scattered two tiles ahead in two buffers; one barrier per tile.
 //
+// FusedMM's scores stay six products of bfloat16 pieces, each wavefront those of its own 16 rows; times S's values they are
+// split in half-precision pieces and passed to the pair through LDS as fragments.  Products that their larger piece loses
+// altogether are noticed there.
+//
 // Measured on MI355X, six products of bfloat16 pieces / this: SPMM 16384^2, 20 %, N = 512 1194 / 760 us, 16384 x 8192, 10 %, 512
-// 662 / 436, 32768 x 8192, 20 %, 192 590 / 390.  Bound by latency: of the 3000 cycles of a tile the matrix cores are busy for
+// 662 / 436, 32768 x 8192, 20 %, 192 590 / 390; FusedMM 16384^2, 20 %, 512/64 1550 / 1150, 16384 x 8192, 10 %, 512/32 767 / 540.
+// Bound by latency: of the 3000 cycles of a tile the matrix cores are busy for
 // half; the wavefronts that come second on their SIMD take 770 + 1065 cycles for the products, 670 for S, 200 to ask for
 // loads, 215 for the fragments (the first ones wait for them at the barrier).  What gave nothing: S between the matrix
 // instructions (780-940 us), four of the wavefronts with S before the products and four behind (756), entries of two halves of
@@ -39,25 +44,38 @@ __device__ __forceinline__ f32x4 mfma(f16x8 a, f16x8 b, f32x4 c) { return __buil
 
 // scaled results below this are computed again
 constexpr float kWideSmall = 1.f;
-// mean entries of a row in a range from which on the sums are put away three times on the way and not seven
-constexpr int kWideLongRow = 2400;
+// mean entries of a row in a range from which on the sums are put away three times on the way and not seven (FusedMM's six
+// products were the further off: 16384 x 8192, 10 %, 512/32 2.5e-7, this 2.2e-7 with three and 1.8e-7 with seven)
+constexpr int kWideLongRow = 2400, kWideLongFusedRow = 700;
 
-template <int CT>
+// DS: 32-element steps of the dot products (0: SPMM)
+template <int CT, int DS>
 struct WideCfg {
     static constexpr int BN = CT * 16, PW = CT / 2;     // columns of a block, 16-column pieces of a wavefront
-    static constexpr int kS = kDenseBM * kSRow;         // bytes of a tile of S
-    static constexpr int kC = CT * 2048;                // ... and of C
+    // SPMM: two tiles of S, shared by pairs.  FusedMM: a tile for each wavefront, and two of the products with the scores, as
+    // fragments.
+    static constexpr int kS = DS == 0 ? kDenseBM * kSRow : kDenseWaves * 2048;
+    static constexpr int kC = CT * 2048;                // bytes of a tile of C
+    static constexpr int kBufs = DS == 0 ? 3 : 2;
     static constexpr int kIssue = kC / (kDenseThreads * 16);
-    static constexpr int kOffS = 3 * kC;
-    static constexpr int kOffCount = kOffS + 2 * kS;
+    static constexpr int kB = DS * 3 * 2048;            // ... and of B
+    static constexpr int kIssueB = (kB + kDenseThreads * 16 - 1) / (kDenseThreads * 16);
+    static constexpr int kOffS = kBufs * kC;
+    static constexpr int kOffRaw = kOffS + 2 * kS;
+    static constexpr int kOffB = kOffRaw + (DS == 0 ? 0 : kDenseWaves * kSWave);
+    static constexpr int kOffCount = kOffB + 2 * kIssueB * kDenseThreads * 16;
     static constexpr int kOffMarks = kOffCount + kDenseWaves * 4;
     static constexpr int kBytes = kOffMarks + 2 * kDenseBM * 4;
     static_assert(CT % 4 == 0 && kBytes <= 160 * 1024, "LDS of a gfx950 CU");
 };
+// FusedMM: what the exponent of S's values is lowered by, so that products of sampled sizes with the scores, of dot products of
+// D elements, are about as large as C's values
+__device__ __forceinline__ int wide_score_exponent(int D) { return 17 + (33 - __clz(D)) / 2; }
 
-template <int CT>
+template <int CT, int DS>
 __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs a) {
-    using L = WideCfg<CT>;
+    using L = WideCfg<CT, DS>;
+    constexpr bool kFused = DS > 0;
     constexpr int PW = L::PW;
     extern __shared__ __attribute__((aligned(16))) char dlds[];
     const int M = a.M, K = a.K, N = a.N;
@@ -70,22 +88,38 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
     const unsigned c_step = (unsigned)a.n_tiles * 2048u, c_end = (unsigned)((K + kDenseK - 1) / kDenseK) * c_step;
     const DenseView cview = dense_view(a.Cp, c_end);
     const unsigned c_off = (unsigned)job.cb * L::kC + threadIdx.x * 16u;
-    auto issue_c = [&](int k0, int buf, int i) CSRK_INLINE {
-        const unsigned tile = (unsigned)(k0 / kDenseK) * c_step, at = (tile < c_end ? tile : c_end) + i * kDenseThreads * 16;
-        const unsigned to = lds0 + buf * L::kC + wave * 1024u + i * kDenseThreads * 16;
+    auto to_lds = [&](const DenseView &view, unsigned off, unsigned step, unsigned end, int k0, unsigned to, int i) CSRK_INLINE {
+        const unsigned tile = (unsigned)(k0 / kDenseK) * step, at = (tile < end ? tile : end) + i * kDenseThreads * 16;
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                     :: "s"(to), "v"(c_off), "s"(cview.rsrc), "s"(at) : "memory");
+                     :: "s"(to + wave * 1024u + i * kDenseThreads * 16), "v"(off), "s"(view.rsrc), "s"(at) : "memory");
+    };
+    auto issue_c = [&](int k0, int buf, int i) CSRK_INLINE { to_lds(cview, c_off, c_step, c_end, k0, lds0 + buf * L::kC, i); };
+    const unsigned b_end = (unsigned)((K + kDenseK - 1) / kDenseK) * L::kB;
+    const DenseView bview = dense_view(a.Bp, kFused ? b_end : 0u);
+    const unsigned b_off = threadIdx.x * 16u < (unsigned)L::kB ? threadIdx.x * 16u : 0xf0000000u;
+    auto issue_b = [&](int k0, int buf, int i) CSRK_INLINE {
+        to_lds(bview, L::kIssueB * kDenseThreads * 16 == L::kB || i == 0 || threadIdx.x * 16u < L::kB % (kDenseThreads * 16u) ? b_off : 0xf0000000u, L::kB,
+               b_end, k0, lds0 + L::kOffB + buf * (L::kIssueB * kDenseThreads * 16), i);
     };
 #pragma unroll
-    for (int i = 0; i < 2 * L::kIssue; ++i) issue_c(job.kb + i / L::kIssue * kDenseK, i / L::kIssue, i % L::kIssue);
+    for (int i = 0; i < (L::kBufs - 1) * L::kIssue; ++i) issue_c(job.kb + i / L::kIssue * kDenseK, i / L::kIssue, i % L::kIssue);
+#pragma unroll
+    for (int i = 0; i < 2 * L::kIssueB; ++i) issue_b(job.kb + i / L::kIssueB * kDenseK, i / L::kIssueB, i % L::kIssueB);
+    bf16x8 af[kFused ? DS : 1][3];
+    if constexpr (kFused) dense_load_a<DS, 3>(a, job.row0 + wave * kDenseRows, af);
 
-    Entries<true> e;
+    int value_exponent = uniform(a.exponents[0]);
+    if constexpr (kFused) {
+        value_exponent -= wide_score_exponent(a.D);
+        value_exponent = value_exponent < -126 ? -126 : value_exponent;
+    }
+    Entries<true, !kFused> e;
     int several;                // rows with more than one entry
     {
         const unsigned bytes = dense_entry_bytes(a, job);
         e.cols = dense_view(job.ci, bytes);
         e.vals = dense_view(a.vals ? (const void *)(a.vals + job.e0) : (const void *)job.ci, a.vals ? bytes : 0u);
-        e.scale = power_of_two(uniform(a.exponents[0]));
+        e.scale = power_of_two(value_exponent);
         e.one = a.vals ? 0.f : e.scale;
         e.q4 = (lane & 3) * 4;
         e.ke = job.ke;
@@ -96,36 +130,69 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
         several = (int)__popcll(__ballot(range.y - range.x > 1)) / 4;
         e.load();
     }
-    char *const swave = dlds + L::kOffS + wave * kSWave;
+    char *const swave = dlds + (kFused ? L::kOffRaw : L::kOffS) + wave * kSWave;
     const unsigned row_at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)(swave + (lane >> 2) * kSRow);
     const unsigned dump = kDenseK * 4u + (lane & 3) * 4u;
     char *const zero_at = swave + (lane >> 3) * kSRow + (lane & 7) * 16;
     auto bring = [&](int k0, int buf) CSRK_INLINE {
         const f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < 2; ++i) *reinterpret_cast<f32x4 *>(zero_at + buf * L::kS + i * 8 * kSRow) = z;
-        e.row_at = row_at + buf * L::kS;
+        for (int i = 0; i < 2; ++i) *reinterpret_cast<f32x4 *>(zero_at + (kFused ? 0 : buf * L::kS) + i * 8 * kSRow) = z;
+        e.row_at = row_at + (kFused ? 0 : buf * L::kS);
         e.dump = e.row_at + dump;
         e.template place<true>(k0, false);
     };
 
     // 32 rows of S as fragments: [rows / 16][larger and smaller pieces]
     const int pair = wave >> 1, half = wave & 1;
-    const char *const sfrag = dlds + L::kOffS + (pair * 32 + (lane & 15)) * kSRow + (lane >> 4) * 16;
+    const char *const sfrag = dlds + L::kOffS + (kFused ? pair * 4096 + lane * 16 : (pair * 32 + (lane & 15)) * kSRow + (lane >> 4) * 16);
     f16x8 s[2][2];
     auto fetch = [&](int buf) CSRK_INLINE {
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
-            u32x4 x[2], h, l;
+            if constexpr (kFused) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i) x[i] = *reinterpret_cast<const u32x4 *>(sfrag + buf * L::kS + r * 16 * kSRow + i * 64);
+                for (int p = 0; p < 2; ++p) s[r][p] = *reinterpret_cast<const f16x8 *>(sfrag + buf * L::kS + (r * 2 + p) * 1024);
+            } else {
+                u32x4 x[2], h, l;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                h[i] = lower_halves(x[i >> 1][(i & 1) * 2], x[i >> 1][(i & 1) * 2 + 1]);
-                l[i] = upper_halves(x[i >> 1][(i & 1) * 2], x[i >> 1][(i & 1) * 2 + 1]);
+                for (int i = 0; i < 2; ++i) x[i] = *reinterpret_cast<const u32x4 *>(sfrag + buf * L::kS + r * 16 * kSRow + i * 64);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    h[i] = lower_halves(x[i >> 1][(i & 1) * 2], x[i >> 1][(i & 1) * 2 + 1]);
+                    l[i] = upper_halves(x[i >> 1][(i & 1) * 2], x[i >> 1][(i & 1) * 2 + 1]);
+                }
+                s[r][0] = __builtin_bit_cast(f16x8, h);
+                s[r][1] = __builtin_bit_cast(f16x8, l);
             }
-            s[r][0] = __builtin_bit_cast(f16x8, h);
-            s[r][1] = __builtin_bit_cast(f16x8, l);
+        }
+    };
+    // FusedMM: the wavefront's own 16 rows times their scores, as fragments for its pair
+    const char *const own = swave + (lane & 15) * kSRow + (lane >> 4) * 16, *const bfrag = dlds + L::kOffB + lane * 16;
+    char *const frag_to = dlds + L::kOffS + wave * 2048 + lane * 16;
+    unsigned least = ~0u;       // of the products' magnitudes (shifted by one and less one: zeros are the largest)
+    auto score = [&](int buf) CSRK_INLINE {
+#pragma clang fp contract(off)
+        if constexpr (kFused) {
+            f32x4 x[2], p[2];
+            dense_scores<DS, 3>(bfrag + buf * (L::kIssueB * kDenseThreads * 16), af, p);
+            u32x4 h, l;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                x[i] = *reinterpret_cast<const f32x4 *>(own + i * 64);
+                p[i] *= x[i];
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const unsigned u = half_pieces(p[i][2 * j]), v = half_pieces(p[i][2 * j + 1]);
+                    h[2 * i + j] = lower_halves(u, v);
+                    l[2 * i + j] = upper_halves(u, v);
+                    const unsigned y = (bits_of(p[i][2 * j]) << 1) - 1, z = (bits_of(p[i][2 * j + 1]) << 1) - 1;
+                    least = y < least ? y : least;
+                    least = z < least ? z : least;
+                }
+            }
+            *reinterpret_cast<u32x4 *>(frag_to + buf * L::kS) = h;
+            *reinterpret_cast<u32x4 *>(frag_to + buf * L::kS + 1024) = l;
         }
     };
     const char *const cfrag = dlds + half * (PW * 2048) + lane * 16;
@@ -161,6 +228,9 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
         }
         for (int i = blockIdx.x * kDenseThreads + t; i < a.c_blocks; i += gridDim.x * kDenseThreads)
             if (a.tiny_met[i] != 0) a.todo[3] = 1;
+        if constexpr (kFused)
+            for (int i = blockIdx.x * kDenseThreads + t; i < a.b_blocks; i += gridDim.x * kDenseThreads)
+                if (a.special_met[i] != 0) a.todo[1] = 1;
     };
 
     // The results, scaled: what is put away in memory, and what has been.
@@ -170,16 +240,19 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
     // lane l holds column l & 15 of each 16-column piece, rows 4 (l / 16) + i; rows past M and columns past N fall outside the view
     auto column_at = [&](int t) CSRK_INLINE {
         const int l = lane_id_again(), col = job.cb * L::BN + (half * PW + t) * 16 + (l & 15);
-        return col < N ? (unsigned)(l >> 4) * 4u * ld_b + (unsigned)col * 4u : 0xf0000000u;
+        unsigned o = col < N ? (unsigned)(l >> 4) * 4u * ld_b + (unsigned)col * 4u : 0xf0000000u;
+        asm("" : "+v"(o));      // (otherwise: a branch for every use)
+        return o;
     };
     auto row_offset = [&](int r, int i) CSRK_INLINE { return (unsigned)(pair * 32 + r * 16 + i) * ld_b; };
     auto result = [&](int r, int t, int i) CSRK_INLINE { return fmaf(low[r][t][i], 1.f / kHalfLow, acc[r][t][i]); };
     auto add_earlier = [&]() CSRK_INLINE {
+        constexpr int T = kFused ? 1 : 2;       // pieces at a time (FusedMM has no more registers)
 #pragma unroll
-        for (int g = 0; g < PW; g += 2) {
-            float y[2][2][4];
+        for (int g = 0; g < PW; g += T) {
+            float y[2][T][4];
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
+            for (int t = 0; t < T; ++t) {
                 const unsigned o = column_at(g + t);
 #pragma unroll
                 for (int r = 0; r < 2; ++r)
@@ -188,7 +261,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
                         y[r][t][i] = float_of(__builtin_amdgcn_raw_buffer_load_b32(oview.rsrc, o, row_offset(r, i), 0));
             }
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+            for (int t = 0; t < T; ++t)
 #pragma unroll
                 for (int r = 0; r < 2; ++r)
 #pragma unroll
@@ -201,8 +274,10 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
 
     bring(job.kb, 0);
     e.rest(job.kb);
-    bring(job.kb + kDenseK, 1);
-    e.rest(job.kb + kDenseK);
+    if constexpr (!kFused) {
+        bring(job.kb + kDenseK, 1);
+        e.rest(job.kb + kDenseK);
+    }
     i32x4 *const counts = reinterpret_cast<i32x4 *>(dlds + L::kOffCount);
     {
         unsigned long long rows = e.bad | e.bad >> 1;
@@ -216,62 +291,73 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
         const i32x4 n = counts[0] + counts[1];
         if (uniform(n[0] + n[1] + n[2] + n[3]) > 0) return say(0xffffu, 0u);
     }
-    fetch(0);
+    if constexpr (kFused) score(0);
+    else fetch(0);
     __syncthreads();
     int cbuf = 0, put_away = 0;
     // tiles until the sums are put away (neighbouring workgroups at different times: all at once, 872 instead of 834 us)
-    const int parts = (long long)uniform(a.rowptr[M]) >= (long long)kWideLongRow * a.segs * M ? 4 : 8;
+    const int parts = (long long)uniform(a.rowptr[M]) >= (long long)(kFused ? kWideLongFusedRow : kWideLongRow) * a.segs * M ? 4 : 8;
     const int part = ((job.ke - job.kb + kDenseK - 1) / kDenseK + parts - 1) / parts;
     int until = part - part * (job.row0 / kDenseBM % 8) / 8;
-    for (int k0 = job.kb, t = 0; k0 < job.ke; k0 += kDenseK, t ^= 1) {
-        // multiplies tile k0, scatters the one after the next
-        f16x8 b[2][2];
-        piece(cbuf, 0, b[0]);
-        const int c2 = cbuf + 2 < 3 ? cbuf + 2 : cbuf - 1;
+    for (int k0 = job.kb, t = 0;;) {
+        // tiles up to where the sums are put away
+        const int stop = k0 + until * kDenseK < job.ke ? k0 + until * kDenseK : job.ke;
+        for (; k0 < stop; k0 += kDenseK, t ^= 1) {
+            // multiplies tile k0, scatters the one after the next (FusedMM: the next one)
+            constexpr int kNext = L::kBufs - 1;
+            if constexpr (kFused) fetch(t);
+            constexpr int kAhead = kFused ? 1 : 2;      // pieces of C read ahead (FusedMM has no registers for more)
+            f16x8 b[kAhead + 1][2];
 #pragma unroll
-        for (int i = 0; i < PW; ++i) {
+            for (int i = 0; i < kAhead; ++i) piece(cbuf, i, b[i]);
+            const int c2 = kFused ? cbuf ^ 1 : cbuf + 2 < 3 ? cbuf + 2 : cbuf - 1;
+#pragma unroll
+            for (int i = 0; i < PW; ++i) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (i + kAhead < PW) piece(cbuf, i + kAhead, b[(i + kAhead) % (kAhead + 1)]);
+                const f16x8(&c)[2] = b[i % (kAhead + 1)];
+#pragma unroll
+                for (int r = 0; r < 2; ++r) acc[r][i] = mfma(s[r][0], c[0], acc[r][i]);
+#pragma unroll
+                for (int r = 0; r < 2; ++r) low[r][i] = mfma(s[r][1], c[0], low[r][i]);
+#pragma unroll
+                for (int r = 0; r < 2; ++r) low[r][i] = mfma(s[r][0], c[1], low[r][i]);
+                if (i == 1) {
+                    bring(k0 + kNext * kDenseK, t);
+                    e.rest(k0 + kNext * kDenseK);
+                }
+                // (in the last steps: next to S's loads they cost 40-70 us more)
+                if (i >= PW - L::kIssue) issue_c(k0 + kNext * kDenseK, c2, i - (PW - L::kIssue));
+                if (kFused && i >= 1 && i <= L::kIssueB) issue_b(k0 + 2 * kDenseK, t, i - 1);
+            }
             __builtin_amdgcn_sched_barrier(0);
-            if (i + 1 < PW) piece(cbuf, i + 1, b[(i + 1) & 1]);
-            const f16x8(&c)[2] = b[i & 1];
-#pragma unroll
-            for (int r = 0; r < 2; ++r) acc[r][i] = mfma(s[r][0], c[0], acc[r][i]);
-#pragma unroll
-            for (int r = 0; r < 2; ++r) low[r][i] = mfma(s[r][1], c[0], low[r][i]);
-#pragma unroll
-            for (int r = 0; r < 2; ++r) low[r][i] = mfma(s[r][0], c[1], low[r][i]);
-            if (i == 1) {
-                bring(k0 + 2 * kDenseK, t);
-                e.rest(k0 + 2 * kDenseK);
-            }
-            if (i >= 1 && i <= L::kIssue) issue_c(k0 + 2 * kDenseK, c2, i - 1);
+            if constexpr (kFused) score(t ^ 1);
+            else fetch(t ^ 1);
+            // SPMM: all loads but the entries (2) and the parts of C's tile after the next one: the next one's are in LDS
+            asm volatile("s_waitcnt vmcnt(%0)" :: "n"(kFused ? 0 : L::kIssue + 2) : "memory");
+            __syncthreads();
+            cbuf = cbuf == kNext ? 0 : cbuf + 1;
         }
-        __builtin_amdgcn_sched_barrier(0);
-        fetch(t ^ 1);
-        if (--until == 0 && k0 + kDenseK < job.ke) {
-            if (put_away) add_earlier();
-            put_away = 1;
-            until = part;
+        if (k0 >= job.ke) break;
+        if (put_away) add_earlier();
+        put_away = 1;
+        until = part;
 #pragma unroll
-            for (int ct = 0; ct < PW; ++ct) {
-                const unsigned o = column_at(ct);
+        for (int ct = 0; ct < PW; ++ct) {
+            const unsigned o = column_at(ct);
 #pragma unroll
-                for (int r = 0; r < 2; ++r)
+            for (int r = 0; r < 2; ++r)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        __builtin_amdgcn_raw_buffer_store_b32(bits_of(result(r, ct, i)), oview.rsrc, o, row_offset(r, i), 0);
-            }
-            clear();
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                for (int i = 0; i < 4; ++i)
+                    __builtin_amdgcn_raw_buffer_store_b32(bits_of(result(r, ct, i)), oview.rsrc, o, row_offset(r, i), 0);
         }
-        // all loads but the entries (2) and the parts of C's tile after the next one: the next one's are in LDS
-        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(L::kIssue + 2) : "memory");
-        __syncthreads();
-        cbuf = cbuf == 2 ? 0 : cbuf + 1;
+        clear();
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // (LDS must not be written to behind the workgroup's end)
     if (put_away) add_earlier();
-    const int back = -(uniform(a.exponents[0]) + uniform(a.exponents[1]));
+    const int back = -(value_exponent + uniform(a.exponents[1]) + (kFused ? uniform(a.exponents[2]) + uniform(a.exponents[3]) : 0));
     const int at = lane_id_again();
     bool odd = false;           // a result that is not finite, small or zero
     auto odd_bits = [&](float y) CSRK_INLINE { return (bits_of(y) << 1) - (bits_of(kWideSmall) << 1) >= (bits_of(kDenseHuge) - bits_of(kWideSmall)) << 1; };
@@ -306,8 +392,18 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
                         if ((zero >> at & 0xffffu) != 0) atomicOr(&zeros[row], 1u << (half * PW + t));
                     }
                 }
+    // FusedMM: rows with products that their larger piece loses
+    unsigned *const lossy = reinterpret_cast<unsigned *>(counts);
+    if constexpr (kFused) {
+        unsigned long long rows = __ballot(least < (bits_of(0x1p-24f) << 1) - 1);
+        rows |= rows >> 32;
+        if (at == 0) lossy[wave] = (unsigned)(rows | rows >> 16) & 0xffffu;
+    }
     __syncthreads();
-    say(threadIdx.x < kDenseBM ? marks[threadIdx.x] : 0u, threadIdx.x < kDenseBM ? zeros[threadIdx.x] : 0u);
+    unsigned again = threadIdx.x < kDenseBM ? marks[threadIdx.x] : 0u, zero = threadIdx.x < kDenseBM ? zeros[threadIdx.x] : 0u;
+    if constexpr (kFused)
+        if (threadIdx.x < kDenseBM && (lossy[threadIdx.x >> 4] >> (threadIdx.x & 15) & 1u) != 0) again |= zero;
+    say(again, zero);
 }
 
 }  // namespace csrk

@@ -1,4 +1,4 @@
-"""SPMM of wide outputs over long ranges of K in half-precision pieces, forced (CSRK_MFMA=2): its tile edges, rows of every kind,
+"""SPMM and FusedMM of wide outputs over long ranges of K in half-precision pieces, forced (CSRK_MFMA=2): its tile edges, rows of every kind,
 and the values that two pieces or their range of exponents cannot hold."""
 import numpy as np
 import pytest
@@ -81,6 +81,56 @@ def test_long_ranges(csrk, monkeypatch, M, K, N, kind):
     assert not bad.any(), (kind, bad.mean(), np.abs(got[fine] - want[fine])[bad].max())
     if kind == "zeros":
         assert (np.abs(want[:, N // 2 + 1]) > 0).any()
+
+
+@pytest.mark.parametrize("M,K,D,N", [(16300, 8200, 64, 500), (16384, 8192, 32, 512), (16320, 9000, 1, 300), (32650, 8224, 33, 180)])
+@pytest.mark.parametrize("kind", ["plain", "ones", "unsorted", "not finite", "small", "large", "mixed", "zeros"])
+def test_long_ranges_fused(csrk, monkeypatch, M, K, D, N, kind):
+    monkeypatch.setenv("CSRK_MFMA", "2")
+    rng = np.random.default_rng(M + K + N + D)
+    rp, ci = matrix(rng, M, K)
+    v = rng.uniform(-1, 1, len(ci)).astype(np.float32)
+    A, B, C = (rng.normal(size=n).astype(np.float32) for n in ((M, D), (K, D), (K, N)))
+    row_of = np.repeat(np.arange(M), np.diff(rp))
+    if kind == "ones":
+        v[:] = 1
+    elif kind == "unsorted":
+        for r in range(0, M, 3):
+            ci[rp[r]:rp[r + 1]] = rng.permutation(ci[rp[r]:rp[r + 1]])
+    elif kind == "not finite":
+        A[M // 3, 0], C[5, 3], v[len(v) // 2] = np.nan, np.inf, -np.inf
+        B[K // 4, D - 1] = np.inf
+    elif kind == "small":
+        v *= np.float32(1e-8)
+        A *= np.float32(1e-12)
+        B *= np.float32(1e-9)
+        C *= np.float32(1e-6)
+    elif kind == "large":
+        v *= np.float32(1e9)
+        A *= np.float32(1e10)
+        B *= np.float32(1e8)
+        C *= np.float32(1e6)
+    elif kind == "mixed":
+        v[row_of % 5 == 1] *= np.float32(1e-9)
+        A[np.arange(M) % 5 == 2] *= np.float32(1e-13)
+        A[np.arange(M) % 25 == 3] *= np.float32(1e6)
+        C[:, N // 3] *= np.float32(1e-10)
+    elif kind == "zeros":
+        C[:, N // 2:] = 0
+        C[K // 3, N // 2 + 1] = 1e-25
+        v[row_of % 7 == 0] = 1e-30
+        A[np.arange(M) % 7 == 1] = 0
+        A[np.arange(M) % 7 == 2] = 1e-25
+    O = csrk.fusedmm_csr(M, K, D, N, dev(rp), dev(ci), None if kind == "ones" else dev(v), dev(A), dev(B), dev(C)).cpu().numpy()
+    rows = np.unique(np.concatenate([np.arange(0, 1000, 50), np.arange(0, M, 57), [M // 3, M - 1], row_of[[len(v) // 2]]]))
+    want, terms = oracle.fusedmm(M, K, D, N, rp, ci, v, A, B, C, rows=rows)
+    got = O[rows]
+    fine = np.isfinite(want) & (terms < 3e38)
+    assert fine.mean() > (0.3 if kind == "not finite" else 0.9)
+    np.testing.assert_array_equal(np.isnan(got)[np.isnan(want)], True)
+    np.testing.assert_array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    bad = np.abs(got[fine] - want[fine]) > TOL * terms[fine] + 2.0 ** -148
+    assert not bad.any(), (kind, bad.mean(), (np.abs(got[fine] - want[fine]) / terms[fine])[bad].max())
 
 
 @pytest.mark.parametrize("M,K,N,p", [(16384, 8192, 512, 0.06), (16384, 8192, 512, 0.1), (16384, 9000, 384, 0.35)])
