@@ -15,8 +15,9 @@ workload is the 16384 x 16384, 20 %-dense configuration the benchmark spec's target is
                rocprofv3 in a recorded run of the same kernels: hbm_counter_*) and of the machine
                rates measured in this run (frac_*_measured), one cold run (caches flushed by writing a 1 GiB buffer) and
                the wall time of the very first call (workspace allocation included).  `kernels` says whether the matrix-core
-               kernels or the vector kernels ran: of the first the rate of the bfloat16 products that they work through
-               (six for an FP32 one, over every cell of S) and its share of the published peak, of the second the rate at
+               kernels or the vector kernels ran: of the first the rate of the 16-bit products that they work through
+               (six bfloat16 ones for an FP32 one, or three half-precision ones by C where ranges of K are long, over every
+               cell of S) and its share of the published peak, of the second the rate at
                which gathered dense rows reach the ALUs (nnz * width * 4 bytes / time)
   measured_peaks  the library's micro-benchmarks (csrk_microbench), run in this process before the timed region:
                device copy (GB/s), independent FP32 multiply-adds acc += x * y without packed FP32 (TFLOP/s), and
@@ -49,6 +50,14 @@ if ROOT not in sys.path:
 
 BF16_MATRIX_PEAK_TFLOPS = 2500.0  # MI355X, published, dense
 PRODUCTS = 6                      # bfloat16 products that the matrix-core kernels make of an FP32 one
+HALF_PRODUCTS = 3                 # half-precision products (the same rate) of an FP32 one by C, over long ranges of K
+
+
+def products_by_c(M, K, N):
+    """Matrix-core products for an FP32 product with C (csrc/dense.hip, kHalvesK): half-precision ones where blocks of more
+    than 128 columns of the output have at least 8192 columns of S to a workgroup on 256 CUs."""
+    workgroups = -(-M // 128) * -(-N // 256)
+    return HALF_PRODUCTS if N > 128 and K >= 8192 and K * workgroups >= 8192 * 256 else PRODUCTS
 FP32_VECTOR_PEAK_TFLOPS = 157.3   # MI355X, published: 256 CUs x 2.4 GHz x 256 flop/clk/CU
 HBM_PEAK_GBS = 8000.0             # MI355X, published
 # The rates this build's instruction mix can reach (plain multiply-adds, since packed FP32 is switched off; 128-bit LDS
@@ -218,7 +227,9 @@ def main():
         else:
             os.environ["CSRK_MFMA"] = mfma_switch
     widths = {name: sum(v_ for k_, v_ in w.ops[name].items() if k_ in ("N", "D")) for name, _ in ops}
-    matrix_flops = {name: PRODUCTS * 2.0 * w.M * w.K * widths[name] for name, _ in ops}
+    matrix_products = {name: products_by_c(w.M, w.K, w.ops[name].get("N", 0)) for name, _ in ops}
+    matrix_flops = {name: 2.0 * w.M * w.K * (matrix_products[name] * w.ops[name].get("N", 0) + PRODUCTS * w.ops[name].get("D", 0))
+                    for name, _ in ops}
     # one cold run per operation: a 1 GiB fill pushes the operands out of L2 and the 256 MB memory-side cache
     cold_ms = {}
     flush = torch.empty(1 << 28, dtype=torch.float32, device="cuda")
@@ -277,7 +288,8 @@ def main():
             "kernel": dom, "bound": "mfma", "achieved": round(rate, 1), "peak": BF16_MATRIX_PEAK_TFLOPS,
             "unit": "TFLOP/s", "frac": round(rate / BF16_MATRIX_PEAK_TFLOPS, 4),
             "useful_TFLOPs": round(achieved, 3),
-            "ceiling_note": "rate of the bfloat16 products that the matrix cores work through: six for an FP32 product, over every "
+            "ceiling_note": "rate of the 16-bit products that the matrix cores work through: "
+                            f"{matrix_products[dom] if w.ops[dom].get('N') else PRODUCTS} for an FP32 product (scores: {PRODUCTS}), over every "
                             "cell of S (stored or not); useful_TFLOPs counts 2 flops per stored entry and column; the peak "
                             "is the published dense one at 2.4 GHz, the clock under this load is 2.0 GHz (power)",
         }

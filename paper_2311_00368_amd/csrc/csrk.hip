@@ -1387,6 +1387,37 @@ double short_bf16_sddmm_us(const DenseShape &s, const DenseConfig &c, int cus, d
     return -3.5 + rounds * (11.0 + c.seg_k / 32 * tile) + (c.ds == 1 ? 0.9 : 1.4) * 1e-6 * nnz;
 }
 
+// The two estimates above err in ways that depend on the class of the call: the kernels of both sides have changed since
+// they were fitted, and a call of 30 us is not a call of 300 us made ten times.  So for the classes where that loses most
+// the ratio of the two times is fitted as well: the matrix-core kernels are also taken where
+//     base + dense * ln(their estimate) + vector * ln(the vector kernels') > 0,
+// from 51000 random calls timed both ways, three sets of operands in turn (M 512-32768, K 512-16384, 6-35 %, N 16-512, D
+// 16-128, a quarter of them with uneven rows), each class by itself, calls near the line counting most.  `base` lies 8-30 %
+// below the fit: so far that of the calls that a class gains hardly one in twelve is slower by more than 3 %.
+//     over 9000 other calls  changes  now faster by > 3 %  slower by > 3 %  at worst  average of those changed
+//     operands in turn           342                  308               19      0.84                      1.43
+//     cold caches                314                  289               13      0.80                      1.40
+// On average over a class: FP32 SDDMM of more than 64 elements 9 %, FusedMM of more than 64 with more than 128 columns 9 %,
+// SPMM of 33-128 / 129-256 / more columns 2 / 4 / 5 %, bfloat16 SDDMM of more than 64 4 %.  What has no row had less than 1 %
+// to win (FP32 SDDMM of up to 64, all narrower outputs, unaligned operands, bfloat16 SPMM and FusedMM).
+struct RatioFit {
+    double base, dense, vector;
+};
+bool dense_is_faster(const DenseShape &s, const DenseConfig &c, bool planned, double density, double vector) {
+    if (s.M < 512 || s.M > 32768 || s.K < 512 || s.K > 16384 || density < 0.055 || density > 0.36 || s.D > 128 || s.N > 512) return false;
+    RatioFit f;
+    if (s.op == kDenseSpmm && !s.bf16 && s.N > 32)
+        f = s.N <= 128 ? RatioFit{0.36, -0.69, 0.62} : s.N <= 256 ? RatioFit{0.55, -0.87, 0.77} : RatioFit{0.58, -0.95, 0.85};
+    else if (s.op == kDenseSddmm && s.D > 64)
+        f = s.bf16 ? RatioFit{0.60, -0.95, 0.75} : RatioFit{0.51, -0.88, 0.78};
+    else if (s.op == kDenseFused && !s.bf16 && s.N > 128)
+        f = s.D <= 64 ? RatioFit{0.32, -0.74, 0.68} : RatioFit{-0.09, -0.68, 0.74};
+    else
+        return false;
+    // (a plan is worth a tenth to the vector kernels where the rows are even)
+    return f.base + f.dense * std::log(c.us) + f.vector * std::log(vector) > (planned ? 0.1 : 0.0);
+}
+
 uintptr_t addresses(std::initializer_list<const void *> pointers) {
     uintptr_t a = 0;
     for (const void *p : pointers) a |= reinterpret_cast<uintptr_t>(p);
@@ -1394,7 +1425,7 @@ uintptr_t addresses(std::initializer_list<const void *> pointers) {
 }
 
 // `operands`: the addresses of the dense operands and of O, or'ed together
-bool dense_wanted(const DeviceState &d, const csrk_plan_s *plan, const DenseShape &s, uintptr_t operands, long long nnz, DenseConfig *c) {
+bool dense_chosen(const DeviceState &d, const csrk_plan_s *plan, const DenseShape &s, uintptr_t operands, long long nnz, DenseConfig *c) {
     const int mode = env_int("CSRK_MFMA", 1);       // 1 auto, 2 force where the kernels can run, 3 off
     if (mode == 3 || nnz < 0 || nnz >= (1ll << 30)) return false;
     // (tests that force or forbid one of the other families mean those)
@@ -1403,18 +1434,35 @@ bool dense_wanted(const DeviceState &d, const csrk_plan_s *plan, const DenseShap
     if (plan && !plan->sorted) return false;
     const int unit = s.bf16 ? 8 : 4;
     const bool wide = s.N % unit == 0 && s.D % unit == 0 && (operands & 15u) == 0;
+    const double vector = vector_us(s, nnz, wide);
     if (mode == 1) {
         if (s.op == kDenseSddmm && !s.bf16 && s.D <= 64 && wide) return false;
-        if (vector_us(s, nnz, wide) < 11.0) return false;     // (less than any configuration is expected to take)
+        if (vector < 11.0) return false;                      // (less than any configuration is expected to take)
     }
     if (!dense_config(s, d.cus, c)) return false;
     if (d.fixed && c->bytes > d.head_floats * sizeof(float)) return false;
     if (mode == 2) return true;
     const double density = (double)nnz / ((double)s.M * (double)s.K);
+    if (wide && dense_is_faster(s, *c, plan != nullptr, density, vector)) return true;
     if (s.op == kDenseSddmm && s.bf16 && s.D <= 64 && wide)
-        return short_bf16_sddmm_us(s, *c, d.cus, (double)nnz, density) * 1.2 < vector_us(s, nnz, wide);
+        return short_bf16_sddmm_us(s, *c, d.cus, (double)nnz, density) * 1.2 < vector;
     const double us = c->us * (s.op == kDenseSddmm ? (0.9 + 0.9 * density) * (wide ? 1.25 : 1.0) : 0.82 + 0.5 * density);
-    return us * 1.1 < vector_us(s, nnz, wide);
+    return us * 1.1 < vector;
+}
+
+// The vector kernels need far less scratch, so a call that cannot have what the matrix-core kernels need is theirs: one
+// that would have to allocate it while its stream is captured, and one for which there is no memory left.
+bool dense_wanted(DeviceState &d, const csrk_plan_s *plan, const DenseShape &s, uintptr_t operands, long long nnz, hipStream_t stream,
+                  DenseConfig *c) {
+    if (!dense_chosen(d, plan, s, operands, nnz, c)) return false;
+    if (d.fixed || c->bytes <= d.head_floats * sizeof(float) || env_int("CSRK_MFMA", 1) == 2) return true;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) == hipSuccess) {
+        if (capture != hipStreamCaptureStatusNone) return false;
+        if (ensure_scratch(d, 1, (c->bytes + sizeof(float) - 1) / sizeof(float)) == CSRK_OK) return true;
+    }
+    (void)hipGetLastError();
+    return false;
 }
 
 csrk_status dense_call(DeviceState &d, const DenseShape &s, const DenseConfig &c, const int32_t *rowptr, const int32_t *colidx,
@@ -1497,7 +1545,7 @@ static csrk_status spmm_run(const csrk_plan_s *plan, const ScratchSource &scratc
     CallRecord rec(1, stream);
     const DenseShape shape{kDenseSpmm, false, M, K, N, 0};
     DenseConfig dense;
-    if (dense_wanted(*d, plan, shape, addresses({B, O}), nnz, &dense)) {
+    if (dense_wanted(*d, plan, shape, addresses({B, O}), nnz, stream, &dense)) {
         rec.begin();
         return dense_call(*d, shape, dense, rowptr, colidx, vals, nullptr, nullptr, B, O, stream);
     }
@@ -1607,7 +1655,7 @@ static csrk_status sddmm_run(const csrk_plan_s *plan, const ScratchSource &scrat
     CallRecord rec(2, stream);
     const DenseShape shape{kDenseSddmm, false, M, K, 0, D};
     DenseConfig dense;
-    if (dense_wanted(*d, plan, shape, addresses({A, B}), nnz, &dense)) {
+    if (dense_wanted(*d, plan, shape, addresses({A, B}), nnz, stream, &dense)) {
         rec.begin();
         return dense_call(*d, shape, dense, rowptr, colidx, vals, A, B, nullptr, P, stream);
     }
@@ -1690,7 +1738,7 @@ static csrk_status fusedmm_run(const csrk_plan_s *plan, const ScratchSource &scr
     CallRecord rec(3, stream);
     const DenseShape shape{kDenseFused, false, M, K, N, D};
     DenseConfig dense;
-    if (dense_wanted(*d, plan, shape, addresses({A, B, C, O}), nnz, &dense)) {
+    if (dense_wanted(*d, plan, shape, addresses({A, B, C, O}), nnz, stream, &dense)) {
         rec.begin();
         return dense_call(*d, shape, dense, rowptr, colidx, vals, A, B, C, O, stream);
     }
@@ -2084,7 +2132,7 @@ static csrk_status spmm_bf16_run(long long nnz, int M, int K, int N, const int32
     CallRecord rec(11, stream);
     const DenseShape shape{kDenseSpmm, true, M, K, N, 0};
     DenseConfig dense;
-    if (dense_wanted(*d, nullptr, shape, addresses({B, O}), nnz, &dense)) {
+    if (dense_wanted(*d, nullptr, shape, addresses({B, O}), nnz, stream, &dense)) {
         rec.begin();
         return dense_call(*d, shape, dense, rowptr, colidx, vals, nullptr, nullptr, B, O, stream);
     }
@@ -2153,7 +2201,7 @@ static csrk_status sddmm_bf16_run(long long nnz, int M, int K, int D, const int3
     CallRecord rec(12, stream);
     const DenseShape shape{kDenseSddmm, true, M, K, 0, D};
     DenseConfig dense;
-    if (dense_wanted(*d, nullptr, shape, addresses({A, B}), nnz, &dense)) {
+    if (dense_wanted(*d, nullptr, shape, addresses({A, B}), nnz, stream, &dense)) {
         rec.begin();
         return dense_call(*d, shape, dense, rowptr, colidx, vals, A, B, nullptr, P, stream);
     }
@@ -2208,7 +2256,7 @@ static csrk_status fusedmm_bf16_run(long long nnz, int M, int K, int D, int N, c
     CallRecord rec(13, stream);
     const DenseShape shape{kDenseFused, true, M, K, N, D};
     DenseConfig dense;
-    if (dense_wanted(*d, nullptr, shape, addresses({A, B, C, O}), nnz, &dense)) {
+    if (dense_wanted(*d, nullptr, shape, addresses({A, B, C, O}), nnz, stream, &dense)) {
         rec.begin();
         return dense_call(*d, shape, dense, rowptr, colidx, vals, A, B, C, O, stream);
     }
