@@ -238,10 +238,11 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
         const DenseKernel f = dense_finish_kernel(s.bf16, s.op == kDenseFused, vec, c.ct, c.halves);
         if (!f.fn) return hipErrorInvalidValue;
         // not many more workgroups than the chip holds at a time (2048 of FusedMM's: 6.8 instead of 5.8 us for the sums of
-        // 16384 x 4096, 128 columns, in 2 ranges), and with long rows to do again some to choose from
+        // 16384 x 4096, 128 columns, in 2 ranges), and with long rows to do again some to choose from; of 16 wavefronts two are on
+        // a CU
         const int rows = a.segs > 1 && a.N < 1024 ? 1024 / a.N : 1;
-        const int blocks = (a.M + rows - 1) / rows, most = s.op == kDenseFused ? 1536 : 1280;
-        hipLaunchKernelGGL(f.fn, dim3(blocks < most ? blocks : most), dim3(256), 0, stream, a);
+        const int blocks = (a.M + rows - 1) / rows, most = c.halves ? 512 : s.op == kDenseFused ? 1536 : 1280;
+        hipLaunchKernelGGL(f.fn, dim3(blocks < most ? blocks : most), dim3(finish_waves(c.halves) * 64), 0, stream, a);
     }
     return hipGetLastError();
 }

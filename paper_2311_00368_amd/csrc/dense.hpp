@@ -41,6 +41,9 @@ struct DenseKernel {
 };
 DenseKernel dense_fused_kernel_f32(int ct, int ds);
 DenseKernel dense_fused_kernel_bf16(int ct, int ds);
+// Wavefronts of a workgroup of the finishing kernel.  After half-precision pieces nearly every call has a few results to do
+// again (kernels_dense_wide.hpp), rows of thousands of entries one after the other: 16 wavefronts share one.
+constexpr int finish_waves(bool halves) { return halves ? 16 : 4; }
 // `vec`: 128-bit accesses of all dense operands and the output
 DenseKernel dense_finish_kernel(bool bf16, bool fused, bool vec, int ct, bool halves);
 

@@ -3,7 +3,7 @@
 //
 // In an ordinary call all that is left of the second part is a look at one word.  Otherwise rows are dealt out to workgroups with
 // the grid's size between them, so that those of one block of S are spread over the chip; a long row's entries are shared by
-// the four wavefronts of a workgroup, of the others each wavefront takes the next one.  (Rows asked for with an atomic
+// the wavefronts of a workgroup, of the others each wavefront takes the next one.  (Rows asked for with an atomic
 // counter, 8 at a time, cost 30 us of atomics on one address where one row was to be done.)
 //
 // Measured on MI355X, against the vector kernels for the same input: 16384^2, 20 %, 512 columns: one pair of entries
@@ -11,6 +11,9 @@
 // 4096^2, 30 %, 128 columns: 72 (172), 173 (300) and 112 us (68).  (With every workgroup doing its own rows again, 65 ms in each
 // of the three and 0.45-7 ms at smaller sizes.)  What it is slow at: rows that are uneven and unordered at once, whose longest
 // ones a workgroup does at its end (FusedMM 8192^2, log-normal rows, 64 columns: 0.45 ms, equal shares 0.17).
+// After half-precision pieces (16384^2, 20 %, 512 columns) every call has some results to do again, a row or two of 3277
+// entries in a workgroup, and their loads one after the other are the kernel's time: with 4 wavefronts 27 us, FusedMM 56, with
+// 16 20 and 42 (whole calls against the six products: 1.64 -> 1.65 times as fast, FusedMM 1.37 -> 1.39; with 8: 1.64, 1.39).
 // Without anything left to do: the time of a kernel that only adds the ranges (16384 x 4096, 128 columns, 2 ranges: 5.8 us),
 // 4.7 us where there are none.
 #pragma once
@@ -19,7 +22,7 @@
 
 namespace csrk {
 
-constexpr int kFinishLong = 1024;       // entries of a row that four wavefronts share whatever else there is to do
+constexpr int kFinishLong = 1024;       // entries of a row that a workgroup's wavefronts share whatever else there is to do
 
 // fused_segment for the entries in special columns alone
 template <int DL, int DT, int VEC, int LG, typename E>
@@ -60,18 +63,19 @@ __device__ __forceinline__ void special_segment(const DenseArgs &a, int row, int
 // 20 %, 128/128 is ordered.)
 // HALVES: after kernels_dense_wide.hpp, whose zeros may be none.
 template <typename E, bool FUSED, int VEC, int LG, bool HALVES = false>
-__global__ __launch_bounds__(kBlockThreads) void dense_finish(DenseArgs a) {
+__global__ __launch_bounds__(finish_waves(HALVES) * kWave) void dense_finish(DenseArgs a) {
+    constexpr int kWaves = finish_waves(HALVES), kThreads = kWaves * kWave;
     constexpr int PL = 16 / VEC;                            // lanes for a 16-column piece
     constexpr int BL = VEC == 1 ? 16 : VEC == 4 ? LG / 2 : LG, BT = LG / BL;    // ... for a block, and tiles of theirs
     constexpr int DL = 16, DT = 128 / (DL * VEC);           // ... for a dot product of up to 128 elements, and tiles of theirs
     constexpr int SL = VEC == 1 ? 16 : 8, ST = 64 / (SL * VEC);     // ... of up to 64
     __shared__ union {
-        RowParts<VEC, LG, 1> whole;
-        RowParts<VEC, BL, BT> block;
-        RowParts<VEC, PL, 1> piece;
+        RowParts<VEC, LG, 1, kWaves> whole;
+        RowParts<VEC, BL, BT, kWaves> block;
+        RowParts<VEC, PL, 1, kWaves> piece;
     } lds;
-    __shared__ float slots[kWavesPerBlock][kWave], vals[kWavesPerBlock][kWave];
-    __shared__ int cols[kWavesPerBlock][kWave], list[kBlockThreads], listed, next;
+    __shared__ float slots[kWaves][kWave], vals[kWaves][kWave];
+    __shared__ int cols[kWaves][kWave], list[kThreads], listed, next;
     const int M = a.M, N = a.N;
     const int lane = lane_id(), wave = uniform(threadIdx.x >> 6);
 
@@ -101,7 +105,7 @@ __global__ __launch_bounds__(kBlockThreads) void dense_finish(DenseArgs a) {
     const bool zeros = HALVES && a.todo[2] != 0, lost = zeros && a.todo[3] != 0;
     if (__builtin_expect(!special && !zeros && a.todo[0] == 0, 1)) {
         if (a.segs > 1)
-            add_ranges(0, (size_t)M * N / kUnit, (size_t)blockIdx.x * kBlockThreads + threadIdx.x, (size_t)gridDim.x * kBlockThreads);
+            add_ranges(0, (size_t)M * N / kUnit, (size_t)blockIdx.x * kThreads + threadIdx.x, (size_t)gridDim.x * kThreads);
         return;
     }
 
@@ -124,7 +128,7 @@ __global__ __launch_bounds__(kBlockThreads) void dense_finish(DenseArgs a) {
     // what is to be done of a row, by this wavefront or with the others of the workgroup (`share`)
     auto redo = [&](int row, int begin, int end, bool share) CSRK_INLINE {
         int s0 = begin, s1 = end;
-        if (share) row_part(begin, end, wave, kWavesPerBlock, s0, s1);
+        if (share) row_part(begin, end, wave, kWaves, s0, s1);
         float *const orow = a.O + (size_t)row * N;
         auto columns = [&](auto lanes, auto tiles, auto &parts, int n) CSRK_INLINE {
             constexpr int LN = decltype(lanes)::value, TN = decltype(tiles)::value;
@@ -137,7 +141,7 @@ __global__ __launch_bounds__(kBlockThreads) void dense_finish(DenseArgs a) {
             } else
                 spmm_segment<VEC, LN, TN>(s0, s1, a.colidx, a.vals, C, N, n, acc);
             fold_groups<VEC, LN, TN>(acc);
-            if (share) add_row_parts<VEC, LN, TN>(parts, wave, wave, kWavesPerBlock, true, orow, N, n, acc);
+            if (share) add_row_parts<VEC, LN, TN, kWaves>(parts, wave, wave, kWaves, true, orow, N, n, acc);
             else store_row<VEC, LN, TN>(orow, N, n, acc);
         };
         if constexpr (FUSED)
@@ -151,7 +155,7 @@ __global__ __launch_bounds__(kBlockThreads) void dense_finish(DenseArgs a) {
                         if ((wave == 0 || !share) && lane < LG && n < N)
 #pragma unroll
                             for (int v = 0; v < VEC; ++v) acc[0][v] += orow[n + v];
-                        if (share) add_row_parts<VEC, LG, 1>(lds.whole, wave, wave, kWavesPerBlock, true, orow, N, n, acc);
+                        if (share) add_row_parts<VEC, LG, 1, kWaves>(lds.whole, wave, wave, kWaves, true, orow, N, n, acc);
                         else store_row<VEC, LG, 1>(orow, N, n, acc);
                     }
         const bool with_zeros = zeros && (lost || (!FUSED && loses_value(begin, end)));
@@ -178,7 +182,7 @@ __global__ __launch_bounds__(kBlockThreads) void dense_finish(DenseArgs a) {
     };
 
     const int step = gridDim.x, rows = (M - (int)blockIdx.x + step - 1) / step;     // rows blockIdx.x, blockIdx.x + step, ...
-    for (int r0 = 0; r0 < rows; r0 += kBlockThreads) {
+    for (int r0 = 0; r0 < rows; r0 += kThreads) {
         if (threadIdx.x == 0) listed = next = 0;
         __syncthreads();
         const int r = r0 + threadIdx.x, row = (int)blockIdx.x + r * step;
@@ -191,7 +195,7 @@ __global__ __launch_bounds__(kBlockThreads) void dense_finish(DenseArgs a) {
             if (m != 0) list[atomicAdd(&listed, 1)] = row;
         }
         if (a.segs > 1)
-            for (int i = r0 + wave; i < rows && i < r0 + kBlockThreads; i += kWavesPerBlock) {
+            for (int i = r0 + wave; i < rows && i < r0 + kThreads; i += kWaves) {
                 const size_t at = (size_t)(blockIdx.x + (size_t)i * step) * N / kUnit;
                 add_ranges(at, at + N / kUnit, lane, kWave);
             }
@@ -200,9 +204,9 @@ __global__ __launch_bounds__(kBlockThreads) void dense_finish(DenseArgs a) {
         const int count = listed;
         for (int q = 0; q < count; ++q) {
             const int row = uniform(list[q]), begin = uniform(a.rowptr[row]), end = uniform(a.rowptr[row + 1]);
-            if (count < kWavesPerBlock || end - begin > kFinishLong) redo(row, begin, end, true);
+            if (count < kWaves || end - begin > kFinishLong) redo(row, begin, end, true);
         }
-        while (count >= kWavesPerBlock) {
+        while (count >= kWaves) {
             int q = 0;
             if (lane == 0) q = atomicAdd(&next, 1);
             q = uniform(q);

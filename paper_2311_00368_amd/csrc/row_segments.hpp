@@ -145,10 +145,10 @@ __device__ __forceinline__ void store_row(float *dst, int N, int n, const float 
 // search, no heads and so no combine step: a call is one launch whose wavefronts go through three or four
 // dependent memory round trips.  For sparse matrices so small that this chain, not throughput, is the whole
 // cost; no balancing of long rows (the host picks it only where a row can hold few chunks).
-template <int VEC, int LG, int T>
+template <int VEC, int LG, int T, int WAVES = kWavesPerBlock>
 struct RowParts {
     static constexpr int kWidth = LG * VEC * T;      // columns one workgroup covers
-    float part[kWavesPerBlock][kWidth];
+    float part[WAVES][kWidth];
 };
 
 // this wavefront's part [s0, s1) of the row [rs, re)
@@ -160,8 +160,8 @@ __device__ __forceinline__ void row_part(int rs, int re, int sub, int wpr, int &
 
 // acc of the `wpr` wavefronts of a row -> O[r, :], added in the order of the parts (wpr > 1 only; all wavefronts
 // of the workgroup come through here together)
-template <int VEC, int LG, int T>
-__device__ __forceinline__ void add_row_parts(RowParts<VEC, LG, T> &lds, int wv, int sub, int wpr, bool valid,
+template <int VEC, int LG, int T, int WAVES>
+__device__ __forceinline__ void add_row_parts(RowParts<VEC, LG, T, WAVES> &lds, int wv, int sub, int wpr, bool valid,
                                               float *orow, int N, int n, float (&acc)[T][VEC]) {
     constexpr int TW = LG * VEC;
     const int lane = lane_id();
