@@ -7,7 +7,7 @@
 // counter, 8 at a time, cost 30 us of atomics on one address where one row was to be done.)
 //
 // Measured on MI355X, against the vector kernels for the same input: 16384^2, 20 %, 512 columns: one pair of entries
-// exchanged 1.50 ms (vector: 10.5, their tiled attempt fails), no row ordered 12.4 (14.2), one NaN in C 1.62 (1.50);
+// exchanged 0.86 ms (vector: 10.7, their tiled attempt fails), every row reversed 11.2 (19.9), one NaN in C 1.28 (1.54);
 // 4096^2, 30 %, 128 columns: 72 (172), 173 (300) and 112 us (68).  (With every workgroup doing its own rows again, 65 ms in each
 // of the three and 0.45-7 ms at smaller sizes.)  What it is slow at: rows that are uneven and unordered at once, whose longest
 // ones a workgroup does at its end (FusedMM 8192^2, log-normal rows, 64 columns: 0.45 ms, equal shares 0.17).

@@ -26,8 +26,8 @@
 // split in half-precision pieces and passed to the pair through LDS as fragments.  Products that their larger piece loses
 // altogether are noticed there.
 //
-// Measured on MI355X, six products of bfloat16 pieces / this: SPMM 16384^2, 20 %, N = 512 1194 / 760 us, 16384 x 8192, 10 %, 512
-// 662 / 436, 32768 x 8192, 20 %, 192 590 / 390; FusedMM 16384^2, 20 %, 512/64 1550 / 1150, 16384 x 8192, 10 %, 512/32 767 / 540.
+// Measured on MI355X, six products of bfloat16 pieces / this: SPMM 16384^2, 20 %, N = 512 1196 / 720 us, 16384 x 8192, 10 %, 512
+// 662 / 436, 32768 x 8192, 20 %, 192 590 / 390; FusedMM 16384^2, 20 %, 512/64 1540 / 1111, 16384 x 8192, 10 %, 512/32 767 / 540.
 // Bound by latency: of the 3000 cycles of a tile the matrix cores are busy for
 // half; the wavefronts that come second on their SIMD take 770 + 1065 cycles for the products, 670 for S, 200 to ask for
 // loads, 215 for the fragments (the first ones wait for them at the barrier).  What gave nothing: S between the matrix
