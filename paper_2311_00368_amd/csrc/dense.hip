@@ -38,7 +38,7 @@ int prepare_blocks(size_t units) {
 
 // where everything lies in the scratch area
 struct Layout {
-    size_t c, b, a, todo, exponents, met, special, tiny, redo, zeros, cuts, partial, bytes;
+    size_t c, b, a, todo, c_most, c_exps, a_exps, b_exps, met, special, redo, cuts, partial, bytes;
     int n_tiles, c_blocks, b_blocks, a_blocks;
     Layout(const DenseShape &s, const DenseConfig &cfg) {
         const bool halves = cfg.halves;
@@ -47,6 +47,7 @@ struct Layout {
         n_tiles = s.op == kDenseSddmm ? 0 : (s.N + bn - 1) / bn * cfg.ct;
         const size_t d = (size_t)cfg.ds * 32, k = up32(s.K), octs = cfg.ds == 3 ? 16 : cfg.ds * 4;
         c_blocks = prepare_blocks(k / 8 * n_tiles * 16);
+        if (halves && c_blocks > n_tiles / 4) c_blocks = c_blocks / (n_tiles / 4) * (n_tiles / 4);
         b_blocks = prepare_blocks(k * octs);
         a_blocks = prepare_blocks(up32(s.M) * octs);
         size_t at = 0;
@@ -55,17 +56,18 @@ struct Layout {
             at += padded(n);
             return was;
         };
-        c = take(k * n_tiles * 16 * (halves ? 4 : pieces));
+        c = take(k * n_tiles * 16 * pieces);
         // (whole tiles of SDDMM's columns)
         b = take((k + kSddmmMaxKt - 32) * d * pieces);
         a = take(up32(s.M) * d * pieces);
         todo = take(16);
-        exponents = take(halves ? 16 : 0);
-        tiny = take(halves ? (size_t)c_blocks * 4 : 0);
+        c_most = take(halves ? (size_t)kRangeParts * n_tiles * 64 : 0);
+        c_exps = take(halves ? (size_t)n_tiles * 128 : 0);
+        a_exps = take(halves && cfg.ds ? (size_t)s.M * 4 : 0);
+        b_exps = take(halves && cfg.ds ? (size_t)s.K * 4 : 0);
         met = take(s.op == kDenseFused ? (size_t)b_blocks * 4 : 0);
         special = take(s.op == kDenseFused ? k : 0);
         redo = take(s.op != kDenseSddmm ? (size_t)cfg.segs * (n_tiles / cfg.ct) * s.M * 2 : 0);
-        zeros = take(halves ? (size_t)cfg.segs * (n_tiles / cfg.ct) * s.M * 2 : 0);
         cuts = take(cfg.segs > 1 ? (size_t)(cfg.segs - 1) * s.M * 4 : 0);
         partial = take(cfg.segs > 1 && s.op != kDenseSddmm ? (size_t)cfg.segs * s.M * s.N * 4 : 0);
         bytes = at;
@@ -89,6 +91,13 @@ DenseKernel wide_kernel(int ct, int ds) {
     CSRK_DENSE_CASE(1)
     CSRK_DENSE_CASE(2)
 #undef CSRK_DENSE_CASE
+    return {nullptr, 0};
+}
+
+DenseKernel again_kernel(int ct, int ds) {
+    if (ds > 0) return dense_again_fused_f32(ct, ds);
+    if (ct == 12) return {dense_kernel<12, 0, 3, true>, DenseCfg<12, 0, 3>::kBytes};
+    if (ct == 16) return {dense_kernel<16, 0, 3, true>, DenseCfg<16, 0, 3>::kBytes};
     return {nullptr, 0};
 }
 
@@ -202,9 +211,14 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
     if (s.op != kDenseSddmm) a.todo = reinterpret_cast<int32_t *>(base + l.todo);
     a.redo = reinterpret_cast<uint16_t *>(base + l.redo);
     if (c.halves) {
-        a.exponents = reinterpret_cast<int32_t *>(base + l.exponents);
-        a.tiny_met = reinterpret_cast<int32_t *>(base + l.tiny);
-        a.zeros = reinterpret_cast<uint16_t *>(base + l.zeros);
+        a.c_most = reinterpret_cast<int32_t *>(base + l.c_most);
+        a.c_exps = reinterpret_cast<int32_t *>(base + l.c_exps);
+        a.a_exps = reinterpret_cast<int32_t *>(base + l.a_exps);
+        a.b_exps = reinterpret_cast<int32_t *>(base + l.b_exps);
+        // 16384^2, 20 %, 512 columns: the finishing kernel takes 0.45 ms for one piece of every row, bfloat16 pieces 1.2 for the
+        // call: as much as for a twelfth of the output.  FusedMM with 64 (the scores anew for every piece): 1.4 and 1.5, a thirtieth.
+        const size_t pieces = (size_t)a.M * l.n_tiles * c.segs / (s.op == kDenseFused ? 30 : 12);
+        a.again_limit = pieces < 0xffffffffu ? (unsigned)pieces : 0xffffffffu;
     }
     a.cuts = reinterpret_cast<int32_t *>(base + l.cuts);
 
@@ -212,7 +226,8 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
                           : s.op == kDenseSpmm  ? (s.bf16 ? spmm_kernel<1>(c.ct) : spmm_kernel<3>(c.ct))
                           : s.op == kDenseSddmm ? (s.bf16 ? sddmm_kernel<1>(c.ds) : sddmm_kernel<3>(c.ds))
                                                 : (s.bf16 ? dense_fused_kernel_bf16(c.ct, c.ds) : dense_fused_kernel_f32(c.ct, c.ds));
-    if (!k.fn) return hipErrorInvalidValue;
+    const DenseKernel again = c.halves ? again_kernel(c.ct, c.ds) : DenseKernel{nullptr, 0};
+    if (!k.fn || (c.halves && !again.fn)) return hipErrorInvalidValue;
     {
         // once per kernel and device (harmless if two threads do it)
         static std::atomic<uint64_t> done[3][3][17][5];
@@ -221,15 +236,28 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
         std::atomic<uint64_t> &seen = done[s.op][s.bf16 ? 1 : c.halves ? 2 : 0][c.ct][c.ds];
         const uint64_t bit = 1ull << (dev & 63);
         if (!(seen.load(std::memory_order_acquire) & bit)) {
-            if (hipError_t e = hipFuncSetAttribute((const void *)k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, k.lds_bytes)) return e;
+            for (const DenseKernel &one : {k, again})
+                if (one.fn)
+                    if (hipError_t e = hipFuncSetAttribute((const void *)one.fn, hipFuncAttributeMaxDynamicSharedMemorySize, one.lds_bytes)) return e;
             seen.fetch_or(bit, std::memory_order_release);
         }
     }
-    const int prepare = a.c_blocks + a.b_blocks + a.a_blocks + (a.segs > 1 ? (a.M + kDenseCutRows - 1) / kDenseCutRows : 0) + (c.halves ? 1 : 0);
+    const int prepare = a.c_blocks + a.b_blocks + a.a_blocks + (a.segs > 1 ? (a.M + kDenseCutRows - 1) / kDenseCutRows : 0);
+    if (c.halves) hipLaunchKernelGGL(dense_range_kernel, dim3(a.n_tiles / 4 * kRangeParts + 1), dim3(256), 0, stream, a);
     if (s.bf16) hipLaunchKernelGGL(dense_prepare_kernel<bf16_t>, dim3(prepare), dim3(256), 0, stream, a);
     else if (c.halves) hipLaunchKernelGGL((dense_prepare_kernel<float, true>), dim3(prepare), dim3(256), 0, stream, a);
     else hipLaunchKernelGGL(dense_prepare_kernel<float>, dim3(prepare), dim3(256), 0, stream, a);
-    hipLaunchKernelGGL(k.fn, dim3((unsigned)a.row_blocks * a.col_blocks * a.segs), dim3(kDenseThreads), k.lds_bytes, stream, a);
+    const dim3 jobs((unsigned)a.row_blocks * a.col_blocks * a.segs);
+    hipLaunchKernelGGL(k.fn, jobs, dim3(kDenseThreads), k.lds_bytes, stream, a);
+    if (c.halves) {
+        // (few workgroups to find that there is nothing to do; no cuts)
+        DenseArgs b = a;
+        b.c_blocks = b.c_blocks < 192 ? b.c_blocks : 192;
+        b.b_blocks = b.b_blocks < 32 ? b.b_blocks : 32;
+        b.a_blocks = b.a_blocks < 32 ? b.a_blocks : 32;
+        hipLaunchKernelGGL((dense_prepare_kernel<float, false, true>), dim3(b.c_blocks + (b.d_steps ? b.b_blocks + b.a_blocks : 0)), dim3(256), 0, stream, b);
+        hipLaunchKernelGGL(again.fn, jobs, dim3(kDenseThreads), again.lds_bytes, stream, b);
+    }
     if (s.op != kDenseSddmm) {
         const int unit = s.bf16 ? 8 : 4;
         uintptr_t at = reinterpret_cast<uintptr_t>(out) | reinterpret_cast<uintptr_t>(C);
@@ -238,11 +266,11 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
         const DenseKernel f = dense_finish_kernel(s.bf16, s.op == kDenseFused, vec, c.ct, c.halves);
         if (!f.fn) return hipErrorInvalidValue;
         // not many more workgroups than the chip holds at a time (2048 of FusedMM's: 6.8 instead of 5.8 us for the sums of
-        // 16384 x 4096, 128 columns, in 2 ranges), and with long rows to do again some to choose from; of 16 wavefronts two are on
-        // a CU
+        // 16384 x 4096, 128 columns, in 2 ranges), and with long rows to do again some to choose from; of 8 and 16 wavefronts two
+        // are on a CU
         const int rows = a.segs > 1 && a.N < 1024 ? 1024 / a.N : 1;
         const int blocks = (a.M + rows - 1) / rows, most = c.halves ? 512 : s.op == kDenseFused ? 1536 : 1280;
-        hipLaunchKernelGGL(f.fn, dim3(blocks < most ? blocks : most), dim3(finish_waves(c.halves) * 64), 0, stream, a);
+        hipLaunchKernelGGL(f.fn, dim3(blocks < most ? blocks : most), dim3(finish_waves(c.halves, s.op == kDenseFused) * 64), 0, stream, a);
     }
     return hipGetLastError();
 }

@@ -61,10 +61,10 @@ __device__ __forceinline__ void special_segment(const DenseArgs &a, int row, int
 // take an entry and many entries are under way: 8 elements of a lane for a dot product, 8 floats of a lane for the sums.  (16
 // elements of FP32 rows of more than 64 took 165 registers, and 652 instead of 577 us where no row of FusedMM 16384 x 4096,
 // 20 %, 128/128 is ordered.)
-// HALVES: after kernels_dense_wide.hpp, whose zeros may be none.
+// HALVES: after kernels_dense_wide.hpp.
 template <typename E, bool FUSED, int VEC, int LG, bool HALVES = false>
-__global__ __launch_bounds__(finish_waves(HALVES) * kWave) void dense_finish(DenseArgs a) {
-    constexpr int kWaves = finish_waves(HALVES), kThreads = kWaves * kWave;
+__global__ __launch_bounds__(finish_waves(HALVES, FUSED) * kWave) void dense_finish(DenseArgs a) {
+    constexpr int kWaves = finish_waves(HALVES, FUSED), kThreads = kWaves * kWave;
     constexpr int PL = 16 / VEC;                            // lanes for a 16-column piece
     constexpr int BL = VEC == 1 ? 16 : VEC == 4 ? LG / 2 : LG, BT = LG / BL;    // ... for a block, and tiles of theirs
     constexpr int DL = 16, DT = 128 / (DL * VEC);           // ... for a dot product of up to 128 elements, and tiles of theirs
@@ -101,28 +101,17 @@ __global__ __launch_bounds__(finish_waves(HALVES) * kWave) void dense_finish(Den
         }
     };
     const bool special = FUSED && a.todo[1] != 0;
-    // pieces with zeros that may be none: values of C were lost, or it depends on the row's values (FusedMM has seen these)
-    const bool zeros = HALVES && a.todo[2] != 0, lost = zeros && a.todo[3] != 0;
-    if (__builtin_expect(!special && !zeros && a.todo[0] == 0, 1)) {
+    if (__builtin_expect(!special && a.todo[0] == 0, 1)) {
         if (a.segs > 1)
             add_ranges(0, (size_t)M * N / kUnit, (size_t)blockIdx.x * kThreads + threadIdx.x, (size_t)gridDim.x * kThreads);
         return;
     }
 
     const int bn = a.bn, pieces = bn / 16;
-    auto marks_of = [&](const uint16_t *all, int row, int cb) CSRK_INLINE {
+    auto marks = [&](int row, int cb) CSRK_INLINE {
         unsigned m = 0;
-        for (int s = 0; s < a.segs; ++s) m |= all[((size_t)s * a.col_blocks + cb) * M + row];
+        for (int s = 0; s < a.segs; ++s) m |= a.redo[((size_t)s * a.col_blocks + cb) * M + row];
         return m;
-    };
-    auto marks = [&](int row, int cb) CSRK_INLINE { return marks_of(a.redo, row, cb); };
-    // whether the row has a value that the larger of two half-precision pieces loses
-    auto loses_value = [&](int begin, int end) CSRK_INLINE {
-        if (!a.vals) return false;
-        const float scale = power_of_two(uniform(a.exponents[0]));
-        bool some = false;
-        for (int p = begin + lane; p < end; p += kWave) some |= a.vals[p] != 0.f && ((unsigned)half_pieces(a.vals[p] * scale) & 0x7fffu) == 0;
-        return __any(some) != 0;
     };
     const E *A = static_cast<const E *>(a.A), *B = static_cast<const E *>(a.B), *C = static_cast<const E *>(a.C);
     // what is to be done of a row, by this wavefront or with the others of the workgroup (`share`)
@@ -158,10 +147,8 @@ __global__ __launch_bounds__(finish_waves(HALVES) * kWave) void dense_finish(Den
                         if (share) add_row_parts<VEC, LG, 1, kWaves>(lds.whole, wave, wave, kWaves, true, orow, N, n, acc);
                         else store_row<VEC, LG, 1>(orow, N, n, acc);
                     }
-        const bool with_zeros = zeros && (lost || (!FUSED && loses_value(begin, end)));
         for (int cb = 0; cb < a.col_blocks; ++cb) {
-            unsigned m = uniform(marks(row, cb));
-            if (with_zeros) m |= uniform(marks_of(a.zeros, row, cb));
+            const unsigned m = uniform(marks(row, cb));
             if (m == 0) continue;
             using Tiles = std::integral_constant<int, BT>;
             using Lanes = std::integral_constant<int, BL>;
@@ -188,10 +175,7 @@ __global__ __launch_bounds__(finish_waves(HALVES) * kWave) void dense_finish(Den
         const int r = r0 + threadIdx.x, row = (int)blockIdx.x + r * step;
         if (r < rows) {
             unsigned m = special;
-            for (int cb = 0; cb < a.col_blocks; ++cb) {
-                m |= marks(row, cb);
-                if (zeros) m |= marks_of(a.zeros, row, cb);
-            }
+            for (int cb = 0; cb < a.col_blocks; ++cb) m |= marks(row, cb);
             if (m != 0) list[atomicAdd(&listed, 1)] = row;
         }
         if (a.segs > 1)

@@ -6,16 +6,24 @@
 // the bytes of C in LDS, and half a dozen instructions less for every cell of S, since S's values are split where they are
 // scattered and not where they are read.  What that costs:
 //
-// - Range.  Half precision has exponents from 2^-14 (2^-24) to 2^15, so S's values and C are multiplied by powers of two that
-//   bring the largest of 1024 sampled values of each to [2^8, 2^9).  Magnitudes of 2^16 and more become infinities, which show
-//   in every result that they are part of; values below 2^-12 lose bits, 2^-36 of them at most.  So a result is computed again,
-//   by the finishing kernel, where it is not finite or where its magnitude (scaled) is below 1, which neither values of the
-//   sampled size nor sums of their products are but for one in 10^5 or fewer (one product of two uniform values: 10^-4); and results that are exactly zero where C
-//   or the row of S has values that the larger piece loses altogether (rows without entries aside).
+// - Range.  Half precision has exponents from 2^-14 (2^-24) to 2^15.  Magnitudes of 2^16 and more become infinities, which show in
+//   every result that they are part of; the pieces of a value from 2^-12 on are off by 2^-23 of it, of a smaller one by up to
+//   2^-36.  So operands are multiplied by powers of two: every column of C by its own, which brings its largest value to
+//   [2^14, 2^15) (dense_range_kernel); every row of S by its own, after samples of its values and of all of them, which leaves
+//   them room upwards (kRowExp); FusedMM's rows of A and B by theirs, and the rows of C by the inverse of B's.  The values below
+//   2^-12 are counted for every column of C and row of S (of FusedMM's products).  With n and t of them the error of a result is
+//   at most (n + t) (2^-36 + 2^-37) 2^16, so a result of 4 (n + t) and more is off by no more than 2^-21 of its terms'
+//   magnitudes; smaller ones, and those that are not finite, are computed again by the finishing kernel, entry by entry.  Of
+//   uniform or normal values hardly one call in ten has such a result.
+// - If more than a twelfth of the output (FusedMM: a thirtieth) would be computed again, the call is done again with six products of bfloat16 pieces
+//   (dense_kernel, AGAIN), which have the range of floats: two launches that look at one word otherwise, 4.5 us each.  At
+//   16384^2, 20 %, 512 columns, FusedMM with dot products of 64: all values of C, S and B from a Cauchy distribution 2.1 and 2.6 ms
+//   (computed again entry by entry: 11.4 and 15.3); one value of C 10^9 times the others 1.24 and 2.5; S log-normal with sigma 3
+//   2.0 and 3.3.
 // - Rounding of sums.  Products of bfloat16 pieces have 16 bits and mostly add up exactly inside an instruction; these have 22,
-//   and long sums are 1.75 times as far from FP64.  So the sums are put away in memory on the way, three times where rows are
-//   long (error at 16384^2, 20 %: 0.86 times that of the six products in one accumulator, which is rounded the less the fewer
-//   entries a tile has) and seven times elsewhere (16384 x 8192, 10 %: 0.91, with three 1.19).
+//   and long sums are 1.75 times as far from FP64.  So the sums are put away in memory on the way (kWideLongRow).  Error in the
+//   2-norm, operands U[-1,1], six products / this: SPMM 16384^2, 20 %, 512 columns 4.2e-7 / 3.6e-7, 16384 x 8192, 10 % 1.81e-7 /
+//   1.64e-7; FusedMM 16384^2, 20 %, 512/64 5.3e-7 / 3.7e-7, 16384 x 8192, 10 %, 512/32 2.44e-7 / 2.24e-7.
 //
 // A workgroup is 8 wavefronts, 128 rows and CT * 16 columns: a pair of wavefronts shares 32 rows, each has half of the columns
 // (two rows' fragments for every read of C's pieces: 2 reads per 6 products; with 16 rows, 2 per 3, the reads bound the kernel).
@@ -23,8 +31,7 @@
 // tiles ahead; S's tiles are scattered two tiles ahead in two buffers; one barrier per tile.
 //
 // FusedMM's scores stay six products of bfloat16 pieces, each wavefront those of its own 16 rows; times S's values they are
-// split in half-precision pieces and passed to the pair through LDS as fragments.  Products that their larger piece loses
-// altogether are noticed there.
+// split in half-precision pieces and passed to the pair through LDS as fragments.
 //
 // Measured on MI355X, six products of bfloat16 pieces / this: SPMM 16384^2, 20 %, N = 512 1196 / 720 us, 16384 x 8192, 10 %, 512
 // 662 / 436, 32768 x 8192, 20 %, 192 590 / 390; FusedMM 16384^2, 20 %, 512/64 1540 / 1111, 16384 x 8192, 10 %, 512/32 767 / 540.
@@ -42,10 +49,8 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ f32x4 mfma(f16x8 a, f16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
 
-// scaled results below this are computed again
-constexpr float kWideSmall = 1.f;
 // mean entries of a row in a range from which on the sums are put away three times on the way and not seven (FusedMM's six
-// products were the further off: 16384 x 8192, 10 %, 512/32 2.5e-7, this 2.2e-7 with three and 1.8e-7 with seven)
+// products were the further off: 16384 x 8192, 10 %, 512/32 2.4e-7, this 2.2e-7 with three and 1.8e-7 with seven)
 constexpr int kWideLongRow = 2400, kWideLongFusedRow = 700;
 
 // DS: 32-element steps of the dot products (0: SPMM)
@@ -65,12 +70,89 @@ struct WideCfg {
     static constexpr int kOffB = kOffRaw + (DS == 0 ? 0 : kDenseWaves * kSWave);
     static constexpr int kOffCount = kOffB + 2 * kIssueB * kDenseThreads * 16;
     static constexpr int kOffMarks = kOffCount + kDenseWaves * 4;
-    static constexpr int kBytes = kOffMarks + 2 * kDenseBM * 4;
+    static constexpr int kOffCols = kOffMarks + 3 * kDenseBM * 4;
+    static constexpr int kBytes = kOffCols + BN * 8;
     static_assert(CT % 4 == 0 && kBytes <= 160 * 1024, "LDS of a gfx950 CU");
 };
-// FusedMM: what the exponent of S's values is lowered by, so that products of sampled sizes with the scores, of dot products of
-// D elements, are about as large as C's values
-__device__ __forceinline__ int wide_score_exponent(int D) { return 17 + (33 - __clz(D)) / 2; }
+// What a row's largest value is expected to be brought to (FusedMM: times the scores' expected size): the largest of 1024 of all of
+// S's values, or of 16 of the row's if that is more; where the row's is below the other by more than 2^kRowOwn, rows differ in
+// size, and it is 2^kRowAbove times the row's.  Samples are four values in a row for each lane of a quad: 32 places of one value
+// each took 9 us at 16384^2, 20 %, 512 columns, for a cache line each.
+constexpr int kRowExp = 8, kRowOwn = 8, kRowAbove = 3;
+constexpr unsigned kGolden = 2654435769u;
+// FusedMM: what the exponent of S's values is lowered by: dot products of D elements of up to 2^9 each are about sqrt(D) times as
+// large as one of their terms
+__device__ __forceinline__ int wide_score_exponent(int D) { return 2 * kDotExp + 1 + (33 - __clz(D)) / 2; }
+// Results below this for each value that the pieces of their row of S and column of C do not hold in full are computed again.
+constexpr float kTinyUnit = 4.f;
+constexpr int kNoTiny = -(1 << 28);     // of a row or column whose results are zeros
+
+// Largest exponents of C's columns, by parts of K; FusedMM: of the rows of C divided by the powers of two that B's are multiplied
+// by, which the first column group's workgroups leave for the preparation.  One workgroup more samples S's values.  Bound by the
+// latency of memory: 9 us for the 33 MB of 16384 x 512 (12 with half as many parts).
+__global__ __launch_bounds__(256) void dense_range_kernel(DenseArgs a) {
+    constexpr int kChunk = 256;
+    __shared__ int most[4][64], row_exps[kChunk];
+    const int lane = lane_id(), wave = uniform(threadIdx.x >> 6);
+    const int groups = a.n_tiles / 4, group = blockIdx.x % groups, part = blockIdx.x / groups, col = group * 64 + lane;
+    const int rows = (a.K + kRangeParts - 1) / kRangeParts, end = (part + 1) * rows < a.K ? (part + 1) * rows : a.K;
+    const float *src = static_cast<const float *>(a.C) + (col < a.N ? col : a.N - 1);
+    int m = -kZeros;
+    if (blockIdx.x == groups * kRangeParts) {
+        // the largest of 1024 of S's values, from places that follow no pattern (multiples of the golden section)
+        unsigned x = a.vals ? 0u : bits_of(1.f);
+        const unsigned n = (unsigned)a.rowptr[a.M];
+        if (a.vals && n > 0)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x = larger(x, finite_magnitude(a.vals[__umulhi((threadIdx.x * 4u + i) * kGolden, n)]));
+#pragma unroll
+        for (int d = kWave / 2; d > 0; d /= 2) x = larger(x, __shfl_xor(x, d));
+        if (lane == 0) most[0][wave] = (int)x;
+        __syncthreads();
+        if (threadIdx.x == 0) a.todo[3] = max(max(most[0][0], most[0][1]), max(most[0][2], most[0][3]));
+        return;
+    }
+    for (int k0 = part * rows; k0 < end; k0 += kChunk) {
+        const int stop = k0 + kChunk < end ? k0 + kChunk : end;
+        if (a.d_steps) {
+            const float *B = static_cast<const float *>(a.B) + (lane < a.D ? lane : a.D - 1);
+            __syncthreads();
+            for (int r = wave * (kChunk / 4); r < (wave + 1) * (kChunk / 4) && k0 + r < stop; r += 8) {
+                unsigned x[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) x[i] = finite_magnitude(B[(size_t)(k0 + r + i < stop ? k0 + r + i : stop - 1) * a.D]);
+#pragma unroll
+                for (int d = kWave / 2; d > 0; d /= 2)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) x[i] = larger(x[i], __shfl_xor(x[i], d));
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (lane == 0) row_exps[r + i] = x[i] == 0 ? kZeros : exponent_to(x[i], kDotExp);
+            }
+            __syncthreads();
+            if (group == 0 && k0 + (int)threadIdx.x < stop) a.b_exps[k0 + threadIdx.x] = row_exps[threadIdx.x];
+        }
+        constexpr int kRows = 16;       // under way at a time
+        for (int k = k0 + wave; k < stop; k += 4 * kRows) {
+            float x[kRows];
+#pragma unroll
+            for (int i = 0; i < kRows; ++i) x[i] = src[(size_t)(k + 4 * i < stop ? k + 4 * i : stop - 1) * a.N];
+#pragma unroll
+            for (int i = 0; i < kRows; ++i) {
+                const unsigned b = finite_magnitude(x[i]);
+                const int row = a.d_steps ? row_exps[(k + 4 * i < stop ? k + 4 * i : stop - 1) - k0] : 0;
+                m = b == 0 || row == kZeros ? m : max(m, (int)larger(b >> 23, 1u) - row);
+            }
+        }
+    }
+    most[wave][lane] = m;
+    __syncthreads();
+    if (wave == 0) {
+        m = max(max(most[0][lane], most[1][lane]), max(most[2][lane], most[3][lane]));
+        a.c_most[(size_t)part * a.n_tiles * 16 + col] = col < a.N ? m : -kZeros;
+        if (part == 0) a.c_exps[2 * col + 1] = 0;
+    }
+}
 
 template <int CT, int DS>
 __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs a) {
@@ -105,22 +187,26 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
     for (int i = 0; i < (L::kBufs - 1) * L::kIssue; ++i) issue_c(job.kb + i / L::kIssue * kDenseK, i / L::kIssue, i % L::kIssue);
 #pragma unroll
     for (int i = 0; i < 2 * L::kIssueB; ++i) issue_b(job.kb + i / L::kIssueB * kDenseK, i / L::kIssueB, i % L::kIssueB);
+    // which pieces of which rows are to be computed again (every workgroup's last word), the exponents of the rows' results, the
+    // values that pieces do not hold in full
+    unsigned *const marks = reinterpret_cast<unsigned *>(dlds + L::kOffMarks);
+    int *const row_exps = reinterpret_cast<int *>(marks + kDenseBM), *const row_tiny = row_exps + kDenseBM;
+    if (threadIdx.x < kDenseBM) marks[threadIdx.x] = 0;
+    // the columns' exponents and such values
+    int2 *const columns = reinterpret_cast<int2 *>(dlds + L::kOffCols);
+    if (threadIdx.x < L::BN) {
+        const int2 c = reinterpret_cast<const int2 *>(a.c_exps)[job.cb * L::BN + threadIdx.x];
+        columns[threadIdx.x] = c.x != kZeros ? c : make_int2(0, c.y >= kNotFinite ? c.y : kNoTiny);
+    }
     bf16x8 af[kFused ? DS : 1][3];
     if constexpr (kFused) dense_load_a<DS, 3>(a, job.row0 + wave * kDenseRows, af);
 
-    int value_exponent = uniform(a.exponents[0]);
-    if constexpr (kFused) {
-        value_exponent -= wide_score_exponent(a.D);
-        value_exponent = value_exponent < -126 ? -126 : value_exponent;
-    }
     Entries<true, !kFused> e;
     int several;                // rows with more than one entry
     {
         const unsigned bytes = dense_entry_bytes(a, job);
         e.cols = dense_view(job.ci, bytes);
         e.vals = dense_view(a.vals ? (const void *)(a.vals + job.e0) : (const void *)job.ci, a.vals ? bytes : 0u);
-        e.scale = power_of_two(value_exponent);
-        e.one = a.vals ? 0.f : e.scale;
         e.q4 = (lane & 3) * 4;
         e.ke = job.ke;
         e.bad = 0;
@@ -129,6 +215,34 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
         e.end = range.y;
         several = (int)__popcll(__ballot(range.y - range.x > 1)) / 4;
         e.load();
+        const unsigned all = (unsigned)uniform(a.todo[3]);
+        unsigned most = all;
+        const int len = range.y - range.x;
+        if (a.vals) {
+            const int places = len > 4 ? len - 3 : len > 0 ? 1 : 0;
+            const f32x4 x = load_f32x4(e.vals, (unsigned)(range.x + (int)__umulhi((unsigned)lane * kGolden, (unsigned)places)) * 4u, 0);
+            most = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) most = larger(most, j < len ? finite_magnitude(x[j]) : 0u);
+            most = larger(most, __shfl_xor(most, 1));
+            most = larger(most, __shfl_xor(most, 2));
+            const bool own = most != 0 && (int)(all >> 23) - (int)(most >> 23) > kRowOwn;
+            most = own ? most + ((unsigned)kRowAbove << 23) : larger(most, all);
+        }
+        int value_exponent = exponent_to(most, kFused ? kRowExp - wide_score_exponent(a.D) : kRowExp);
+        value_exponent = value_exponent < -126 ? -126 : value_exponent;
+        e.scale = power_of_two(value_exponent);
+        e.one = a.vals ? 0.f : e.scale;
+        e.full_key = tiny_key(ldexpf(1.f, kFullExp - value_exponent));
+        e.tiny = 0;
+        const int r = wave * kDenseRows + (lane >> 2);
+        // (Rows without entries: results of zero are what they should be.  FusedMM, values scaled so far down that the smallest
+        // normal float would become a zero: all of the row's.)
+        if ((lane & 3) == 0) {
+            row_tiny[r] = len == 0 ? kNoTiny : kFused && value_exponent < -23 ? len : 0;
+            if constexpr (kFused) value_exponent += a.a_exps[job.row0 + r < M ? job.row0 + r : M - 1];
+            row_exps[r] = value_exponent;
+        }
     }
     char *const swave = dlds + (kFused ? L::kOffRaw : L::kOffS) + wave * kSWave;
     const unsigned row_at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)(swave + (lane >> 2) * kSRow);
@@ -170,13 +284,14 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
     // FusedMM: the wavefront's own 16 rows times their scores, as fragments for its pair
     const char *const own = swave + (lane & 15) * kSRow + (lane >> 4) * 16, *const bfrag = dlds + L::kOffB + lane * 16;
     char *const frag_to = dlds + L::kOffS + wave * 2048 + lane * 16;
-    unsigned least = ~0u;       // of the products' magnitudes (shifted by one and less one: zeros are the largest)
+    int tiny = 0;               // products that their pieces do not hold in full
     auto score = [&](int buf) CSRK_INLINE {
 #pragma clang fp contract(off)
         if constexpr (kFused) {
             f32x4 x[2], p[2];
             dense_scores<DS, 3>(bfrag + buf * (L::kIssueB * kDenseThreads * 16), af, p);
             u32x4 h, l;
+            unsigned least = ~0u;
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 x[i] = *reinterpret_cast<const f32x4 *>(own + i * 64);
@@ -186,11 +301,14 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
                     const unsigned u = half_pieces(p[i][2 * j]), v = half_pieces(p[i][2 * j + 1]);
                     h[2 * i + j] = lower_halves(u, v);
                     l[2 * i + j] = upper_halves(u, v);
-                    const unsigned y = (bits_of(p[i][2 * j]) << 1) - 1, z = (bits_of(p[i][2 * j + 1]) << 1) - 1;
+                    const unsigned y = tiny_key(p[i][2 * j]), z = tiny_key(p[i][2 * j + 1]);
                     least = y < least ? y : least;
                     least = z < least ? z : least;
                 }
             }
+            if (__builtin_expect(__any(least < tiny_key(power_of_two(kFullExp))), 0))
+#pragma unroll
+                for (int j = 0; j < 8; ++j) tiny += tiny_key(p[j >> 2][j & 3]) < tiny_key(power_of_two(kFullExp)) ? 1 : 0;
             *reinterpret_cast<u32x4 *>(frag_to + buf * L::kS) = h;
             *reinterpret_cast<u32x4 *>(frag_to + buf * L::kS + 1024) = l;
         }
@@ -209,25 +327,20 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
     };
     clear();
 
-    // which pieces of which rows are to be computed again, and which have zeros; every workgroup's last word
-    unsigned *const marks = reinterpret_cast<unsigned *>(dlds + L::kOffMarks), *const zeros = marks + kDenseBM;
-    if (threadIdx.x < kDenseBM) marks[threadIdx.x] = zeros[threadIdx.x] = 0;
-    auto say = [&](unsigned again, unsigned zero) CSRK_INLINE {
+    auto say = [&](unsigned again) CSRK_INLINE {
         const int t = threadIdx.x, row = job.row0 + t;
+        // (the upper half of the word: pieces that bfloat16 pieces would not leave)
+        int pieces = row < M ? (int)__popc(again >> 16) : 0;
+        if (__any(pieces != 0)) {
+#pragma unroll
+            for (int d = kWave / 2; d > 0; d /= 2) pieces += __shfl_xor(pieces, d);
+            if (t % kWave == 0) atomicAdd(&a.todo[2], pieces);
+        }
         if (t < kDenseBM && row < M) {
-            if (zero != 0) {            // (rows without entries have nothing but)
-                const int2 range = dense_row_range(a, job, t);
-                if (range.x >= range.y) zero = 0;
-            }
-            const size_t at = ((size_t)job.seg * a.col_blocks + job.cb) * M + row;
-            a.redo[at] = (uint16_t)again;
-            a.zeros[at] = (uint16_t)zero;
+            a.redo[((size_t)job.seg * a.col_blocks + job.cb) * M + row] = (uint16_t)again;
             // (plain stores of the same word: see kernels_dense.hpp)
             if (again != 0) a.todo[0] = 1;
-            if (zero != 0) a.todo[2] = 1;
         }
-        for (int i = blockIdx.x * kDenseThreads + t; i < a.c_blocks; i += gridDim.x * kDenseThreads)
-            if (a.tiny_met[i] != 0) a.todo[3] = 1;
         if constexpr (kFused)
             for (int i = blockIdx.x * kDenseThreads + t; i < a.b_blocks; i += gridDim.x * kDenseThreads)
                 if (a.special_met[i] != 0) a.todo[1] = 1;
@@ -289,7 +402,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
     {
         // (half of the rows with more than one entry out of order: see kernels_dense.hpp)
         const i32x4 n = counts[0] + counts[1];
-        if (uniform(n[0] + n[1] + n[2] + n[3]) > 0) return say(0xffffu, 0u);
+        if (uniform(n[0] + n[1] + n[2] + n[3]) > 0) return say(0xffffu);
     }
     if constexpr (kFused) score(0);
     else fetch(0);
@@ -357,53 +470,60 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // (LDS must not be written to behind the workgroup's end)
     if (put_away) add_earlier();
-    const int back = -(value_exponent + uniform(a.exponents[1]) + (kFused ? uniform(a.exponents[2]) + uniform(a.exponents[3]) : 0));
     const int at = lane_id_again();
-    bool odd = false;           // a result that is not finite, small or zero
-    auto odd_bits = [&](float y) CSRK_INLINE { return (bits_of(y) << 1) - (bits_of(kWideSmall) << 1) >= (bits_of(kDenseHuge) - bits_of(kWideSmall)) << 1; };
-#pragma unroll
-    for (int t = 0; t < PW; ++t) {
-        const unsigned o = column_at(t);
-#pragma unroll
-        for (int r = 0; r < 2; ++r)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float y = result(r, t, i);
-                odd |= odd_bits(y);
-                __builtin_amdgcn_raw_buffer_store_b32(bits_of(ldexpf(y, back)), oview.rsrc, o, row_offset(r, i), 0);
-            }
+    if constexpr (kFused) {
+        tiny += __shfl_xor(tiny, 16);
+        tiny += __shfl_xor(tiny, 32);
+        if (at < kDenseRows && tiny != 0) row_tiny[wave * kDenseRows + at] += tiny;
+    } else {
+        int n = e.tiny;
+        n += __shfl_xor(n, 1);
+        n += __shfl_xor(n, 2);
+        if ((at & 3) == 0 && n != 0) row_tiny[wave * kDenseRows + (at >> 2)] += 4 * n;
     }
     const unsigned long long unused = __ballot(e.pos < e.end) | e.bad;
     if (__builtin_expect(unused != 0, 0) && at < kDenseRows && ((unsigned)(unused >> at * 4) & 0xfu) != 0)
         atomicOr(&marks[wave * kDenseRows + at], 0xffffu);
+    __syncthreads();
+    auto column_of = [&](int t) CSRK_INLINE { return columns[(half * PW + t) * 16 + (at & 15)]; };
+    // four rows' words
+    auto rows_of = [&](const int *words, int r) CSRK_INLINE { return *reinterpret_cast<const i32x4 *>(words + pair * 32 + r * 16 + (at >> 4) * 4); };
+    auto odd_result = [&](float y, int tinies) CSRK_INLINE { return !(fabsf(y) < kDenseHuge) || fabsf(y) < kTinyUnit * (float)tinies; };
+    bool odd = false;
+#pragma unroll
+    for (int t = 0; t < PW; ++t) {
+        const unsigned o = column_at(t);
+        const int2 c = column_of(t);
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const i32x4 exps = rows_of(row_exps, r), tinies = rows_of(row_tiny, r);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float y = result(r, t, i);
+                odd |= odd_result(y, c.y + tinies[i]);
+                __builtin_amdgcn_raw_buffer_store_b32(bits_of(ldexpf(y, -(exps[i] + c.x))), oview.rsrc, o, row_offset(r, i), 0);
+            }
+        }
+    }
     if (__builtin_expect(__any(odd), 0))
 #pragma unroll
-        for (int t = 0; t < PW; ++t)
+        for (int t = 0; t < PW; ++t) {
+            const bool inside = column_at(t) != 0xf0000000u;
+            const int2 c = column_of(t);
 #pragma unroll
-            for (int r = 0; r < 2; ++r)
+            for (int r = 0; r < 2; ++r) {
+                const i32x4 tinies = rows_of(row_tiny, r);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float y = result(r, t, i);
-                    const bool inside = column_at(t) != 0xf0000000u;
-                    const unsigned long long again = __ballot(inside && y != 0.f && odd_bits(y)), zero = __ballot(inside && y == 0.f);
-                    const int row = pair * 32 + r * 16 + (at >> 4) * 4 + i;
-                    if ((at & 15) == 0) {
-                        if ((again >> at & 0xffffu) != 0) atomicOr(&marks[row], 1u << (half * PW + t));
-                        if ((zero >> at & 0xffffu) != 0) atomicOr(&zeros[row], 1u << (half * PW + t));
-                    }
+                    const bool odd = inside && odd_result(result(r, t, i), c.y + tinies[i]);
+                    const unsigned long long again = __ballot(odd), other = __ballot(odd && c.y < kNotFinite);
+                    if ((at & 15) == 0 && (again >> at & 0xffffu) != 0)
+                        atomicOr(&marks[pair * 32 + r * 16 + (at >> 4) * 4 + i], ((other >> at & 0xffffu) != 0 ? 0x10001u : 1u) << (half * PW + t));
                 }
-    // FusedMM: rows with products that their larger piece loses
-    unsigned *const lossy = reinterpret_cast<unsigned *>(counts);
-    if constexpr (kFused) {
-        unsigned long long rows = __ballot(least < (bits_of(0x1p-24f) << 1) - 1);
-        rows |= rows >> 32;
-        if (at == 0) lossy[wave] = (unsigned)(rows | rows >> 16) & 0xffffu;
-    }
+            }
+        }
     __syncthreads();
-    unsigned again = threadIdx.x < kDenseBM ? marks[threadIdx.x] : 0u, zero = threadIdx.x < kDenseBM ? zeros[threadIdx.x] : 0u;
-    if constexpr (kFused)
-        if (threadIdx.x < kDenseBM && (lossy[threadIdx.x >> 4] >> (threadIdx.x & 15) & 1u) != 0) again |= zero;
-    say(again, zero);
+    say(threadIdx.x < kDenseBM ? marks[threadIdx.x] : 0u);
 }
 
 }  // namespace csrk
