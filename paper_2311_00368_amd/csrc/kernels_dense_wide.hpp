@@ -20,10 +20,11 @@
 //   16384^2, 20 %, 512 columns, FusedMM with dot products of 64: all values of C, S and B from a Cauchy distribution 2.1 and 2.6 ms
 //   (computed again entry by entry: 11.4 and 15.3); one value of C 10^9 times the others 1.24 and 2.5; S log-normal with sigma 3
 //   2.0 and 3.3.
+// - Rows of few entries: 23 bits instead of 24 show, and they are computed again (kWideShortRow).
 // - Rounding of sums.  Products of bfloat16 pieces have 16 bits and mostly add up exactly inside an instruction; these have 22,
-//   and long sums are 1.75 times as far from FP64.  So the sums are put away in memory on the way (kWideLongRow).  Error in the
+//   and long sums are 1.75 times as far from FP64.  So the sums are put away in memory on the way (wide_parts).  Error in the
 //   2-norm, operands U[-1,1], six products / this: SPMM 16384^2, 20 %, 512 columns 4.2e-7 / 3.6e-7, 16384 x 8192, 10 % 1.81e-7 /
-//   1.64e-7; FusedMM 16384^2, 20 %, 512/64 5.3e-7 / 3.7e-7, 16384 x 8192, 10 %, 512/32 2.44e-7 / 2.24e-7.
+//   1.64e-7, 6 % 1.34e-7 / 1.28e-7; FusedMM 16384^2, 20 %, 512/64 5.3e-7 / 3.7e-7, 16384 x 8192, 10 %, 512/32 2.44e-7 / 2.24e-7.
 //
 // A workgroup is 8 wavefronts, 128 rows and CT * 16 columns: a pair of wavefronts shares 32 rows, each has half of the columns
 // (two rows' fragments for every read of C's pieces: 2 reads per 6 products; with 16 rows, 2 per 3, the reads bound the kernel).
@@ -49,9 +50,17 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ f32x4 mfma(f16x8 a, f16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
 
-// mean entries of a row in a range from which on the sums are put away three times on the way and not seven (FusedMM's six
-// products were the further off: 16384 x 8192, 10 %, 512/32 2.4e-7, this 2.2e-7 with three and 1.8e-7 with seven)
-constexpr int kWideLongRow = 2400, kWideLongFusedRow = 700;
+// Into how many parts a range of K falls, after each of which but the last one the sums are put away, by the mean entries of a
+// row in the range: as few as leave the error in the 2-norm below that of the six products, which grows faster with the entries.
+// Both are level at, ranges of 8192 / 16384 columns, operands U[-1,1]: SPMM 4 parts 1470 / 2130 entries, 8 parts 560 / 700, 12
+// parts 430; FusedMM 4 parts 530 / 655, 8 parts 250, 12 below 250.  (16384 x 8192, 512 columns, 6 %: six products 1.34e-7, 8 parts
+// 1.40e-7 in 470 us, 12 parts 1.28e-7 in 490, 16 1.24e-7 in 535.)
+__device__ __forceinline__ int wide_parts(bool fused, long long nnz, long long rows) {
+    return nnz >= (fused ? 700 : 2400) * rows ? 4 : nnz >= (fused ? 300 : 800) * rows ? 8 : 12;
+}
+// Rows of up to this many entries are computed again as sums of FP32: level at 32 entries (8e-8), with one the pieces' 23 bits are
+// three times as far off (7.3e-8 against 2.6e-8 in the 2-norm, 3.3e-7 against 5.9e-8 at most).
+constexpr int kWideShortRow = 32;
 
 // DS: 32-element steps of the dot products (0: SPMM)
 template <int CT, int DS>
@@ -337,6 +346,8 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
             if (t % kWave == 0) atomicAdd(&a.todo[2], pieces);
         }
         if (t < kDenseBM && row < M) {
+            const int entries = a.rowptr[row + 1] - a.rowptr[row];
+            if (entries > 0 && entries <= kWideShortRow) again = 0xffffu;
             a.redo[((size_t)job.seg * a.col_blocks + job.cb) * M + row] = (uint16_t)again;
             // (plain stores of the same word: see kernels_dense.hpp)
             if (again != 0) a.todo[0] = 1;
@@ -409,7 +420,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
     __syncthreads();
     int cbuf = 0, put_away = 0;
     // tiles until the sums are put away (neighbouring workgroups at different times: all at once, 872 instead of 834 us)
-    const int parts = (long long)uniform(a.rowptr[M]) >= (long long)(kFused ? kWideLongFusedRow : kWideLongRow) * a.segs * M ? 4 : 8;
+    const int parts = wide_parts(kFused, uniform(a.rowptr[M]), (long long)a.segs * M);
     const int part = ((job.ke - job.kb + kDenseK - 1) / kDenseK + parts - 1) / parts;
     int until = part - part * (job.row0 / kDenseBM % 8) / 8;
     for (int k0 = job.kb, t = 0;;) {
