@@ -49,15 +49,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 BF16_MATRIX_PEAK_TFLOPS = 2500.0  # MI355X, published, dense
-PRODUCTS = 6                      # bfloat16 products that the matrix-core kernels make of an FP32 one
-HALF_PRODUCTS = 3                 # half-precision products (the same rate) of an FP32 one by C, over long ranges of K
-
-
-def products_by_c(M, K, N):
-    """Matrix-core products for an FP32 product with C (csrc/dense.hip, kHalvesK): half-precision ones where blocks of more
-    than 128 columns of the output have at least 8192 columns of S to a workgroup on 256 CUs."""
-    workgroups = -(-M // 128) * -(-N // 256)
-    return HALF_PRODUCTS if N > 128 and K >= 8192 and K * workgroups >= 8192 * 256 else PRODUCTS
+PRODUCTS = 6                      # bfloat16 products that the matrix-core kernels make of an FP32 one (by C: the library says)
 FP32_VECTOR_PEAK_TFLOPS = 157.3   # MI355X, published: 256 CUs x 2.4 GHz x 256 flop/clk/CU
 HBM_PEAK_GBS = 8000.0             # MI355X, published
 # The rates this build's instruction mix can reach (plain multiply-adds, since packed FP32 is switched off; 128-bit LDS
@@ -227,7 +219,9 @@ def main():
         else:
             os.environ["CSRK_MFMA"] = mfma_switch
     widths = {name: sum(v_ for k_, v_ in w.ops[name].items() if k_ in ("N", "D")) for name, _ in ops}
-    matrix_products = {name: products_by_c(w.M, w.K, w.ops[name].get("N", 0)) for name, _ in ops}
+    op_codes = {"spmm": binding.CSRK_OP_SPMM, "sddmm": binding.CSRK_OP_SDDMM, "fusedmm": binding.CSRK_OP_FUSEDMM}
+    matrix_products = {name: binding.csrk_matrix_core_form(op_codes[name], w.M, w.K, w.ops[name].get("N", 0), w.ops[name].get("D", 0))[0]
+                       for name, _ in ops}
     matrix_flops = {name: 2.0 * w.M * w.K * (matrix_products[name] * w.ops[name].get("N", 0) + PRODUCTS * w.ops[name].get("D", 0))
                     for name, _ in ops}
     # one cold run per operation: a 1 GiB fill pushes the operands out of L2 and the 256 MB memory-side cache

@@ -174,6 +174,14 @@ csrk_status fusedmm_csr_bf16(int M, int K, int D, int N,
 #define CSRK_OP_SDDMM    2
 #define CSRK_OP_FUSEDMM  3
 csrk_status csrk_workspace_bytes(int op, int M, int K, int N, int D, size_t *bytes);
+
+/*
+ * Host-only, for measurements and tests: what the matrix-core kernels make of an FP32 call of this operation (CSRK_OP_*) and
+ * shape on the current device, where they are chosen.  *products receives the 16-bit products for one of FP32 by C (SDDMM: by
+ * B), 6 of bfloat16 pieces or 3 of half-precision ones, 0 for shapes that these kernels do not take; *ranges the ranges into
+ * which K is cut.
+ */
+csrk_status csrk_matrix_core_form(int op, int M, int K, int N, int D, int *products, int *ranges);
 csrk_status spmm_csr_ws(int M, int K, int N,
                         const int32_t *rowptr, const int32_t *colidx, const float *vals,
                         const float *B, float *O,

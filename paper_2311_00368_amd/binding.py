@@ -77,6 +77,7 @@ def load(build_if_missing: bool = True):
     lib.fusedmm_csr_plan.argtypes = [p, i, i, p, p, p, p, p, p]
     sz = ctypes.c_size_t
     lib.csrk_workspace_bytes.argtypes = [i, i, i, i, i, ctypes.POINTER(sz)]
+    lib.csrk_matrix_core_form.argtypes = [i, i, i, i, i, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]
     lib.spmm_csr_ws.argtypes = [i, i, i, p, p, p, p, p, p, sz, p]
     lib.sddmm_csr_ws.argtypes = [i, i, i, p, p, p, p, p, p, p, sz, p]
     lib.fusedmm_csr_ws.argtypes = [i, i, i, i, p, p, p, p, p, p, p, p, sz, p]
@@ -96,7 +97,7 @@ def load(build_if_missing: bool = True):
               lib.csrk_plan_info, lib.spmm_csr_plan, lib.sddmm_csr_plan, lib.fusedmm_csr_plan,
               lib.csrk_profile_enable, lib.csrk_profile_collect, lib.csrk_workspace_bytes, lib.spmm_csr_ws,
               lib.sddmm_csr_ws, lib.fusedmm_csr_ws, lib.csrk_plan_reserve, lib.csrk_tile_phases,
-              lib.csrk_debug_row_rotation, lib.fusedmm_csr_static, lib.csrk_microbench, lib.csrk_call):
+              lib.csrk_debug_row_rotation, lib.fusedmm_csr_static, lib.csrk_microbench, lib.csrk_call, lib.csrk_matrix_core_form):
         f.restype = ctypes.c_int
     lib.csrk_last_error.restype = ctypes.c_char_p
     lib.csrk_version.restype = ctypes.c_char_p
@@ -240,6 +241,14 @@ def csrk_workspace_bytes(op: int, M: int, K: int, N: int, D: int = 0) -> int:
     out = ctypes.c_size_t(0)
     _check(load().csrk_workspace_bytes(op, M, K, N, D, ctypes.byref(out)))
     return int(out.value)
+
+
+def csrk_matrix_core_form(op: int, M: int, K: int, N: int, D: int = 0) -> tuple[int, int]:
+    """What the matrix-core kernels make of an FP32 call of this operation (CSRK_OP_*) and shape on the current device, where they
+    are chosen: 16-bit products for one of FP32 by C (SDDMM: by B; 0 if they do not take the shape), ranges of K."""
+    products, ranges = ctypes.c_int(0), ctypes.c_int(0)
+    _check(load().csrk_matrix_core_form(op, M, K, N, D, ctypes.byref(products), ctypes.byref(ranges)))
+    return products.value, ranges.value
 
 
 def _ws_ptr(workspace: torch.Tensor, dev):

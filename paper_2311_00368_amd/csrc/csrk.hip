@@ -1901,6 +1901,21 @@ csrk_status csrk_workspace_bytes(int op, int M, int K, int N, int D, size_t *byt
     return CSRK_OK;
 }
 
+csrk_status csrk_matrix_core_form(int op, int M, int K, int N, int D, int *products, int *ranges) {
+    if (!products || !ranges) return fail(CSRK_INVALID_ARG, "csrk_matrix_core_form: products and ranges must not be NULL");
+    if (op != CSRK_OP_SPMM && op != CSRK_OP_SDDMM && op != CSRK_OP_FUSEDMM)
+        return fail(CSRK_INVALID_ARG, "csrk_matrix_core_form: unknown operation %d", op);
+    if (csrk_status s = check_dims("csrk_matrix_core_form", M, K, N, D)) return s;
+    const DeviceInfo *info = nullptr;
+    if (csrk_status s = device_info(&info)) return s;
+    const DenseOp kind = op == CSRK_OP_SPMM ? kDenseSpmm : op == CSRK_OP_SDDMM ? kDenseSddmm : kDenseFused;
+    DenseConfig c;
+    const bool taken = dense_config(DenseShape{kind, false, M, K, kind == kDenseSddmm ? 0 : N, kind == kDenseSpmm ? 0 : D}, info->cus, &c);
+    *products = !taken ? 0 : c.halves ? 3 : 6;
+    *ranges = taken ? c.segs : 0;
+    return CSRK_OK;
+}
+
 csrk_status spmm_csr_ws(int M, int K, int N, const int32_t *rowptr, const int32_t *colidx, const float *vals,
                         const float *B, float *O, void *workspace, size_t workspace_bytes, hipStream_t stream) {
     if (!workspace) return fail(CSRK_INVALID_ARG, "spmm_csr_ws: workspace must not be NULL");

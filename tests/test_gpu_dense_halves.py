@@ -12,6 +12,14 @@ pytestmark = pytest.mark.gpu
 # Relative to the sum of the terms' magnitudes: two pieces leave 2^-23 of each operand and 2^-22 of their product, 4.8e-7 in all;
 # the rows checked have up to 9000 terms, whose sums of random rounding errors stay below 1e-6 of it.
 TOL = 2e-6
+OPS = {"spmm": 1, "fusedmm": 3}
+
+
+def assert_halves(csrk, op, M, K, N, D=0):
+    """That the shape is one for half-precision pieces; its ranges of K."""
+    products, ranges = csrk.csrk_matrix_core_form(OPS[op], M, K, N, D)
+    assert products == 3
+    return ranges
 
 
 def matrix(rng, M, K):
@@ -30,10 +38,12 @@ def matrix(rng, M, K):
     return rp, np.concatenate(rows).astype(np.int32)
 
 
-@pytest.mark.parametrize("M,K,N", [(16300, 8200, 500), (16384, 8192, 512), (16320, 9000, 300), (32650, 8224, 180)])
+@pytest.mark.parametrize("M,K,N", [(16300, 8200, 500), (16384, 8192, 512), (16320, 9000, 300), (32650, 8224, 180),
+                                   (8192, 16384, 512), (16300, 16390, 250)])       # two ranges of K
 @pytest.mark.parametrize("kind", ["plain", "ones", "unsorted", "not finite", "small", "large", "mixed", "zeros"])
 def test_long_ranges(csrk, monkeypatch, M, K, N, kind):
     monkeypatch.setenv("CSRK_MFMA", "2")
+    assert assert_halves(csrk, "spmm", M, K, N) == K // 8192
     rng = np.random.default_rng(M + K + N)
     rp, ci = matrix(rng, M, K)
     v = rng.uniform(-1, 1, len(ci)).astype(np.float32)
@@ -83,10 +93,12 @@ def test_long_ranges(csrk, monkeypatch, M, K, N, kind):
         assert (np.abs(want[:, N // 2 + 1]) > 0).any()
 
 
-@pytest.mark.parametrize("M,K,D,N", [(16300, 8200, 64, 500), (16384, 8192, 32, 512), (16320, 9000, 1, 300), (32650, 8224, 33, 180)])
+@pytest.mark.parametrize("M,K,D,N", [(16300, 8200, 64, 500), (16384, 8192, 32, 512), (16320, 9000, 1, 300), (32650, 8224, 33, 180),
+                                     (8192, 16384, 64, 512), (16300, 16390, 20, 250)])
 @pytest.mark.parametrize("kind", ["plain", "ones", "unsorted", "not finite", "small", "large", "mixed", "zeros"])
 def test_long_ranges_fused(csrk, monkeypatch, M, K, D, N, kind):
     monkeypatch.setenv("CSRK_MFMA", "2")
+    assert assert_halves(csrk, "fusedmm", M, K, N, D) == K // 8192
     rng = np.random.default_rng(M + K + N + D)
     rp, ci = matrix(rng, M, K)
     v = rng.uniform(-1, 1, len(ci)).astype(np.float32)
@@ -141,12 +153,87 @@ def bernoulli(gen, M, K, p):
     return at, rp, at[:, 1].to(torch.int32).contiguous()
 
 
+@pytest.mark.parametrize("op,M,K,D,N", [("spmm", 4096, 32768, 0, 512), ("fusedmm", 4096, 32768, 40, 500)])
+def test_rows_in_one_range(csrk, monkeypatch, op, M, K, D, N):
+    # rows with entries in one, two or all of four ranges of K, small ones in the others; results of zero in some
+    monkeypatch.setenv("CSRK_MFMA", "2")
+    assert assert_halves(csrk, op, M, K, N, D) == 4
+    rng = np.random.default_rng(9)
+    kinds = np.arange(M) % 8
+    v, rows = [], []
+    for r in range(M):
+        ranges = [[0], [3], [1, 2], [0, 1, 2, 3], [0, 3], [2], [], [1]][kinds[r]]
+        c = np.unique(np.concatenate([rng.integers(8192, size=200) + 8192 * q for q in ranges] or [np.zeros(0, int)]))
+        x = rng.uniform(-1, 1, len(c))
+        if kinds[r] == 4: x[c >= 8192] *= 1e-12     # the last range's values are small, and these are all that some columns add up
+        if kinds[r] == 5: x[:] = 0
+        rows.append(c)
+        v.append(x)
+    rp = np.concatenate([[0], np.cumsum([len(c) for c in rows])]).astype(np.int32)
+    ci, v = np.concatenate(rows).astype(np.int32), np.concatenate(v).astype(np.float32)
+    A, B, C = (rng.normal(size=n).astype(np.float32) for n in ((M, D), (K, D), (K, N)))
+    C[:8192, ::7] = 0
+    some = np.unique(np.concatenate([np.arange(0, M, 11), [M - 1]]))
+    if op == "spmm":
+        O = csrk.spmm_csr(M, K, N, dev(rp), dev(ci), dev(v), dev(C)).cpu().numpy()
+        want, terms = oracle.spmm(M, K, N, rp, ci, v, C, rows=some)
+    else:
+        O = csrk.fusedmm_csr(M, K, D, N, dev(rp), dev(ci), dev(v), dev(A), dev(B), dev(C)).cpu().numpy()
+        want, terms = oracle.fusedmm(M, K, D, N, rp, ci, v, A, B, C, rows=some)
+    bad = np.abs(O[some] - want) > TOL * terms
+    assert not bad.any(), (bad.mean(), np.unique(kinds[some[bad.any(1)]]))
+
+
+@pytest.mark.parametrize("op", ["spmm", "fusedmm"])
+@pytest.mark.parametrize("M,K", [(16384, 8192), (8192, 16384)])
+def test_every_entry_point_and_replays(csrk, monkeypatch, op, M, K):
+    # planned, on a workspace and captured: the same bits as the plain call, on every replay, also after operands were exchanged
+    # for ones with rows to be done again, and for ones that bfloat16 pieces do again
+    monkeypatch.setenv("CSRK_MFMA", "2")
+    D, N = 32, 512
+    ranges = assert_halves(csrk, op, M, K, N, D if op == "fusedmm" else 0)
+    assert ranges == K // 8192
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    at, rp, ci = bernoulli(gen, M, K, 0.06)
+    v, C = torch.rand(len(ci), device="cuda", generator=gen), torch.randn((K, N), device="cuda", generator=gen)
+    A, B = torch.randn((M, D), device="cuda", generator=gen), torch.randn((K, D), device="cuda", generator=gen)
+    plan = csrk.csrk_plan_create(M, K, rp, ci)
+    ws = torch.empty(csrk.csrk_workspace_bytes(OPS[op], M, K, N, D), dtype=torch.uint8, device="cuda")
+    if op == "spmm":
+        plain = lambda: csrk.spmm_csr(M, K, N, rp, ci, v, C)
+        others = [lambda: csrk.spmm_csr_plan(plan, N, v, C), lambda: csrk.spmm_csr_ws(M, K, N, rp, ci, v, C, ws)]
+    else:
+        plain = lambda: csrk.fusedmm_csr(M, K, D, N, rp, ci, v, A, B, C)
+        others = [lambda: csrk.fusedmm_csr_plan(plan, D, N, v, A, B, C), lambda: csrk.fusedmm_csr_ws(M, K, D, N, rp, ci, v, A, B, C, ws)]
+    ordinary = plain()
+    for f in others:
+        assert torch.equal(f(), ordinary)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        out = others[1]()
+    kept = C.clone()
+    for change in (None, "few", "all", None, "all", "few", None):
+        C.copy_(kept)
+        if change == "few":             # a value that is not finite
+            C[5, 7] = float("inf")
+        elif change == "all":           # a value in every column that leaves the others out of its pieces' range
+            C[torch.arange(N), torch.arange(N)] = 1e12
+        want = plain()
+        out.fill_(7)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(torch.nan_to_num(out), torch.nan_to_num(want)), change
+        assert change is not None or torch.equal(want, ordinary)
+
+
 @pytest.mark.parametrize("op", ["spmm", "fusedmm"])
 def test_short_rows(csrk, monkeypatch, op):
     # Rows of up to 32 entries among longer ones: no further from FP64 than the vector kernels by more than the order of a sum's
     # terms makes out, at most for two terms: two products and their sum are rounded, or one product and the sum with the other,
     # sqrt(3 / 2) = 1.22 in the 2-norm.
     M, K, D, N = 16384, 8192, 32, 512
+    assert assert_halves(csrk, op, M, K, N, D if op == "fusedmm" else 0) == 1
     gen = torch.Generator(device="cuda").manual_seed(2)
     lens = torch.tensor([1, 2, 3, 5, 8, 16, 31, 32, 100, 33])
     counts = lens.repeat(M // len(lens) + 1)[:M]
@@ -199,6 +286,7 @@ def test_error_is_the_vector_kernels(csrk, monkeypatch, M, K, N, p, sign):
 @pytest.mark.parametrize("M,K,D,N,p", [(16384, 8192, 64, 512, 0.06), (16384, 8192, 32, 512, 0.1), (8192, 16384, 64, 512, 0.06), (16384, 9000, 16, 384, 0.3)])
 def test_error_is_the_vector_kernels_fused(csrk, monkeypatch, M, K, D, N, p):
     # the same for FusedMM (measured: 0.3-0.45 times)
+    assert_halves(csrk, "fusedmm", M, K, N, D)
     gen = torch.Generator(device="cuda").manual_seed(K)
     at, rp, ci = bernoulli(gen, M, K, p)
     v, C = torch.rand(len(ci), device="cuda", generator=gen) - 0.5, torch.randn((K, N), device="cuda", generator=gen)
