@@ -11,7 +11,9 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [("spmm", "f32", 3000, 3000, 0, 96, 0.3), ("spmm", "f32", 3000, 3000, 0, 256, 0.2), ("spmm", "f32", 2048, 2048, 0, 512, 0.25),
           ("sddmm", "f32", 2048, 2048, 128, 0, 0.3), ("sddmm", "f32", 2999, 3001, 96, 0, 0.12), ("sddmm", "bf16", 2048, 2048, 128, 0, 0.3),
-          ("fusedmm", "f32", 2048, 2048, 64, 256, 0.15), ("fusedmm", "f32", 2048, 2048, 128, 256, 0.15)]
+          ("fusedmm", "f32", 2048, 2048, 64, 256, 0.15), ("fusedmm", "f32", 2048, 2048, 128, 256, 0.15),
+          # outside of the sizes that the ratio was fitted to
+          ("spmm", "f32", 3200, 896, 0, 632, 0.294), ("sddmm", "f32", 11264, 384, 120, 0, 0.587), ("fusedmm", "f32", 1595, 706, 16, 656, 0.682)]
 
 
 def call_of(csrk, op, dtype, M, K, D, N, density):
