@@ -38,7 +38,7 @@ int prepare_blocks(size_t units) {
 
 // where everything lies in the scratch area
 struct Layout {
-    size_t c, b, a, todo, c_most, c_exps, a_exps, b_exps, met, special, redo, cuts, partial, bytes;
+    size_t c, b, a, todo, met, special, redo, cuts, partial, bytes;
     int n_tiles, c_blocks, b_blocks, a_blocks;
     Layout(const DenseShape &s, const DenseConfig &cfg) {
         const bool halves = cfg.halves;
@@ -60,11 +60,7 @@ struct Layout {
         // (whole tiles of SDDMM's columns)
         b = take((k + kSddmmMaxKt - 32) * d * pieces);
         a = take(up32(s.M) * d * pieces);
-        todo = take(16);
-        c_most = take(halves ? (size_t)kRangeParts * n_tiles * 64 : 0);
-        c_exps = take(halves ? (size_t)n_tiles * 128 : 0);
-        a_exps = take(halves && cfg.ds ? (size_t)s.M * 4 : 0);
-        b_exps = take(halves && cfg.ds ? (size_t)s.K * 4 : 0);
+        todo = take(halves ? DenseScales::bytes(n_tiles, s.K, s.M) : 8);
         met = take(s.op == kDenseFused ? (size_t)b_blocks * 4 : 0);
         special = take(s.op == kDenseFused ? k : 0);
         redo = take(s.op != kDenseSddmm ? (size_t)cfg.segs * (n_tiles / cfg.ct) * s.M * 2 : 0);
@@ -210,16 +206,6 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
     }
     if (s.op != kDenseSddmm) a.todo = reinterpret_cast<int32_t *>(base + l.todo);
     a.redo = reinterpret_cast<uint16_t *>(base + l.redo);
-    if (c.halves) {
-        a.c_most = reinterpret_cast<int32_t *>(base + l.c_most);
-        a.c_exps = reinterpret_cast<int32_t *>(base + l.c_exps);
-        a.a_exps = reinterpret_cast<int32_t *>(base + l.a_exps);
-        a.b_exps = reinterpret_cast<int32_t *>(base + l.b_exps);
-        // 16384^2, 20 %, 512 columns: the finishing kernel takes 0.45 ms for one piece of every row, bfloat16 pieces 1.2 for the
-        // call: as much as for a twelfth of the output.  FusedMM with 64 (the scores anew for every piece): 1.4 and 1.5, a thirtieth.
-        const size_t pieces = (size_t)a.M * l.n_tiles * c.segs / (s.op == kDenseFused ? 30 : 12);
-        a.again_limit = pieces < 0xffffffffu ? (unsigned)pieces : 0xffffffffu;
-    }
     a.cuts = reinterpret_cast<int32_t *>(base + l.cuts);
 
     const DenseKernel k = c.halves              ? wide_kernel(c.ct, c.ds)

@@ -101,6 +101,7 @@ constexpr int kNoTiny = -(1 << 28);     // of a row or column whose results are 
 // latency of memory: 9 us for the 33 MB of 16384 x 512 (12 with half as many parts).
 __global__ __launch_bounds__(256) void dense_range_kernel(DenseArgs a) {
     constexpr int kChunk = 256;
+    const DenseScales scales(a);
     __shared__ int most[4][64], row_exps[kChunk];
     const int lane = lane_id(), wave = uniform(threadIdx.x >> 6);
     const int groups = a.n_tiles / 4, group = blockIdx.x % groups, part = blockIdx.x / groups, col = group * 64 + lane;
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(256) void dense_range_kernel(DenseArgs a) {
                     if (lane == 0) row_exps[r + i] = x[i] == 0 ? kZeros : exponent_to(x[i], kDotExp);
             }
             __syncthreads();
-            if (group == 0 && k0 + (int)threadIdx.x < stop) a.b_exps[k0 + threadIdx.x] = row_exps[threadIdx.x];
+            if (group == 0 && k0 + (int)threadIdx.x < stop) scales.b_exps[k0 + threadIdx.x] = row_exps[threadIdx.x];
         }
         constexpr int kRows = 16;       // under way at a time
         for (int k = k0 + wave; k < stop; k += 4 * kRows) {
@@ -158,8 +159,8 @@ __global__ __launch_bounds__(256) void dense_range_kernel(DenseArgs a) {
     __syncthreads();
     if (wave == 0) {
         m = max(max(most[0][lane], most[1][lane]), max(most[2][lane], most[3][lane]));
-        a.c_most[(size_t)part * a.n_tiles * 16 + col] = col < a.N ? m : -kZeros;
-        if (part == 0) a.c_exps[2 * col + 1] = 0;
+        scales.c_most[(size_t)part * a.n_tiles * 16 + col] = col < a.N ? m : -kZeros;
+        if (part == 0) scales.c_exps[2 * col + 1] = 0;
     }
 }
 
@@ -173,6 +174,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
     const int lane = lane_id();
     const int wave = uniform(threadIdx.x >> 6);
     const DenseJob job = dense_job(a);
+    const DenseScales scales(a);
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)dlds;
 
     // part i of C's tile to LDS (tiles past the last one read as zeros: the uniform part of the address stops at the view's end)
@@ -204,7 +206,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
     // the columns' exponents and such values
     int2 *const columns = reinterpret_cast<int2 *>(dlds + L::kOffCols);
     if (threadIdx.x < L::BN) {
-        const int2 c = reinterpret_cast<const int2 *>(a.c_exps)[job.cb * L::BN + threadIdx.x];
+        const int2 c = reinterpret_cast<const int2 *>(scales.c_exps)[job.cb * L::BN + threadIdx.x];
         columns[threadIdx.x] = c.x != kZeros ? c : make_int2(0, c.y >= kNotFinite ? c.y : kNoTiny);
     }
     bf16x8 af[kFused ? DS : 1][3];
@@ -249,7 +251,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_wide_kernel(DenseArgs 
         // normal float would become a zero: all of the row's.)
         if ((lane & 3) == 0) {
             row_tiny[r] = len == 0 ? kNoTiny : kFused && value_exponent < -23 ? len : 0;
-            if constexpr (kFused) value_exponent += a.a_exps[job.row0 + r < M ? job.row0 + r : M - 1];
+            if constexpr (kFused) value_exponent += scales.a_exps[job.row0 + r < M ? job.row0 + r : M - 1];
             row_exps[r] = value_exponent;
         }
     }
