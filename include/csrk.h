@@ -37,7 +37,9 @@
  *    matrix-core kernels are chosen (S dense enough and its number of entries known:
  *    planned calls, csrk_call), the dense operands in pieces: 6 bytes per element of A,
  *    B and C (2 for bfloat16), lengths rounded up to 32, partial outputs likewise, and
- *    2 bytes for each row, range and block of up to 256 columns.  Three ways to provide it:
+ *    2 bytes for each row, range and block of up to 256 columns; for FP32 outputs of more
+ *    than 128 columns over long rows also 640 bytes per column of the output and 4 per row
+ *    and column of S.  Three ways to provide it:
  *      * spmm_csr / sddmm_csr / fusedmm_csr (and their planned and bfloat16 forms) use
  *        an area the library keeps per device.  It is allocated (hipMalloc, which
  *        synchronises) the first time it is needed, replaced when it has to grow (after

@@ -15,11 +15,10 @@ constexpr int kMaxRows = 1 << 26;
 constexpr long long kMaxGroups = 1 << 22;
 
 // Ranges of K from this length on are done in half-precision pieces where blocks of 192 or 256 columns of FP32 are the best
-// choice (narrower blocks add up their sums on the way and are the more exact).  Shorter ranges would not be: the error in the
-// 2-norm against FP64, six products of bfloat16 / three of halves, is 4.2e-7 / 3.6e-7 at 16384^2, 20 %, 512 columns, 1.8e-7 /
-// 1.6e-7 at 16384 x 8192, 10 %, but 1.36e-7 / 1.41e-7 at 8192^2, log-normal rows, 256 columns, in ranges of 2048, and putting
-// the sums away (8 times 4 us or so) would weigh more.  FusedMM: 5.3e-7 / 3.7e-7 at 16384^2, 20 %, 512/64, 2.5e-7 / 1.8e-7 at
-// 16384 x 8192, 10 %, 512/32.  A tile takes 1.4-1.5 us, FusedMM's 2.1.
+// choice (narrower blocks add up their sums on the way and are the more exact).  Shorter ranges would have to put their sums away
+// after fewer tiles for an error no larger than that of the six products of bfloat16 (at 8192^2, log-normal rows, 256 columns, in
+// ranges of 2048, 1.36e-7 against 1.41e-7 in the 2-norm with 8 parts, which take 4 us each; kernels_dense_wide.hpp has the figures
+// of longer ranges).  A tile takes 1.4-1.5 us, FusedMM's 2.1.
 constexpr int kHalvesK = 8192;
 constexpr double kHalvesTileUs = 1.5, kHalvesFusedTileUs = 2.1;
 

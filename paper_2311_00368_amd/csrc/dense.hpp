@@ -43,9 +43,7 @@ DenseKernel dense_fused_kernel_f32(int ct, int ds);
 DenseKernel dense_fused_kernel_bf16(int ct, int ds);
 // the same kernel for calls whose results after half-precision pieces would mostly be computed again
 DenseKernel dense_again_fused_f32(int ct, int ds);
-// Wavefronts of a workgroup of the finishing kernel.  After half-precision pieces, in calls with little else to wait for, the
-// rows of thousands of entries that are done again take their time one after the other, and 16 wavefronts share one (one pair of
-// entries exchanged, 16384^2, 20 %, 512 columns: 0.84 ms, with 4 0.95); FusedMM has registers for 8.
+// Wavefronts of a workgroup of the finishing kernel (kernels_dense_finish.hpp says what each is worth)
 constexpr int finish_waves(bool halves, bool fused) { return halves ? (fused ? 8 : 16) : 4; }
 // `vec`: 128-bit accesses of all dense operands and the output
 DenseKernel dense_finish_kernel(bool bf16, bool fused, bool vec, int ct, bool halves);

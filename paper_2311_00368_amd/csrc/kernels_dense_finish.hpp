@@ -7,13 +7,13 @@
 // counter, 8 at a time, cost 30 us of atomics on one address where one row was to be done.)
 //
 // Measured on MI355X, against the vector kernels for the same input: 16384^2, 20 %, 512 columns: one pair of entries
-// exchanged 0.86 ms (vector: 10.7, their tiled attempt fails), every row reversed 11.2 (19.9), one NaN in C 1.28 (1.54);
+// exchanged 0.82 ms (vector: 10.7, their tiled attempt fails), every row reversed 10.8 (19.2), one NaN in C 1.26 (1.49);
 // 4096^2, 30 %, 128 columns: 72 (172), 173 (300) and 112 us (68).  (With every workgroup doing its own rows again, 65 ms in each
 // of the three and 0.45-7 ms at smaller sizes.)  What it is slow at: rows that are uneven and unordered at once, whose longest
 // ones a workgroup does at its end (FusedMM 8192^2, log-normal rows, 64 columns: 0.45 ms, equal shares 0.17).
-// After half-precision pieces (16384^2, 20 %, 512 columns) every call has some results to do again, a row or two of 3277
-// entries in a workgroup, and their loads one after the other are the kernel's time: with 4 wavefronts 27 us, FusedMM 56, with
-// 16 20 and 42 (whole calls against the six products: 1.64 -> 1.65 times as fast, FusedMM 1.37 -> 1.39; with 8: 1.64, 1.39).
+// After half-precision pieces little else is waited for, and where a row or two of 3277 entries fall to a workgroup their loads one
+// after the other are the kernel's time: one pair exchanged at 16384^2, 20 %, 512 columns 0.95 ms with 4 wavefronts, 0.82 with 16;
+// FusedMM with 64 1.38 and, with 8 (16 have 128 registers each and spill), 1.25.
 // Without anything left to do: the time of a kernel that only adds the ranges (16384 x 4096, 128 columns, 2 ranges: 5.8 us),
 // 4.7 us where there are none.
 #pragma once

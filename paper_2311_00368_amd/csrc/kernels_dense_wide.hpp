@@ -14,12 +14,12 @@
 //   2^-12 are counted for every column of C and row of S (of FusedMM's products).  With n and t of them the error of a result is
 //   at most (n + t) (2^-36 + 2^-37) 2^16, so a result of 4 (n + t) and more is off by no more than 2^-21 of its terms'
 //   magnitudes; smaller ones, and those that are not finite, are computed again by the finishing kernel, entry by entry.  Of
-//   uniform or normal values hardly one call in ten has such a result.
-// - If more than a twelfth of the output (FusedMM: a thirtieth) would be computed again, the call is done again with six products of bfloat16 pieces
-//   (dense_kernel, AGAIN), which have the range of floats: two launches that look at one word otherwise, 4.5 us each.  At
-//   16384^2, 20 %, 512 columns, FusedMM with dot products of 64: all values of C, S and B from a Cauchy distribution 2.1 and 2.6 ms
-//   (computed again entry by entry: 11.4 and 15.3); one value of C 10^9 times the others 1.24 and 2.5; S log-normal with sigma 3
-//   2.0 and 3.3.
+//   uniform or normal values that is less than one result of a call, by an estimate from these sizes.
+// - If more than a twelfth of the output (FusedMM: a thirtieth) would be computed again, the call is done again with six products
+//   of bfloat16 pieces (dense_kernel, AGAIN), which have the range of floats: two launches that look at one word otherwise, 4 us
+//   each.  At 16384^2, 20 %, 512 columns, FusedMM with dot products of 64, instead of 0.73 and 1.11 ms: all values of C, S and B from a
+//   Cauchy distribution 2.0 and 2.6 (entry by entry: 11.3 and 15.5); one value of C 10^9 times the others 1.2 and 2.5 (10^4 times:
+//   no more than without); S log-normal with sigma 3 1.4 and 1.8.
 // - Rows of few entries: 23 bits instead of 24 show, and they are computed again (kWideShortRow).
 // - Rounding of sums.  Products of bfloat16 pieces have 16 bits and mostly add up exactly inside an instruction; these have 22,
 //   and long sums are 1.75 times as far from FP64.  So the sums are put away in memory on the way (wide_parts).  Error in the
@@ -34,8 +34,9 @@
 // FusedMM's scores stay six products of bfloat16 pieces, each wavefront those of its own 16 rows; times S's values they are
 // split in half-precision pieces and passed to the pair through LDS as fragments.
 //
-// Measured on MI355X, six products of bfloat16 pieces / this: SPMM 16384^2, 20 %, N = 512 1196 / 720 us, 16384 x 8192, 10 %, 512
-// 662 / 436, 32768 x 8192, 20 %, 192 590 / 390; FusedMM 16384^2, 20 %, 512/64 1540 / 1111, 16384 x 8192, 10 %, 512/32 767 / 540.
+// Measured on MI355X, six products of bfloat16 pieces / this: SPMM 16384^2, 20 %, N = 512 1195 / 733 us, 16384 x 8192, 10 %, 512
+// 580 / 385, 32768 x 8192, 20 %, 192 503 / 400; FusedMM 16384^2, 20 %, 512/64 1538 / 1110, 16384 x 8192, 10 %, 512/32 674 / 455.
+// Of SPMM's 733 the range kernel, the preparation, the two launches that end at once and the finishing kernel are 9 + 13 + 8 + 4.
 // Bound by latency: of the 3000 cycles of a tile the matrix cores are busy for
 // half; the wavefronts that come second on their SIMD take 770 + 1065 cycles for the products, 670 for S, 200 to ask for
 // loads, 215 for the fragments (the first ones wait for them at the barrier).  What gave nothing: S between the matrix
@@ -54,7 +55,8 @@ __device__ __forceinline__ f32x4 mfma(f16x8 a, f16x8 b, f32x4 c) { return __buil
 // row in the range: as few as leave the error in the 2-norm below that of the six products, which grows faster with the entries.
 // Both are level at, ranges of 8192 / 16384 columns, operands U[-1,1]: SPMM 4 parts 1470 / 2130 entries, 8 parts 560 / 700, 12
 // parts 430; FusedMM 4 parts 530 / 655, 8 parts 250, 12 below 250.  (16384 x 8192, 512 columns, 6 %: six products 1.34e-7, 8 parts
-// 1.40e-7 in 470 us, 12 parts 1.28e-7 in 490, 16 1.24e-7 in 535.)
+// 1.40e-7 in 470 us, 12 parts 1.28e-7 in 490, 16 1.24e-7 in 535.)  Seven of eight row blocks have one part more, a shorter one in
+// front, so that not all put their sums away at the same time.
 __device__ __forceinline__ int wide_parts(bool fused, long long nnz, long long rows) {
     return nnz >= (fused ? 700 : 2400) * rows ? 4 : nnz >= (fused ? 300 : 800) * rows ? 8 : 12;
 }

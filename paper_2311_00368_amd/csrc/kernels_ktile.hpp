@@ -589,8 +589,11 @@ __global__ __launch_bounds__(WAVES *kWave, WAVES == 16 ? 4 : 2) void ktile_kerne
 // Sixty-four lanes that each read 16 bytes of a different, arbitrary row would collide in the
 // LDS banks (rows start at the same bank), so every lane walks its row in a ROTATED order:
 // at step s lane i (numbered inside its group of 16 lanes) reads the 16-byte piece number
-// (i - s) mod 16 of its row.  The 16 lanes the LDS serves together then touch 16 different
-// pieces, i.e. all banks once, whatever rows they are in; no padding is needed.  The row of
+// (i - s) mod S of its row, S = 8 in rows of up to 32 floats and 16 in longer ones.  With 16
+// the lanes the LDS serves together touch 16 different pieces, i.e. all banks once, whatever
+// rows they are in; no padding is needed.  With 8 lanes i and i + 8 read the same piece and
+// meet in a bank unless their rows lie apart by an odd number (32768 x 8192, 10 %, 32: the
+// banks conflict for 40 % of the LDS's active cycles, 18 % of the kernel's).  The row of
 // A that multiplies these pieces is spread over the same 16 lanes, piece i in lane i, and
 // the rotation `row_ror:s` of the DPP operand of the multiply-add hands lane i piece (i - s)
 // at no extra instruction.  Nothing is carried from tile to tile except the per-row cursor
