@@ -94,6 +94,26 @@ def test_sums_of_small_values(csrk, monkeypatch, op, ones, kind):
 
 
 @pytest.mark.parametrize("op", ["spmm", "fusedmm"])
+def test_small_values_behind_a_large_one(csrk, monkeypatch, op):
+    # a value of 1 at the beginning of the checked rows and 2^-27 behind it: the other rows have results that only bfloat16 pieces
+    # hold, and these do the whole call; the small values must not be lost one after the other in an accumulator that holds the large one
+    monkeypatch.setenv("CSRK_MFMA", "2")
+    _, rp, ci, v = operands(5, ones=True)
+    N = 512
+    C = torch.full((K, N), 2.0 ** -27, device="cuda")
+    C[5] = 1        # (a column of S in which only rows of 3277 and of all entries have one)
+    S = rows_of(rp, ci, v)
+    if op == "spmm":
+        got = csrk.spmm_csr(M, K, N, rp, ci, v, C)
+    else:
+        A, B = torch.full((M, D), 0.5, device="cuda"), torch.full((K, D), 0.5, device="cuda")
+        S *= D / 4
+        got = csrk.fusedmm_csr(M, K, D, N, rp, ci, v, A, B, C)
+    want = S @ C.double()
+    check(got, want, want, op, TOL)
+
+
+@pytest.mark.parametrize("op", ["spmm", "fusedmm"])
 @pytest.mark.parametrize("kind", ["row", "column", "row of B"])
 def test_values_that_scales_lose(csrk, monkeypatch, op, kind):
     # a value so far above the rest of its row or column that the others underflow where they are scaled, in results without it
