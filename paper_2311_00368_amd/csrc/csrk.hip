@@ -1366,6 +1366,8 @@ double vector_us(const DenseShape &s, long long nnz, bool wide) {
                          : s.op == kDenseSpmm              ? (s.bf16 ? bf16_spmm : f32_spmm)[w]
                          : s.op == kDenseFused             ? (s.bf16 ? bf16_fused : f32_fused)[w]
                          : s.bf16                          ? (s.D <= 64 ? VectorCost{4.8, 12.3, 7.35, 0.03} : VectorCost{4.6, 10.6, 12.5, 0.14})
+                         : s.D <= 32                       ? VectorCost{4.8, 0, 5.4, 0.16}
+                         : s.D <= 64                       ? VectorCost{5.3, 0, 6.9, 0.46}
                                                            : VectorCost{5.4, 0, 14.3, 0.71};
     return c.call + c.work * 1e-9 * (double)nnz * (s.N + s.D) + c.entries * 1e-6 * (double)nnz + c.cells * 1e-6 * (double)s.M * s.K;
 }
@@ -1374,18 +1376,11 @@ double vector_us(const DenseShape &s, long long nnz, bool wide) {
 // 4000 other random calls of the ranges above, uneven rows among them, that made the average call 1.34 times as fast
 // (always the better of the two: 1.46), and 22 calls slower by more than 3 % (at worst 0.77 times as fast).  Over 4000 calls
 // of M 16-200000, K 32-65536, up to 2048 columns and 0.4-95 % it was 1.14 times (1.37), 4 slower (at worst 0.64).
-// FP32 SDDMM with dot products of up to 64 elements and aligned rows stays with the vector kernels: it is bound by S and P,
-// which the tiled kernel streams, and the matrix-core kernel was 0.4-1.1 times as fast there (32768 x 8192, 10 %, 32: 292
-// against 149 us).  With bfloat16 operands, which the vector kernel has to widen, it is the better one where the chip is
-// full: its time for a round of workgroups and for each of their tiles, by density, is fitted to 150 random calls
-// (scatter 14-18 %; uneven rows among them).  Taking it where it is expected to win by a fifth made them 1.10 times as fast on
-// average (always the better of the two: 1.14), 2 of them slower by more than 3 %, at worst 0.89 times; a tenth would take
-// more calls with a few percent to win and some of very uneven rows with as much as a third to lose.
-double short_bf16_sddmm_us(const DenseShape &s, const DenseConfig &c, int cus, double nnz, double density) {
-    const int rounds = ((s.M + 127) / 128 * c.segs + cus - 1) / cus;
-    const double tile = c.ds == 1 ? 0.36 + 1.32 * density : 0.535 + 0.94 * density;
-    return -3.5 + rounds * (11.0 + c.seg_k / 32 * tile) + (c.ds == 1 ? 0.9 : 1.4) * 1e-6 * nnz;
-}
+// SDDMM in slabs of scores (all of bfloat16, FP32 of up to 64 elements) has an estimate of its own and is taken where that is a tenth
+// below the vector kernels'.  Of 1200 other random calls of these ranges, uneven rows among them, that makes the average one of up to 32 /
+// 64 FP32 elements 1.11 / 1.14 times as fast as the vector kernels (always the better of the two: 1.17 / 1.23) and that of bfloat16 1.19
+// times as fast as the choice before (1.26).  Of 1800 FP32 calls with even rows 5 are slower by more than 3 %, at worst 0.89 times as fast;
+// of those with log-normal rows, which the host cannot tell, a twentieth, at worst 0.78 times as fast.
 
 // The two estimates above err in ways that depend on the class of the call: the kernels of both sides have changed since
 // they were fitted, and a call of 30 us is not a call of 300 us made ten times.  So for the classes where that loses most
@@ -1398,8 +1393,8 @@ double short_bf16_sddmm_us(const DenseShape &s, const DenseConfig &c, int cus, d
 //     operands in turn           342                  308               19      0.84                      1.43
 //     cold caches                314                  289               13      0.80                      1.40
 // On average over a class: FP32 SDDMM of more than 64 elements 9 %, FusedMM of more than 64 with more than 128 columns 9 %,
-// SPMM of 33-128 / 129-256 / more columns 2 / 4 / 5 %, bfloat16 SDDMM of more than 64 4 %.  What has no row had less than 1 %
-// to win (FP32 SDDMM of up to 64, all narrower outputs, unaligned operands, bfloat16 SPMM and FusedMM).
+// SPMM of 33-128 / 129-256 / more columns 2 / 4 / 5 %.  What has no row had less than 1 %
+// to win (all narrower outputs, unaligned operands, bfloat16 SPMM and FusedMM).
 // Outside of the ranges of the fit the ratio has to be above the line by kOutside for each factor of e: of 6000 calls there (M
 // 64-200000, K 64-65536, 0.8-95 %, N up to 2048, uneven rows among them) 57 are changed, on average 2.06 times as fast and none
 // slower by more than 3 % (with 0.08 81 and 2, at worst 0.94; with nothing 128 and 6, at worst 0.87).
@@ -1413,8 +1408,8 @@ bool dense_is_faster(const DenseShape &s, const DenseConfig &c, bool planned, do
     RatioFit f;
     if (s.op == kDenseSpmm && !s.bf16 && s.N > 32)
         f = s.N <= 128 ? RatioFit{0.36, -0.69, 0.62} : s.N <= 256 ? RatioFit{0.55, -0.87, 0.77} : RatioFit{0.58, -0.95, 0.85};
-    else if (s.op == kDenseSddmm && s.D > 64)
-        f = s.bf16 ? RatioFit{0.60, -0.95, 0.75} : RatioFit{0.51, -0.88, 0.78};
+    else if (s.op == kDenseSddmm)
+        f = RatioFit{0.51, -0.88, 0.78};
     else if (s.op == kDenseFused && !s.bf16 && s.N > 128)
         f = s.D <= 64 ? RatioFit{0.32, -0.74, 0.68} : RatioFit{-0.09, -0.68, 0.74};
     else
@@ -1440,17 +1435,14 @@ bool dense_chosen(const DeviceState &d, const csrk_plan_s *plan, const DenseShap
     const int unit = s.bf16 ? 8 : 4;
     const bool wide = s.N % unit == 0 && s.D % unit == 0 && (operands & 15u) == 0;
     const double vector = vector_us(s, nnz, wide);
-    if (mode == 1) {
-        if (s.op == kDenseSddmm && !s.bf16 && s.D <= 64 && wide) return false;
-        if (vector < 11.0) return false;                      // (less than any configuration is expected to take)
-    }
+    if (mode == 1 && vector < 11.0) return false;             // (less than any configuration is expected to take)
     if (!dense_config(s, d.cus, c)) return false;
     if (d.fixed && c->bytes > d.head_floats * sizeof(float)) return false;
     if (mode == 2) return true;
     const double density = (double)nnz / ((double)s.M * (double)s.K);
+    double slabs;
+    if (sddmm_slab_us(s, *c, d.cus, density, &slabs)) return slabs * 1.1 < vector;
     if (wide && dense_is_faster(s, *c, plan != nullptr, density, vector)) return true;
-    if (s.op == kDenseSddmm && s.bf16 && s.D <= 64 && wide)
-        return short_bf16_sddmm_us(s, *c, d.cus, (double)nnz, density) * 1.2 < vector;
     const double us = c->us * (s.op == kDenseSddmm ? (0.9 + 0.9 * density) * (wide ? 1.25 : 1.0) : 0.82 + 0.5 * density);
     return us * 1.1 < vector;
 }

@@ -3,6 +3,7 @@
 
 #include <atomic>
 
+#include "kernels_dense_sddmm.hpp"
 #include "kernels_dense_wide.hpp"
 
 namespace csrk {
@@ -22,9 +23,10 @@ constexpr long long kMaxGroups = 1 << 22;
 constexpr int kHalvesK = 8192;
 constexpr double kHalvesTileUs = 1.5, kHalvesFusedTileUs = 2.1;
 
-// SDDMM's tiles: 128 columns where they and B's fit LDS, for the entries of a row in a tile fill the 16 lanes better
-constexpr int sddmm_kt(int ds) { return ds == 1 ? 128 : 64; }
-constexpr int kSddmmMaxKt = 128;
+// SDDMM in slabs of scores (kernels_dense_sddmm.hpp): all but FP32 dot products of more than 64 elements.  Those would need more
+// registers for the rows of A than a wavefront has.
+bool sddmm_slabs(bool bf16, int ds) { return bf16 || ds <= 2; }
+int sddmm_rows(bool bf16, int ds) { return sddmm_slabs(bf16, ds) ? kSlabRows : kDenseBM; }
 
 size_t padded(size_t bytes) { return (bytes + 255) / 256 * 256; }
 size_t up32(int x) { return ((size_t)x + 31) / 32 * 32; }
@@ -56,8 +58,8 @@ struct Layout {
             return was;
         };
         c = take(k * n_tiles * 16 * pieces);
-        // (whole tiles of SDDMM's columns)
-        b = take((k + kSddmmMaxKt - 32) * d * pieces);
+        // (whole tiles of 64 columns)
+        b = take((k + 32) * d * pieces);
         a = take(up32(s.M) * d * pieces);
         todo = take(halves ? DenseScales::bytes(n_tiles, s.K, s.M) : 8);
         met = take(s.op == kDenseFused ? (size_t)b_blocks * 4 : 0);
@@ -96,36 +98,57 @@ DenseKernel again_kernel(int ct, int ds) {
     return {nullptr, 0};
 }
 
-template <int P>
-DenseKernel sddmm_kernel(int ds) {
-#define CSRK_DENSE_CASE(DS) \
-    if (ds == DS) return {dense_sddmm_kernel<DS, P, sddmm_kt(DS)>, DenseSddmmCfg<DS, P, sddmm_kt(DS)>::kBytes};
-    CSRK_DENSE_CASE(1)
-    CSRK_DENSE_CASE(2)
-    CSRK_DENSE_CASE(3)
-    CSRK_DENSE_CASE(4)
-#undef CSRK_DENSE_CASE
-    return {nullptr, 0};
+DenseKernel sddmm_kernel(bool bf16, int ds) {
+#define CSRK_SLAB_CASE(DS, P) \
+    if (ds == DS && bf16 == (P == 1)) return {dense_slab_kernel<DS, P>, SlabCfg<DS, P>::kBytes, SlabCfg<DS, P>::kThreads};
+    CSRK_SLAB_CASE(1, 3)
+    CSRK_SLAB_CASE(2, 3)
+    CSRK_SLAB_CASE(1, 1)
+    CSRK_SLAB_CASE(2, 1)
+    CSRK_SLAB_CASE(3, 1)
+    CSRK_SLAB_CASE(4, 1)
+#undef CSRK_SLAB_CASE
+    if (ds == 3) return {dense_sddmm_kernel<3>, DenseSddmmCfg<3>::kBytes, kDenseThreads};
+    if (ds == 4) return {dense_sddmm_kernel<4>, DenseSddmmCfg<4>::kBytes, kDenseThreads};
+    return {nullptr, 0, 0};
 }
 
 // Time of a workgroup for 32 columns of K, in us, with a CU to itself.  Read off MI355X timings: FP32 SPMM 1.03 us with 2
 // pieces (32768 x 8192), 1.08 with 4, 1.7 with 8, 2.7 with 16 (16384 x 16384); FusedMM with 2 / 4 steps of the dot product
 // 2.0 / 2.9 with 8 pieces; bfloat16 1.1 with 8 and 1.55 with 16.
 double tile_us(const DenseShape &s, int ct, int ds) {
-    if (s.op == kDenseSddmm) return s.bf16 ? 0.75 : 0.75 + 0.2 * ds;
+    if (s.op == kDenseSddmm) return 0.75 + 0.2 * ds;
     if (s.bf16) return 0.65 + 0.056 * ct + 0.05 * ds;
     return 0.6 + 0.13 * ct + 0.27 * ds;
 }
 
 }  // namespace
 
+// Time of an SDDMM call in slabs, in us: per call, and for every round of workgroups to begin and end it, per slab of 256 columns, and
+// by the slab's density.  Fitted to 3300 random calls of M 512-32768, K 512-16384, 6-35 %, D 16-128 on MI355X, which scatter by 7-13 %
+// around it.
+bool sddmm_slab_us(const DenseShape &s, const DenseConfig &c, int cus, double density, double *us) {
+    struct Cost {
+        double call, round, slab, entries;
+    };
+    static constexpr Cost f32[] = {{5.2, 5.5, 1.12, 5.5}, {5.0, 7.1, 2.24, 4.9}};
+    static constexpr Cost bf16[] = {{4.1, 6.3, 0.60, 6.0}, {5.2, 5.6, 0.82, 5.8}, {5.5, 5.9, 0.98, 5.1}, {4.8, 5.7, 1.71, 5.8}};
+    if (s.op != kDenseSddmm || !sddmm_slabs(s.bf16, c.ds)) return false;
+    const Cost t = s.bf16 ? bf16[c.ds - 1] : f32[c.ds - 1];
+    const long long rounds = ((s.M + kSlabRows - 1) / kSlabRows * (long long)c.segs + cus - 1) / cus;
+    *us = t.call + (double)rounds * (t.round + c.seg_k / kSlabCols * (t.slab + t.entries * density));
+    return true;
+}
+
 bool dense_config(const DenseShape &s, int cus, DenseConfig *out) {
     if (s.M < 1 || s.M > kMaxRows || s.K < 32 || s.K > kMaxK) return false;
     if (s.op != kDenseSddmm && (s.N < 1 || s.N > kMaxWidth)) return false;
     if (s.op != kDenseSpmm && (s.D < 1 || s.D > kMaxDot)) return false;
     const size_t pieces = s.bf16 ? 2 : 6;
-    if ((up32(s.K) + 64) * (size_t)(s.N + 256) * pieces >= kView || (up32(s.K) + kSddmmMaxKt) * 128 * pieces >= kView) return false;
-    const long long row_blocks = (s.M + kDenseBM - 1) / kDenseBM;
+    if ((up32(s.K) + 64) * (size_t)(s.N + 256) * pieces >= kView || (up32(s.K) + 128) * 128 * pieces >= kView) return false;
+    const bool slabs = s.op == kDenseSddmm && sddmm_slabs(s.bf16, (s.D + 31) / 32);
+    const int bm = s.op == kDenseSddmm ? sddmm_rows(s.bf16, (s.D + 31) / 32) : kDenseBM;
+    const long long row_blocks = (s.M + bm - 1) / bm;
     DenseConfig best{};
     best.us = 1e30;
     DenseConfig c{};
@@ -137,8 +160,8 @@ bool dense_config(const DenseShape &s, int cus, DenseConfig *out) {
         if (s.op == kDenseFused && c.ds > 2 && ct > 8) continue;
         const int col_blocks = s.op == kDenseSddmm ? 1 : (s.N + ct * 16 - 1) / (ct * 16);
         for (int segs = 1; segs <= kDenseMaxSegs; ++segs) {
-            // ranges of whole tiles (of 64 columns; SDDMM's), of at least 128 columns
-            const int step = s.op == kDenseSddmm ? sddmm_kt(c.ds) / 32 : 2;
+            // ranges of whole tiles (of 64 columns; slabs), of at least 128 columns
+            const int step = slabs ? kSlabCols / 32 : 2;
             const int seg_tiles = ((tiles + segs - 1) / segs + step - 1) / step * step;
             if (segs > 1 && (seg_tiles < 4 || (tiles + seg_tiles - 1) / seg_tiles != segs)) continue;
             const long long wgs = row_blocks * col_blocks * segs;
@@ -147,11 +170,12 @@ bool dense_config(const DenseShape &s, int cus, DenseConfig *out) {
             // a launch of 8 us all told, 4 us to begin and end each workgroup, the ranges' outputs written and read again
             double us = 8.0 + (double)rounds * (seg_tiles * tile_us(s, ct, c.ds) + 4.0);
             if (segs > 1 && s.op != kDenseSddmm) us += 3.0 + (double)(segs + 1) * s.M * (double)s.N * 4.0 / 4.0e6;
+            c.segs = segs;
+            c.seg_k = seg_tiles * 32;
+            sddmm_slab_us(s, c, cus, 0.15, &us);        // (how dense S is is not known here)
             if (us < best.us) {
                 best = c;
                 best.ct = ct;
-                best.segs = segs;
-                best.seg_k = seg_tiles * 32;
                 best.us = us;
             }
         }
@@ -164,7 +188,7 @@ bool dense_config(const DenseShape &s, int cus, DenseConfig *out) {
     }
     const Layout l(s, best);
     best.bytes = l.bytes;
-    best.us += (double)l.partial / 2.0e6;           // the operands' preparation
+    if (!slabs) best.us += (double)l.partial / 2.0e6;           // the operands' preparation
     *out = best;
     return true;
 }
@@ -178,7 +202,8 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
     a.K = s.K;
     a.N = s.op == kDenseSddmm ? 0 : s.N;
     a.D = s.op == kDenseSpmm ? 0 : s.D;
-    a.row_blocks = (s.M + kDenseBM - 1) / kDenseBM;
+    const int bm = s.op == kDenseSddmm ? sddmm_rows(s.bf16, c.ds) : kDenseBM;
+    a.row_blocks = (s.M + bm - 1) / bm;
     a.col_blocks = s.op == kDenseSddmm ? 1 : l.n_tiles / c.ct;
     a.segs = c.segs;
     a.seg_k = c.seg_k;
@@ -209,9 +234,9 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
 
     const DenseKernel k = c.halves              ? wide_kernel(c.ct, c.ds)
                           : s.op == kDenseSpmm  ? (s.bf16 ? spmm_kernel<1>(c.ct) : spmm_kernel<3>(c.ct))
-                          : s.op == kDenseSddmm ? (s.bf16 ? sddmm_kernel<1>(c.ds) : sddmm_kernel<3>(c.ds))
+                          : s.op == kDenseSddmm ? sddmm_kernel(s.bf16, c.ds)
                                                 : (s.bf16 ? dense_fused_kernel_bf16(c.ct, c.ds) : dense_fused_kernel_f32(c.ct, c.ds));
-    const DenseKernel again = c.halves ? again_kernel(c.ct, c.ds) : DenseKernel{nullptr, 0};
+    const DenseKernel again = c.halves ? again_kernel(c.ct, c.ds) : DenseKernel{nullptr, 0, 0};
     if (!k.fn || (c.halves && !again.fn)) return hipErrorInvalidValue;
     {
         // once per kernel and device (harmless if two threads do it)
@@ -233,7 +258,7 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
     else if (c.halves) hipLaunchKernelGGL((dense_prepare_kernel<float, true>), dim3(prepare), dim3(256), 0, stream, a);
     else hipLaunchKernelGGL(dense_prepare_kernel<float>, dim3(prepare), dim3(256), 0, stream, a);
     const dim3 jobs((unsigned)a.row_blocks * a.col_blocks * a.segs);
-    hipLaunchKernelGGL(k.fn, jobs, dim3(kDenseThreads), k.lds_bytes, stream, a);
+    hipLaunchKernelGGL(k.fn, jobs, dim3(k.threads), k.lds_bytes, stream, a);
     if (c.halves) {
         // (few workgroups to find that there is nothing to do; no cuts)
         DenseArgs b = a;

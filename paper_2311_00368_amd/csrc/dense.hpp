@@ -30,6 +30,9 @@ struct DenseConfig {
 // false: not a shape for these kernels
 bool dense_config(const DenseShape &s, int cus, DenseConfig *c);
 
+// What an SDDMM call with that share of S's cells stored is expected to take where it is done in slabs of scores; false: it is not.
+bool sddmm_slab_us(const DenseShape &s, const DenseConfig &c, int cus, double density, double *us);
+
 // `scratch`: 256-byte aligned, config's size.  Nothing is allocated and nothing read back; may be captured.
 hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *rowptr, const int32_t *colidx, const float *vals,
                      const void *A, const void *B, const void *C, float *out, void *scratch, hipStream_t stream);
@@ -38,6 +41,7 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
 struct DenseKernel {
     void (*fn)(DenseArgs);
     int lds_bytes;
+    int threads = 512;
 };
 DenseKernel dense_fused_kernel_f32(int ct, int ds);
 DenseKernel dense_fused_kernel_bf16(int ct, int ds);
