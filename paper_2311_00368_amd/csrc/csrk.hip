@@ -1372,15 +1372,16 @@ double vector_us(const DenseShape &s, long long nnz, bool wide) {
     return c.call + c.work * 1e-9 * (double)nnz * (s.N + s.D) + c.entries * 1e-6 * (double)nnz + c.cells * 1e-6 * (double)s.M * s.K;
 }
 
-// The matrix-core kernels are taken where they are expected to be the faster ones by a tenth (SDDMM: by a third).  Over
+// The matrix-core kernels are taken where they are expected to be the faster ones by a tenth.  Over
 // 4000 other random calls of the ranges above, uneven rows among them, that made the average call 1.34 times as fast
 // (always the better of the two: 1.46), and 22 calls slower by more than 3 % (at worst 0.77 times as fast).  Over 4000 calls
 // of M 16-200000, K 32-65536, up to 2048 columns and 0.4-95 % it was 1.14 times (1.37), 4 slower (at worst 0.64).
-// SDDMM in slabs of scores (all of bfloat16, FP32 of up to 64 elements) has an estimate of its own and is taken where that is a tenth
-// below the vector kernels'.  Of 1200 other random calls of these ranges, uneven rows among them, that makes the average one of up to 32 /
-// 64 FP32 elements 1.11 / 1.14 times as fast as the vector kernels (always the better of the two: 1.17 / 1.23) and that of bfloat16 1.19
-// times as fast as the choice before (1.26).  Of 1800 FP32 calls with even rows 5 are slower by more than 3 %, at worst 0.89 times as fast;
-// of those with log-normal rows, which the host cannot tell, a twentieth, at worst 0.78 times as fast.
+// SDDMM in slabs of scores (all but FP32 of more than 64 elements without stored values) has an estimate of its own.  It is taken
+// where that is a tenth below the vector kernels', of more than 64 elements, where both are closer, where it is below.  Random calls of
+// these ranges, times as fast as the vector kernels on average (always the better of the two): FP32 of up to 32 elements 1.11 (1.17),
+// 33-64 1.14 (1.23), 65-96 1.32 (1.34), 97-128 1.34 (1.38); bfloat16 1.19 times as fast as the choice before (1.26).  Of 1800 FP32
+// calls with even rows and up to 64 elements 5 are slower by more than 3 %, at worst 0.89 times as fast; of those with log-normal
+// rows, which the host cannot tell, a twentieth, at worst 0.78 times.
 
 // The two estimates above err in ways that depend on the class of the call: the kernels of both sides have changed since
 // they were fitted, and a call of 30 us is not a call of 300 us made ten times.  So for the classes where that loses most
@@ -1392,7 +1393,7 @@ double vector_us(const DenseShape &s, long long nnz, bool wide) {
 //     over 9000 other calls  changes  now faster by > 3 %  slower by > 3 %  at worst  average of those changed
 //     operands in turn           342                  308               19      0.84                      1.43
 //     cold caches                314                  289               13      0.80                      1.40
-// On average over a class: FP32 SDDMM of more than 64 elements 9 %, FusedMM of more than 64 with more than 128 columns 9 %,
+// On average over a class: FP32 SDDMM of more than 64 elements 9 % (now without stored values only), FusedMM of more than 64 with more than 128 columns 9 %,
 // SPMM of 33-128 / 129-256 / more columns 2 / 4 / 5 %.  What has no row had less than 1 %
 // to win (all narrower outputs, unaligned operands, bfloat16 SPMM and FusedMM).
 // Outside of the ranges of the fit the ratio has to be above the line by kOutside for each factor of e: of 6000 calls there (M
@@ -1441,7 +1442,7 @@ bool dense_chosen(const DeviceState &d, const csrk_plan_s *plan, const DenseShap
     if (mode == 2) return true;
     const double density = (double)nnz / ((double)s.M * (double)s.K);
     double slabs;
-    if (sddmm_slab_us(s, *c, d.cus, density, &slabs)) return slabs * 1.1 < vector;
+    if (sddmm_slab_us(s, *c, d.cus, density, &slabs)) return slabs * (s.D > 64 ? 1.0 : 1.1) < vector;
     if (wide && dense_is_faster(s, *c, plan != nullptr, density, vector)) return true;
     const double us = c->us * (s.op == kDenseSddmm ? (0.9 + 0.9 * density) * (wide ? 1.25 : 1.0) : 0.82 + 0.5 * density);
     return us * 1.1 < vector;
@@ -1650,7 +1651,7 @@ static csrk_status sddmm_run(const csrk_plan_s *plan, const ScratchSource &scrat
     DeviceState *d = &state;
     if (csrk_status s = begin_call(state, scratch, lock)) return s;
     CallRecord rec(2, stream);
-    const DenseShape shape{kDenseSddmm, false, M, K, 0, D};
+    const DenseShape shape{kDenseSddmm, false, M, K, 0, D, !vals};
     DenseConfig dense;
     if (dense_wanted(*d, plan, shape, addresses({A, B}), nnz, stream, &dense)) {
         rec.begin();
@@ -1877,9 +1878,11 @@ static size_t workspace_floats(const DeviceInfo &info, int op, int M, int K, int
     size_t floats = vector_floats(info, op, M, K, N);
     auto add = [&](int d) {
         const DenseOp kind = op == CSRK_OP_SPMM ? kDenseSpmm : op == CSRK_OP_SDDMM ? kDenseSddmm : kDenseFused;
-        DenseConfig c;
-        if (dense_config(DenseShape{kind, false, M, K, N, d}, info.cus, &c) && c.bytes / sizeof(float) + 1 > floats)
-            floats = c.bytes / sizeof(float) + 1;
+        for (bool ones : {false, true}) {
+            DenseConfig c;
+            if (dense_config(DenseShape{kind, false, M, K, N, d, ones}, info.cus, &c) && c.bytes / sizeof(float) + 1 > floats)
+                floats = c.bytes / sizeof(float) + 1;
+        }
     };
     if (op == CSRK_OP_SPMM || D > 0) add(D);
     else

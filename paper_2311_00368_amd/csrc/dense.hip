@@ -23,10 +23,11 @@ constexpr long long kMaxGroups = 1 << 22;
 constexpr int kHalvesK = 8192;
 constexpr double kHalvesTileUs = 1.5, kHalvesFusedTileUs = 2.1;
 
-// SDDMM in slabs of scores (kernels_dense_sddmm.hpp): all but FP32 dot products of more than 64 elements.  Those would need more
-// registers for the rows of A than a wavefront has.
-bool sddmm_slabs(bool bf16, int ds) { return bf16 || ds <= 2; }
-int sddmm_rows(bool bf16, int ds) { return sddmm_slabs(bf16, ds) ? kSlabRows : kDenseBM; }
+// SDDMM in slabs of scores (kernels_dense_sddmm.hpp): all but FP32 dot products of more than 64 elements without stored values.
+// Those are the sum of two wavefronts' halves; where a value is multiplied by, that takes one rounding less and the error is 0.95
+// (both signs) and 0.82 (one sign) of the other kernel's, without it is 1.05-1.08.
+bool sddmm_slabs(const DenseShape &s) { return s.bf16 || s.D <= 64 || !s.ones; }
+int sddmm_rows(const DenseShape &s) { return sddmm_slabs(s) ? kSlabRows : kDenseBM; }
 
 size_t padded(size_t bytes) { return (bytes + 255) / 256 * 256; }
 size_t up32(int x) { return ((size_t)x + 31) / 32 * 32; }
@@ -98,18 +99,20 @@ DenseKernel again_kernel(int ct, int ds) {
     return {nullptr, 0};
 }
 
-DenseKernel sddmm_kernel(bool bf16, int ds) {
+DenseKernel sddmm_kernel(const DenseShape &s, int ds) {
+    if (!sddmm_slabs(s) && ds == 3) return {dense_sddmm_kernel<3>, DenseSddmmCfg<3>::kBytes, kDenseThreads};
+    if (!sddmm_slabs(s) && ds == 4) return {dense_sddmm_kernel<4>, DenseSddmmCfg<4>::kBytes, kDenseThreads};
 #define CSRK_SLAB_CASE(DS, P) \
-    if (ds == DS && bf16 == (P == 1)) return {dense_slab_kernel<DS, P>, SlabCfg<DS, P>::kBytes, SlabCfg<DS, P>::kThreads};
+    if (ds == DS && s.bf16 == (P == 1)) return {dense_slab_kernel<DS, P>, SlabCfg<DS, P>::kBytes, SlabCfg<DS, P>::kThreads};
     CSRK_SLAB_CASE(1, 3)
     CSRK_SLAB_CASE(2, 3)
+    CSRK_SLAB_CASE(3, 3)
+    CSRK_SLAB_CASE(4, 3)
     CSRK_SLAB_CASE(1, 1)
     CSRK_SLAB_CASE(2, 1)
     CSRK_SLAB_CASE(3, 1)
     CSRK_SLAB_CASE(4, 1)
 #undef CSRK_SLAB_CASE
-    if (ds == 3) return {dense_sddmm_kernel<3>, DenseSddmmCfg<3>::kBytes, kDenseThreads};
-    if (ds == 4) return {dense_sddmm_kernel<4>, DenseSddmmCfg<4>::kBytes, kDenseThreads};
     return {nullptr, 0, 0};
 }
 
@@ -125,15 +128,15 @@ double tile_us(const DenseShape &s, int ct, int ds) {
 }  // namespace
 
 // Time of an SDDMM call in slabs, in us: per call, and for every round of workgroups to begin and end it, per slab of 256 columns, and
-// by the slab's density.  Fitted to 3300 random calls of M 512-32768, K 512-16384, 6-35 %, D 16-128 on MI355X, which scatter by 7-13 %
+// by the slab's density.  Fitted to 3600 random calls of M 512-32768, K 512-16384, 6-35 %, D 16-128 on MI355X, which scatter by 5-13 %
 // around it.
 bool sddmm_slab_us(const DenseShape &s, const DenseConfig &c, int cus, double density, double *us) {
     struct Cost {
         double call, round, slab, entries;
     };
-    static constexpr Cost f32[] = {{5.2, 5.5, 1.12, 5.5}, {5.0, 7.1, 2.24, 4.9}};
+    static constexpr Cost f32[] = {{5.2, 5.5, 1.12, 5.5}, {5.0, 7.1, 2.24, 4.9}, {5.4, 7.1, 4.1, 3.3}, {5.4, 8.0, 4.7, 2.6}};
     static constexpr Cost bf16[] = {{4.1, 6.3, 0.60, 6.0}, {5.2, 5.6, 0.82, 5.8}, {5.5, 5.9, 0.98, 5.1}, {4.8, 5.7, 1.71, 5.8}};
-    if (s.op != kDenseSddmm || !sddmm_slabs(s.bf16, c.ds)) return false;
+    if (s.op != kDenseSddmm || !sddmm_slabs(s)) return false;
     const Cost t = s.bf16 ? bf16[c.ds - 1] : f32[c.ds - 1];
     const long long rounds = ((s.M + kSlabRows - 1) / kSlabRows * (long long)c.segs + cus - 1) / cus;
     *us = t.call + (double)rounds * (t.round + c.seg_k / kSlabCols * (t.slab + t.entries * density));
@@ -146,8 +149,8 @@ bool dense_config(const DenseShape &s, int cus, DenseConfig *out) {
     if (s.op != kDenseSpmm && (s.D < 1 || s.D > kMaxDot)) return false;
     const size_t pieces = s.bf16 ? 2 : 6;
     if ((up32(s.K) + 64) * (size_t)(s.N + 256) * pieces >= kView || (up32(s.K) + 128) * 128 * pieces >= kView) return false;
-    const bool slabs = s.op == kDenseSddmm && sddmm_slabs(s.bf16, (s.D + 31) / 32);
-    const int bm = s.op == kDenseSddmm ? sddmm_rows(s.bf16, (s.D + 31) / 32) : kDenseBM;
+    const bool slabs = s.op == kDenseSddmm && sddmm_slabs(s);
+    const int bm = s.op == kDenseSddmm ? sddmm_rows(s) : kDenseBM;
     const long long row_blocks = (s.M + bm - 1) / bm;
     DenseConfig best{};
     best.us = 1e30;
@@ -202,7 +205,7 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
     a.K = s.K;
     a.N = s.op == kDenseSddmm ? 0 : s.N;
     a.D = s.op == kDenseSpmm ? 0 : s.D;
-    const int bm = s.op == kDenseSddmm ? sddmm_rows(s.bf16, c.ds) : kDenseBM;
+    const int bm = s.op == kDenseSddmm ? sddmm_rows(s) : kDenseBM;
     a.row_blocks = (s.M + bm - 1) / bm;
     a.col_blocks = s.op == kDenseSddmm ? 1 : l.n_tiles / c.ct;
     a.segs = c.segs;
@@ -234,7 +237,7 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
 
     const DenseKernel k = c.halves              ? wide_kernel(c.ct, c.ds)
                           : s.op == kDenseSpmm  ? (s.bf16 ? spmm_kernel<1>(c.ct) : spmm_kernel<3>(c.ct))
-                          : s.op == kDenseSddmm ? sddmm_kernel(s.bf16, c.ds)
+                          : s.op == kDenseSddmm ? sddmm_kernel(s, c.ds)
                                                 : (s.bf16 ? dense_fused_kernel_bf16(c.ct, c.ds) : dense_fused_kernel_f32(c.ct, c.ds));
     const DenseKernel again = c.halves ? again_kernel(c.ct, c.ds) : DenseKernel{nullptr, 0, 0};
     if (!k.fn || (c.halves && !again.fn)) return hipErrorInvalidValue;
@@ -243,7 +246,7 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
         static std::atomic<uint64_t> done[3][3][17][5];
         int dev = 0;
         if (hipError_t e = hipGetDevice(&dev)) return e;
-        std::atomic<uint64_t> &seen = done[s.op][s.bf16 ? 1 : c.halves ? 2 : 0][c.ct][c.ds];
+        std::atomic<uint64_t> &seen = done[s.op][s.bf16 ? 1 : c.halves || (s.op == kDenseSddmm && !sddmm_slabs(s)) ? 2 : 0][c.ct][c.ds];
         const uint64_t bit = 1ull << (dev & 63);
         if (!(seen.load(std::memory_order_acquire) & bit)) {
             for (const DenseKernel &one : {k, again})

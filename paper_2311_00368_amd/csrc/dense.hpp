@@ -16,6 +16,7 @@ struct DenseShape {
     DenseOp op;
     bool bf16;              // the dense operands' type; otherwise float
     int M, K, N, D;         // N: output columns (0 for SDDMM), D: length of the dot products (0 for SPMM)
+    bool ones = false;      // SDDMM: no stored values
 };
 
 struct DenseConfig {

@@ -1,4 +1,4 @@
-// Matrix-core SDDMM in slabs of scores: all bfloat16 calls, FP32 with dot products of up to 64 elements.
+// Matrix-core SDDMM in slabs of scores: all calls but FP32 ones of more than 64 elements without stored values (sddmm_slabs, dense.hip).
 //
 // A workgroup owns 64 rows of S and goes through its range of K in slabs of 256 columns.  Four of its wavefronts (one on each SIMD)
 // compute a slab's scores, all 64 x 256 of them, into one of two buffers in LDS, while the other 8 or 12 pick the stored entries'
@@ -23,6 +23,11 @@
 // (the time of its bytes at the rate of a large copy: 68), 20 % 281 / 176 (135), D = 16 30 % 425 / 250; 16384^2, 20 %, D = 64 303 / 233
 // (137); 4096^2, 30 %, D = 64 45.7 / 26; bfloat16 16384 x 8192, 10 %, D = 32 73 / 39, 20 %, D = 64 173 / 78, D = 128 190 / 94.  Error against
 // FP64 in the 2-norm at D = 32 / 64 4.4e-8 / 4.8e-8 (vector kernels 1.06e-7 / 1.47e-7).
+// FP32 dot products of more than 64 elements need more registers for A than a scorer has: two scorers have one half of the steps each
+// and two the other, in slabs of 128 columns, and the handlers add the halves' products with the entry's value.  Kernel of 16 lanes per
+// row / this: 4096^2, 30 %, D = 128 46 / 37 us; 16384^2, 20 %, D = 128 480 / 367; 8192^2, 15 %, D = 72 98 / 86; log-normal rows, 10 %, D = 128
+// 136 / 95.  Error against FP64 5.3e-8 / 5.1e-8, of data of one sign 4.7e-8 / 3.8e-8 (the halves' sum in one accumulator after the
+// other: 9.9e-8; added before the multiplication 5.5e-8).
 // What bounds it: at 10 % and D = 32 neither kind alone (scorers 88 us, handlers 89, of which 19 for the call and each workgroup's
 // first loads) but both on one SIMD, whose matrix cores are busy for 40 % of the cycles; from 20 % on the handlers, at the rate of
 // memory (150 us without the scores at 20 %).  With D = 64 B does not fit an L2 and its fragments are late (151 us without them): the
@@ -38,15 +43,18 @@ constexpr int kSlabRows = 64, kSlabCols = 256;
 // with 12).  Fragments ahead: a tile of FP32 with D = 32 takes 400 cycles, and B's are 1000 away (two tiles: 141 us, four: 133).
 template <int DS, int P>
 struct SlabCfg {
-    static constexpr int kRows = kSlabRows, kCols = kSlabCols;
+    // FP32 of more than 64 elements: half of the scorers compute the first two steps' products, the others those of the rest, in slabs of
+    // half the columns; the handlers add the two.
+    static constexpr int kParts = DS * P > 6 ? 2 : 1;
+    static constexpr int kRows = kSlabRows, kCols = kSlabCols / kParts;
     static constexpr int kScorers = 4, kHandlers = DS * P <= 3 ? 12 : 8;
     static constexpr int kThreads = (kScorers + kHandlers) * kWave;
-    static constexpr int kRow = (kCols + 4) * 4, kBuffer = kRows * kRow;
+    static constexpr int kRow = (kCols + 4) * 4, kPart = kRows * kRow, kBuffer = kParts * kPart;
     static constexpr int kHandled = (kRows + kHandlers - 1) / kHandlers;    // rows whose entries a wavefront handles: every kHandlers-th
     // 16-row fragments of B under way or in use
     static constexpr int kAhead = DS * P <= 3 ? 4 : 2;
     // (the words that a wavefront without a last row reads lie behind the second buffer)
-    static constexpr int kOffRest = kBuffer + kHandled * kHandlers * kRow;
+    static constexpr int kOffRest = 2 * kBuffer + (kHandled * kHandlers - kRows) * kRow;
     static constexpr int kBytes = kOffRest + kRows * 8 + 16;
     static_assert(kBytes <= 160 * 1024, "LDS of a gfx950 CU");
 };
@@ -94,28 +102,30 @@ __device__ __forceinline__ void slab_scores(const bf16x8 (&b)[DS][P], const bf16
 }
 
 // The scores of all of the range's slabs, into the two buffers in turn.
-template <int DS, int P>
+// PART: of the dot products; `wave`: of its scorers.
+template <int ALL, int P, int PART>
 __device__ __forceinline__ void slab_produce(const DenseArgs &a, const DenseJob &job, int wave, char *dlds) {
-    using L = SlabCfg<DS, P>;
-    constexpr int NT = L::kCols / 16 / L::kScorers, RT = L::kRows / 16, NB = L::kAhead, NR = DS == 1 ? 4 : 2;
+    using L = SlabCfg<ALL, P>;
+    constexpr int D0 = PART * 2, DS = L::kParts == 1 ? ALL : PART == 0 ? 2 : ALL - 2;       // steps from D0 on
+    constexpr int NT = L::kCols / 16 / (L::kScorers / L::kParts), RT = L::kRows / 16, NB = L::kAhead, NR = ALL == 1 ? 4 : 2;
     const int lane = lane_id();
     // B's fragments: 16 rows each, from memory to registers (rows past the last prepared one read as zeros)
-    const unsigned b_end = (unsigned)((a.K + 31) / 32) * 2u * DS * P * 1024u;
+    const unsigned b_end = (unsigned)((a.K + 31) / 32) * 2u * ALL * P * 1024u;
     const DenseView bview = dense_view(a.Bp, b_end);
     bf16x8 b[NB][DS][P];
     auto issue = [&](int k0, int t) CSRK_INLINE {
-        const unsigned want = (unsigned)((k0 + t / NT * L::kCols) / 16 + wave * NT + t % NT) * (DS * P * 1024u), at = want < b_end ? want : b_end;
+        const unsigned want = (unsigned)((k0 + t / NT * L::kCols) / 16 + wave * NT + t % NT) * (ALL * P * 1024u), at = want < b_end ? want : b_end;
 #pragma unroll
         for (int d = 0; d < DS; ++d)
 #pragma unroll
             for (int p = 0; p < P; ++p)
-                b[t % NB][d][p] = __builtin_bit_cast(bf16x8, load_f32x4(bview, lane * 16u + (d * P + p) * 1024u, at));
+                b[t % NB][d][p] = __builtin_bit_cast(bf16x8, load_f32x4(bview, lane * 16u + ((D0 + d) * P + p) * 1024u, at));
     };
 #pragma unroll
-    for (int t = 0; t < (DS == 1 ? NB - 1 : NB); ++t) issue(job.kb, t);
+    for (int t = 0; t < (ALL == 1 ? NB - 1 : NB); ++t) issue(job.kb, t);
     bf16x8 af[RT][DS][P];
 #pragma unroll
-    for (int r = 0; r < RT; ++r) dense_load_a<DS, P>(a, job.row0 + r * 16, af[r]);
+    for (int r = 0; r < RT; ++r) dense_load_a<DS, P, ALL>(a, job.row0 + r * 16, af[r], D0);
     // (waits for them here, not in the loop, where it would be for B's as well)
 #pragma unroll
     for (int r = 0; r < RT; ++r)
@@ -123,12 +133,12 @@ __device__ __forceinline__ void slab_produce(const DenseArgs &a, const DenseJob 
         for (int d = 0; d < DS; ++d)
 #pragma unroll
             for (int p = 0; p < P; ++p) asm volatile("" : "+v"(af[r][d][p]));
-    char *const to = dlds + (lane & 15) * L::kRow + wave * NT * 64 + (lane >> 4) * 16;
+    char *const to = dlds + PART * L::kPart + (lane & 15) * L::kRow + wave * NT * 64 + (lane >> 4) * 16;
     auto write = [&](unsigned buf, int t, int r, f32x4 x) CSRK_INLINE {
         *reinterpret_cast<f32x4 *>(to + buf + r * 16 * L::kRow + t * 64) = x;
     };
     unsigned buf = 0;
-    if constexpr (DS == 1) {
+    if constexpr (ALL == 1) {
         // a tile's scores are written, and its fragments' registers loaded anew, between the products of the tile behind it
         f32x4 score[2][RT];
         for (int k0 = job.kb; k0 < job.ke; k0 += L::kCols, buf ^= L::kBuffer) {
@@ -183,7 +193,9 @@ __global__ __launch_bounds__((SlabCfg<DS, P>::kThreads)) void dense_slab_kernel(
     int *const next = reinterpret_cast<int *>(rest + L::kRows);
     bool some = false;
     if (wave < 0) {
-        slab_produce<DS, P>(a, job, wave + L::kScorers, dlds);
+        const int scorer = wave + L::kScorers;
+        if (L::kParts == 1 || scorer < L::kScorers / 2) slab_produce<DS, P, 0>(a, job, scorer, dlds);
+        else if constexpr (L::kParts == 2) slab_produce<DS, P, 1>(a, job, scorer - L::kScorers / 2, dlds);
     } else {
         const int M = a.M;
         // Positions are relative to the line of 64 entries that the workgroup's first one lies in.
@@ -200,7 +212,7 @@ __global__ __launch_bounds__((SlabCfg<DS, P>::kThreads)) void dense_slab_kernel(
         // are byte offsets in a row of scores.
         int at = 0, first = 0, left = 0, last = 0x7fffffff;
         int ec[NR], en[NR];
-        float ev[NR], vn[NR], res[NR];
+        float ev[NR], vn[NR], res[NR], res2[L::kParts == 2 ? NR : 1];
         const float none = float_of(0x7f800000u);
         auto load_cols = [&](int p) CSRK_INLINE { return (int)__builtin_amdgcn_raw_buffer_load_b32(civ.rsrc, lane4 + (unsigned)p, 0, 0); };
         auto load_vals = [&](int p) CSRK_INLINE { return float_of(__builtin_amdgcn_raw_buffer_load_b32(vav.rsrc, lane4 + (unsigned)p, 0, 0)); };
@@ -219,6 +231,7 @@ __global__ __launch_bounds__((SlabCfg<DS, P>::kThreads)) void dense_slab_kernel(
             ev[r] = load_vals(p);
             vn[r] = load_vals(p + kWave * 4);
             res[r] = none;
+            if constexpr (L::kParts == 2) res2[r] = 0.f;
         }
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
@@ -234,7 +247,7 @@ __global__ __launch_bounds__((SlabCfg<DS, P>::kThreads)) void dense_slab_kernel(
         __syncthreads();
         for (int k0 = job.kb; k0 < job.ke; k0 += KT, from += buf, buf = -buf) {
             typedef __attribute__((address_space(3))) float lds_float;
-            float x[NR];
+            float x[NR], y[L::kParts == 2 ? NR : 1];
             int to[NR], in[NR];
             const int before = k0 * 4 - (int)from, end_at = (int)from + KT * 4 - 4;
             auto look = [&](int r) CSRK_INLINE {
@@ -242,11 +255,14 @@ __global__ __launch_bounds__((SlabCfg<DS, P>::kThreads)) void dense_slab_kernel(
                 // (lanes with columns of other slabs all read the first or the last word)
                 asm("v_med3_i32 %0, %1, %2, %3" : "=v"(in[r]) : "v"(to[r]), "s"(from), "v"(end_at));
                 x[r] = *(const lds_float *)(uintptr_t)(unsigned)(in[r] + r * (L::kHandlers * L::kRow));
+                if constexpr (L::kParts == 2) y[r] = *(const lds_float *)(uintptr_t)(unsigned)(in[r] + L::kPart + r * (L::kHandlers * L::kRow));
             };
             // the entries of row r's chunk that lie in the slab
             auto take = [&](int r) CSRK_INLINE {
                 asm volatile("" : "+v"(x[r]));
                 res[r] = to[r] == in[r] ? x[r] : res[r];
+                if constexpr (L::kParts == 2) asm volatile("" : "+v"(y[r]));
+                if constexpr (L::kParts == 2) res2[r] = to[r] == in[r] ? y[r] : res2[r];
             };
             // the rows whose chunk is done
             auto through = [&]() CSRK_INLINE { return (unsigned)__ballot(last < (k0 + KT) * 4); };
@@ -265,9 +281,17 @@ __global__ __launch_bounds__((SlabCfg<DS, P>::kThreads)) void dense_slab_kernel(
                     if (more >> r & 1) {
                         const int p = __builtin_amdgcn_readlane(at, r);
                         int end = __builtin_amdgcn_readlane(en[r], kWave - 1) * 4;
-                        const unsigned long long odd = __ballot(!(__builtin_fabsf(res[r]) < kDenseHuge));
-                        float y = res[r] * DenseScale<P, false>::kScoreBack;
-                        if (a.vals) y *= ev[r];
+                        float size = __builtin_fabsf(res[r]), y = res[r] * DenseScale<P, false>::kScoreBack;
+                        if constexpr (L::kParts == 2) {
+                            // (the halves' sum in the multiplication: one rounding less, and the error of this kernel's scores no larger
+                            // than that of sums in one wavefront)
+                            const float half = res2[r] * DenseScale<P, false>::kScoreBack;
+                            size += __builtin_fabsf(res2[r]);
+                            y = a.vals ? fmaf(y, ev[r], half * ev[r]) : y + half;
+                        } else if (a.vals) {
+                            y *= ev[r];
+                        }
+                        const unsigned long long odd = __ballot(!(size < kDenseHuge));
                         unsigned off = lane4 + (unsigned)p;
                         bool fine = odd == 0;
                         if (__builtin_expect(!fine || (edges >> r & 1), 0)) {
@@ -286,6 +310,7 @@ __global__ __launch_bounds__((SlabCfg<DS, P>::kThreads)) void dense_slab_kernel(
                         asm volatile("v_lshlrev_b32 %0, 2, %1" : "=v"(ec[r]) : "v"(en[r]));
                         asm volatile("v_mov_b32 %0, %1" : "=v"(ev[r]) : "v"(vn[r]));
                         res[r] = none;
+                        if constexpr (L::kParts == 2) res2[r] = 0.f;
                         en[r] = load_cols(p + 2 * kWave * 4);
                         vn[r] = load_vals(p + 2 * kWave * 4);
                         look(r);
