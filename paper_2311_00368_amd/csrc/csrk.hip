@@ -1425,6 +1425,13 @@ uintptr_t addresses(std::initializer_list<const void *> pointers) {
     return a;
 }
 
+// What the matrix-core kernels are expected to take, in us; `wide`: 128-bit accesses of all operands.
+double dense_us(const DeviceState &d, const DenseShape &s, const DenseConfig &c, double density, bool wide) {
+    double us = c.us;
+    if (sddmm_slab_us(s, c, d.cus, density, &us)) return us;
+    return us * (s.op == kDenseSddmm ? (0.9 + 0.9 * density) * (wide ? 1.25 : 1.0) : 0.82 + 0.5 * density);
+}
+
 // `operands`: the addresses of the dense operands and of O, or'ed together
 bool dense_chosen(const DeviceState &d, const csrk_plan_s *plan, const DenseShape &s, uintptr_t operands, long long nnz, DenseConfig *c) {
     const int mode = env_int("CSRK_MFMA", 1);       // 1 auto, 2 force where the kernels can run, 3 off
@@ -1441,11 +1448,9 @@ bool dense_chosen(const DeviceState &d, const csrk_plan_s *plan, const DenseShap
     if (d.fixed && c->bytes > d.head_floats * sizeof(float)) return false;
     if (mode == 2) return true;
     const double density = (double)nnz / ((double)s.M * (double)s.K);
-    double slabs;
-    if (sddmm_slab_us(s, *c, d.cus, density, &slabs)) return slabs * (s.D > 64 ? 1.0 : 1.1) < vector;
-    if (wide && dense_is_faster(s, *c, plan != nullptr, density, vector)) return true;
-    const double us = c->us * (s.op == kDenseSddmm ? (0.9 + 0.9 * density) * (wide ? 1.25 : 1.0) : 0.82 + 0.5 * density);
-    return us * 1.1 < vector;
+    if (!(s.op == kDenseSddmm && sddmm_in_slabs(s)) && wide && dense_is_faster(s, *c, plan != nullptr, density, vector)) return true;
+    const double us = dense_us(d, s, *c, density, wide);
+    return us * (s.op == kDenseSddmm && sddmm_in_slabs(s) && s.D > 64 ? 1.0 : 1.1) < vector;
 }
 
 // The vector kernels need far less scratch, so a call that cannot have what the matrix-core kernels need is theirs: one
@@ -1467,6 +1472,61 @@ csrk_status dense_call(DeviceState &d, const DenseShape &s, const DenseConfig &c
                        const float *vals, const void *A, const void *B, const void *C, float *out, hipStream_t stream) {
     if (csrk_status e = ensure_scratch(d, 1, (c.bytes + sizeof(float) - 1) / sizeof(float))) return e;
     CSRK_HIP(dense_run(s, c, rowptr, colidx, vals, A, B, C, out, d.head, stream));
+    return CSRK_OK;
+}
+
+// FusedMM as SDDMM and SPMM on its result, which lies in scratch for so long: a workgroup of FusedMM computes the scores of its
+// block of the output, so all of them once per block.  In half-precision pieces (kernels_dense_wide.hpp), whose blocks have up to 256
+// columns, and with dot products of 33-64 elements that costs more than writing the products and reading them again where there
+// are two blocks: 16384^2, 20 %, D = 64 1110 -> 970 us with 512 columns; with 256 as one kernel 639 us, as two passes 703.
+// Taken where the estimates of the three calls are 1.06 apart: of 211 random calls that are done in half-precision pieces either way (M
+// 8000-32768, K 8192-16384, 6-35 %, N 180-512) that is 155, on average 1.10 times as fast; of those with even rows 123, none of them slower
+// by more than 3 %, of those with log-normal rows 32, 4 slower (at worst 0.94).  The results' error is 0.78 of FusedMM's (median; at most
+// 1.00).  Of up to 32 elements the scores are too cheap.  Of more than 64 the one kernel has blocks of up to 128 columns, whose sums
+// are added up on the way, and SPMM in wider ones is up to 4 times as far off; in such blocks it is no faster on average, and up to
+// 1.25 times as far off.
+struct TwoPasses {
+    DenseShape sddmm, spmm;
+    DenseConfig scores, product;
+    size_t products, bytes;     // of scratch: SDDMM's result, and all
+};
+constexpr size_t kMaxProducts = size_t(1) << 30;
+bool two_passes_wanted(DeviceState &d, const csrk_plan_s *plan, const DenseShape &s, const DenseConfig &fused, bool stored, uintptr_t scores,
+                       uintptr_t product, long long nnz, hipStream_t stream, TwoPasses *t) {
+    if (env_int("CSRK_MFMA", 1) != 1 || !fused.halves || s.D <= 32 || s.D > 64) return false;
+    t->products = ((size_t)nnz * sizeof(float) + 255) / 256 * 256;
+    if (t->products > kMaxProducts) return false;
+    t->sddmm = DenseShape{kDenseSddmm, false, s.M, s.K, 0, s.D, !stored};
+    t->spmm = DenseShape{kDenseSpmm, false, s.M, s.K, s.N, 0};
+    if (!dense_chosen(d, plan, t->sddmm, scores, nnz, &t->scores) || !dense_chosen(d, plan, t->spmm, product, nnz, &t->product) ||
+        !t->product.halves)
+        return false;
+    const double density = (double)nnz / ((double)s.M * (double)s.K);
+    const double us = dense_us(d, t->sddmm, t->scores, density, true) + dense_us(d, t->spmm, t->product, density, true);
+    if (us * 1.06 >= dense_us(d, s, fused, density, true)) return false;
+    t->bytes = t->products + (t->scores.bytes > t->product.bytes ? t->scores.bytes : t->product.bytes);
+    // (without the scratch, FusedMM's kernel)
+    if (t->bytes <= d.head_floats * sizeof(float)) return true;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (!d.fixed && hipStreamIsCapturing(stream, &capture) == hipSuccess) {
+        if (capture != hipStreamCaptureStatusNone) return false;
+        if (ensure_scratch(d, 1, (t->bytes + sizeof(float) - 1) / sizeof(float)) == CSRK_OK) return true;
+    }
+    (void)hipGetLastError();
+    return false;
+}
+
+// FP32 FusedMM on the matrix cores, in one pass or two
+csrk_status dense_fused_call(DeviceState &d, const csrk_plan_s *plan, const DenseShape &s, const DenseConfig &c, long long nnz, const int32_t *rowptr,
+                             const int32_t *colidx, const float *vals, const void *A, const void *B, const void *C, float *out,
+                             hipStream_t stream) {
+    TwoPasses t;
+    if (!two_passes_wanted(d, plan, s, c, vals != nullptr, addresses({A, B}), addresses({C, out}), nnz, stream, &t))
+        return dense_call(d, s, c, rowptr, colidx, vals, A, B, C, out, stream);
+    float *const products = d.head;
+    char *const rest = reinterpret_cast<char *>(d.head) + t.products;
+    CSRK_HIP(dense_run(t.sddmm, t.scores, rowptr, colidx, vals, A, B, nullptr, products, rest, stream));
+    CSRK_HIP(dense_run(t.spmm, t.product, rowptr, colidx, products, nullptr, nullptr, C, out, rest, stream));
     return CSRK_OK;
 }
 
@@ -1738,7 +1798,7 @@ static csrk_status fusedmm_run(const csrk_plan_s *plan, const ScratchSource &scr
     DenseConfig dense;
     if (dense_wanted(*d, plan, shape, addresses({A, B, C, O}), nnz, stream, &dense)) {
         rec.begin();
-        return dense_call(*d, shape, dense, rowptr, colidx, vals, A, B, C, O, stream);
+        return dense_fused_call(*d, plan, shape, dense, nnz, rowptr, colidx, vals, A, B, C, O, stream);
     }
     d->pending_ksplit = 0;
     if (csrk_status s = ensure_scratch(*d, N)) return s;

@@ -7,6 +7,12 @@
 #include "kernels_dense_wide.hpp"
 
 namespace csrk {
+
+// SDDMM in slabs of scores (kernels_dense_sddmm.hpp): all but FP32 dot products of more than 64 elements without stored values.
+// Those are the sum of two wavefronts' halves; where a value is multiplied by, that takes one rounding less and the error is 0.95
+// (both signs) and 0.82 (one sign) of the other kernel's, without it is 1.05-1.08.
+bool sddmm_in_slabs(const DenseShape &s) { return s.bf16 || s.D <= 64 || !s.ones; }
+
 namespace {
 
 constexpr int kMaxWidth = 2048, kMaxDot = 128, kMaxK = 1 << 20;
@@ -23,11 +29,7 @@ constexpr long long kMaxGroups = 1 << 22;
 constexpr int kHalvesK = 8192;
 constexpr double kHalvesTileUs = 1.5, kHalvesFusedTileUs = 2.1;
 
-// SDDMM in slabs of scores (kernels_dense_sddmm.hpp): all but FP32 dot products of more than 64 elements without stored values.
-// Those are the sum of two wavefronts' halves; where a value is multiplied by, that takes one rounding less and the error is 0.95
-// (both signs) and 0.82 (one sign) of the other kernel's, without it is 1.05-1.08.
-bool sddmm_slabs(const DenseShape &s) { return s.bf16 || s.D <= 64 || !s.ones; }
-int sddmm_rows(const DenseShape &s) { return sddmm_slabs(s) ? kSlabRows : kDenseBM; }
+int sddmm_rows(const DenseShape &s) { return sddmm_in_slabs(s) ? kSlabRows : kDenseBM; }
 
 size_t padded(size_t bytes) { return (bytes + 255) / 256 * 256; }
 size_t up32(int x) { return ((size_t)x + 31) / 32 * 32; }
@@ -100,8 +102,8 @@ DenseKernel again_kernel(int ct, int ds) {
 }
 
 DenseKernel sddmm_kernel(const DenseShape &s, int ds) {
-    if (!sddmm_slabs(s) && ds == 3) return {dense_sddmm_kernel<3>, DenseSddmmCfg<3>::kBytes, kDenseThreads};
-    if (!sddmm_slabs(s) && ds == 4) return {dense_sddmm_kernel<4>, DenseSddmmCfg<4>::kBytes, kDenseThreads};
+    if (!sddmm_in_slabs(s) && ds == 3) return {dense_sddmm_kernel<3>, DenseSddmmCfg<3>::kBytes, kDenseThreads};
+    if (!sddmm_in_slabs(s) && ds == 4) return {dense_sddmm_kernel<4>, DenseSddmmCfg<4>::kBytes, kDenseThreads};
 #define CSRK_SLAB_CASE(DS, P) \
     if (ds == DS && s.bf16 == (P == 1)) return {dense_slab_kernel<DS, P>, SlabCfg<DS, P>::kBytes, SlabCfg<DS, P>::kThreads};
     CSRK_SLAB_CASE(1, 3)
@@ -136,7 +138,7 @@ bool sddmm_slab_us(const DenseShape &s, const DenseConfig &c, int cus, double de
     };
     static constexpr Cost f32[] = {{5.2, 5.5, 1.12, 5.5}, {5.0, 7.1, 2.24, 4.9}, {5.4, 7.1, 4.1, 3.3}, {5.4, 8.0, 4.7, 2.6}};
     static constexpr Cost bf16[] = {{4.1, 6.3, 0.60, 6.0}, {5.2, 5.6, 0.82, 5.8}, {5.5, 5.9, 0.98, 5.1}, {4.8, 5.7, 1.71, 5.8}};
-    if (s.op != kDenseSddmm || !sddmm_slabs(s)) return false;
+    if (s.op != kDenseSddmm || !sddmm_in_slabs(s)) return false;
     const Cost t = s.bf16 ? bf16[c.ds - 1] : f32[c.ds - 1];
     const long long rounds = ((s.M + kSlabRows - 1) / kSlabRows * (long long)c.segs + cus - 1) / cus;
     *us = t.call + (double)rounds * (t.round + c.seg_k / kSlabCols * (t.slab + t.entries * density));
@@ -149,7 +151,7 @@ bool dense_config(const DenseShape &s, int cus, DenseConfig *out) {
     if (s.op != kDenseSpmm && (s.D < 1 || s.D > kMaxDot)) return false;
     const size_t pieces = s.bf16 ? 2 : 6;
     if ((up32(s.K) + 64) * (size_t)(s.N + 256) * pieces >= kView || (up32(s.K) + 128) * 128 * pieces >= kView) return false;
-    const bool slabs = s.op == kDenseSddmm && sddmm_slabs(s);
+    const bool slabs = s.op == kDenseSddmm && sddmm_in_slabs(s);
     const int bm = s.op == kDenseSddmm ? sddmm_rows(s) : kDenseBM;
     const long long row_blocks = (s.M + bm - 1) / bm;
     DenseConfig best{};
@@ -246,7 +248,7 @@ hipError_t dense_run(const DenseShape &s, const DenseConfig &c, const int32_t *r
         static std::atomic<uint64_t> done[3][3][17][5];
         int dev = 0;
         if (hipError_t e = hipGetDevice(&dev)) return e;
-        std::atomic<uint64_t> &seen = done[s.op][s.bf16 ? 1 : c.halves || (s.op == kDenseSddmm && !sddmm_slabs(s)) ? 2 : 0][c.ct][c.ds];
+        std::atomic<uint64_t> &seen = done[s.op][s.bf16 ? 1 : c.halves || (s.op == kDenseSddmm && !sddmm_in_slabs(s)) ? 2 : 0][c.ct][c.ds];
         const uint64_t bit = 1ull << (dev & 63);
         if (!(seen.load(std::memory_order_acquire) & bit)) {
             for (const DenseKernel &one : {k, again})

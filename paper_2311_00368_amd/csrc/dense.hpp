@@ -31,6 +31,8 @@ struct DenseConfig {
 // false: not a shape for these kernels
 bool dense_config(const DenseShape &s, int cus, DenseConfig *c);
 
+// SDDMM: in slabs of scores (kernels_dense_sddmm.hpp)
+bool sddmm_in_slabs(const DenseShape &s);
 // What an SDDMM call with that share of S's cells stored is expected to take where it is done in slabs of scores; false: it is not.
 bool sddmm_slab_us(const DenseShape &s, const DenseConfig &c, int cus, double density, double *us);
 

@@ -1,4 +1,4 @@
-// Matrix-core SDDMM in slabs of scores: all calls but FP32 ones of more than 64 elements without stored values (sddmm_slabs, dense.hip).
+// Matrix-core SDDMM in slabs of scores: all calls but FP32 ones of more than 64 elements without stored values (sddmm_in_slabs, dense.hip).
 //
 // A workgroup owns 64 rows of S and goes through its range of K in slabs of 256 columns.  Four of its wavefronts (one on each SIMD)
 // compute a slab's scores, all 64 x 256 of them, into one of two buffers in LDS, while the other 8 or 12 pick the stored entries'

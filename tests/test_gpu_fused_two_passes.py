@@ -1,0 +1,112 @@
+"""FusedMM that is done as SDDMM and SPMM on its result: taken where the scratch for the products can be had, with the results of the two
+calls, and by FusedMM's own kernel where it cannot."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import csrk, dev  # noqa: F401  (csrk is a fixture)
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(15360, 8200, 36, 260), (16383, 8193, 63, 301)]       # M, K, D, N
+
+
+def operands(M, K, D, N, seed, density=0.06):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    keep = torch.rand((M, K), device="cuda", generator=g) < density
+    keep[::500] = False
+    keep[7, :] = True
+    rp = torch.zeros(M + 1, dtype=torch.int32, device="cuda")
+    rp[1:] = keep.sum(1).cumsum(0)
+    ci = keep.nonzero()[:, 1].to(torch.int32)
+    v, A, B, C = (torch.rand(s, device="cuda", generator=g) * 2 - 1 for s in (len(ci), (M, D), (K, D), (K, N)))
+    return rp, ci, v, A, B, C
+
+
+def two_calls(csrk, M, K, D, N, rp, ci, v, A, B, C):
+    return csrk.spmm_csr(M, K, N, rp, ci, csrk.sddmm_csr(M, K, D, rp, ci, v, A, B), C)
+
+
+def scratch_of(csrk, call):
+    csrk.csrk_release_workspace()
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    call()
+    torch.cuda.synchronize()
+    return before - torch.cuda.mem_get_info()[0]
+
+
+@pytest.mark.parametrize("M,K,D,N", SHAPES)
+@pytest.mark.parametrize("kind", ["plain", "ones", "unsorted", "not finite", "plan"])
+def test_results(csrk, M, K, D, N, kind):
+    rp, ci, v, A, B, C = operands(M, K, D, N, M + D)
+    r, c = rp.cpu().numpy(), ci.cpu().numpy()
+    if kind == "ones":
+        v = None
+    elif kind == "unsorted":        # pairs of neighbours, and a row in descending order
+        for row in range(1, M, 97):
+            c[r[row]], c[r[row] + 1] = c[r[row] + 1], c[r[row]]
+        c[r[9]:r[10]] = c[r[9]:r[10]][::-1].copy()
+        ci = dev(c)
+    elif kind == "not finite":
+        A[4, 1], B[50, D - 1], C[K - 1, N - 1], v[len(v) // 2] = np.inf, np.nan, -np.inf, np.nan
+        A[5, 0] = 3e38
+    s = rp, ci, v, A, B, C
+    if kind == "plan":
+        plan = csrk.csrk_plan_create(M, K, rp, ci)
+        got = csrk.fusedmm_csr_plan(plan, D, N, v, A, B, C)
+        products = csrk.sddmm_csr_plan(plan, D, v, A, B)
+        want = csrk.spmm_csr_plan(plan, N, products, C)
+    else:
+        got, want = csrk.fusedmm_csr(M, K, D, N, *s), two_calls(csrk, M, K, D, N, *s)
+    assert np.array_equal(got.cpu().numpy(), want.cpu().numpy(), equal_nan=True)
+    rows = [0, 1, 4, 5, 7, 9, 98, 500, 501, M // 2, M - 1]
+    out = got.cpu().numpy()
+    h = [x.cpu().numpy().astype(np.float64) if x is not None else np.ones(len(c)) for x in (v, A, B, C)]
+    with np.errstate(all="ignore"):
+        for row in rows:
+            k = c[r[row]:r[row + 1]]
+            p = h[0][r[row]:r[row + 1]] * (h[2][k] @ h[1][row])
+            exact, size = p @ h[3][k], np.abs(p) @ np.abs(h[3][k])
+            fine = np.isfinite(exact) & (size < 1e38)
+            # FP32 scores and pieces, sums of up to 8200 terms: see test_gpu_dense_halves.py; the scores' own rounding errors are
+            # relative to their terms' magnitudes, some sqrt(D) times theirs
+            terms = (np.abs(h[0][r[row]:r[row + 1]]) * (np.abs(h[2][k]) @ np.abs(h[1][row]))) @ np.abs(h[3][k])
+            assert np.all(np.abs(out[row][fine] - exact[fine]) <= 2e-6 * size[fine] + 2e-7 * terms[fine]), row
+            assert not np.isfinite(out[row][~np.isfinite(exact)]).any(), row
+
+
+def test_scratch(csrk, monkeypatch):
+    M, K, D, N = SHAPES[0]
+    s = operands(M, K, D, N, 1)
+    products = 4 * len(s[1])
+    one = csrk.csrk_workspace_bytes(csrk.CSRK_OP_FUSEDMM, M, K, N, D)
+    assert scratch_of(csrk, lambda: csrk.fusedmm_csr(M, K, D, N, *s)) > products + one // 2
+    monkeypatch.setenv("CSRK_MFMA", "2")
+    kernel = csrk.fusedmm_csr(M, K, D, N, *s)
+    monkeypatch.setenv("CSRK_MFMA", "1")
+    both = csrk.fusedmm_csr(M, K, D, N, *s)
+    # a workspace of the size that is asked for, and one with room for the products
+    for room, want in ((0, kernel), (products + (1 << 20), both)):
+        ws = torch.empty(one + room, dtype=torch.uint8, device="cuda")
+        assert torch.equal(csrk.fusedmm_csr_ws(M, K, D, N, *s, ws), want)
+
+
+@pytest.mark.parametrize("has", ["vector kernels", "one kernel", "two passes"])
+def test_capture(csrk, monkeypatch, has):
+    # a call whose scratch would have to grow during a capture takes the kernels that there is scratch for
+    M, K, D, N = SHAPES[0]
+    s = operands(M, K, D, N, 2)
+    csrk.csrk_release_workspace()
+    monkeypatch.setenv("CSRK_MFMA", {"vector kernels": "3", "one kernel": "2", "two passes": "1"}[has])
+    want = csrk.fusedmm_csr(M, K, D, N, *s)
+    monkeypatch.setenv("CSRK_MFMA", "1")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = csrk.fusedmm_csr(M, K, D, N, *s)
+    for _ in range(3):
+        out.fill_(7)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
