@@ -1342,6 +1342,33 @@ Choice choose_fused(const DeviceState &d, const csrk_plan_s *plan, int M, int K,
     return Choice{};
 }
 
+// Which family does a call in the end (CSRK_FAMILY_*): what the row analysis (row_analysis in kernels_ktile.hpp) or the plan's facts
+// say to an attempt.  `even`, `nearly`: the longest row has at most 2 or 16 times the mean and 64 entries.
+int family_done(const DeviceState &d, DenseOp op, Choice ch, bool planned, int M, int K, long long nnz, bool even, bool nearly) {
+    const bool attempted = ch.gated;
+    if (ch.gated) {
+        const bool wide = ch.min_density >= kUnevenOk;
+        const double threshold = wide ? (double)(ch.min_density - kUnevenOk) : (double)ch.min_density;
+        const bool dense = (double)nnz >= threshold * (double)M * (double)K;
+        const bool suits = planned ? even : (even || (wide && nearly));
+        if (!(ch.min_density < 0.f || (dense && suits))) ch.family = kFamGeneral;
+    }
+    switch (ch.family) {
+        case kFamRows: return CSRK_FAMILY_ROWS;
+        case kFamNarrow:
+        case kFamNarrowSlabs: return CSRK_FAMILY_TILED_NARROW;
+        case kFamWide: return CSRK_FAMILY_TILED_WIDE;
+        case kFamSddmmTile:
+        case kFamSddmmPieces: return CSRK_FAMILY_TILED_SDDMM;
+        case kFamSchedule: return CSRK_FAMILY_SCHEDULE;
+        default: {
+            // the general kernels deal out whole rows where they know the rows to be even
+            const bool asked = planned || attempted || (op != kDenseSddmm && even_rows_worth_asking(d, M, K, op == kDenseFused));
+            return asked && even ? CSRK_FAMILY_GENERAL_ROWS : CSRK_FAMILY_GENERAL_SHARES;
+        }
+    }
+}
+
 // --- the matrix-core kernels (dense.hpp) ----------------------------------------------------------------------
 // They are asked first.  They work through every cell of S, so the stored entries have to be a large enough share of it,
 // and the host has to know how many there are: from a plan, or from the caller (`nnz`; -1: not known).
@@ -1369,6 +1396,46 @@ double vector_us(const DenseShape &s, long long nnz, bool wide) {
                          : s.D <= 32                       ? VectorCost{4.8, 0, 5.4, 0.16}
                          : s.D <= 64                       ? VectorCost{5.3, 0, 6.9, 0.46}
                                                            : VectorCost{5.4, 0, 14.3, 0.71};
+    return c.call + c.work * 1e-9 * (double)nnz * (s.N + s.D) + c.entries * 1e-6 * (double)nnz + c.cells * 1e-6 * (double)s.M * s.K;
+}
+
+// The same for FP32 SPMM and FusedMM by the family that does the call if its rows are even, which is most of what the estimate above
+// does not know: fitted by least squares of the relative error to 9100 calls of the same ranges, those of a family scatter by 4-25 %
+// around it (around the other by as much, and off by up to 2.3 times).  The matrix-core kernels are also taken where they are expected
+// to be the faster by 8 %: of 3632 other calls with even rows that changes 291, 274 of them become faster by more than 3 % and 2 slower
+// (at worst 0.89), and all of them on average 2.8 % faster; of 1250 with log-normal rows 74, 71 and 2 (0.92), 2.6 %.  (By 12 % 232, 224 and
+// none; by 5 % 349, 313 and 7.)  Planned calls have fewer launches and take them by 19 %, with even rows and not from the tiled
+// kernels (which a plan makes faster than this estimate: 13 of 20 faster, 6 slower): of 1779 that changes 48, 47 and 1, on average 1.5
+// times as fast.  0: not known (no such calls in the fit).
+// [SPMM, FusedMM of up to 64 elements, of more][equal shares, whole rows, whole-row kernels, tiled][N to 32, 128, 256, more]
+double family_us(const DeviceState &d, const csrk_plan_s *plan, const DenseShape &s, long long nnz) {
+    static constexpr VectorCost costs[3][4][4] = {
+        {{{11.6, 1.59, 5.21, 0}, {11, 144, 3.11, 0}, {10.5, 92.4, 19.7, 0.389}, {5.37, 272, 0, 0.978}},
+         {{10, 0, 5.49, 0.0428}, {10.7, 138, 3.04, 0.00749}, {11.2, 33, 28.4, 0.119}, {28, 31.8, 48.5, 0}},
+         {{4.11, 9.68, 4.98, 0.103}, {4.43, 138, 3.17, 0.0361}, {6.46, 16.1, 28.3, 0.0652}, {7.15, 14.5, 57.7, 0.113}},
+         {{14, 0, 2.82, 0.429}, {16.8, 78.9, 0, 0.496}, {20.1, 0, 13.5, 0.983}, {27.3, 7.86, 18.9, 1.84}}},
+        {{{11.5, 192, 0.55, 0.0155}, {8.99, 177, 2.75, 0.356}, {7.2, 183, 8.7, 0.288}, {0, 307, 11.8, 0.054}},
+         {{9.27, 131, 3.54, 0}, {13, 121, 5.99, 0}, {9.45, 76.9, 18.2, 0.554}, {0, 0, 0, 0}},
+         {{4.82, 117, 3.96, 0.193}, {6.4, 145, 0, 0.236}, {5.74, 34.1, 28.3, 0.407}, {6.12, 30.8, 54.4, 0.815}},
+         {{0, 0, 0, 0}, {20.5, 51.1, 2.83, 1.56}, {24.9, 8.74, 17.2, 1.92}, {31.6, 11.4, 21.8, 2.88}}},
+        {{{9.89, 128, 15.8, 0.03}, {6.59, 161, 12.6, 0.567}, {2.03, 115, 35.1, 1.54}, {4.36, 266, 0, 3.54}},
+         {{11.6, 9.9, 26.2, 0.0396}, {12.2, 67.8, 21.6, 0.145}, {6.85, 61.8, 33, 1.02}, {29.2, 73.1, 34, 2.22}},
+         {{6.98, 1.38, 26.2, 0.0219}, {6.33, 65.2, 21.8, 0}, {7.05, 5.71, 48, 0.0242}, {8.73, 9.79, 75.2, 0.589}},
+         {{0, 0, 0, 0}, {22.5, 33.7, 4.7, 2.42}, {55.5, 0, 26.2, 4.12}, {79, 92.3, 0, 7.15}}}};
+    if (s.bf16 || s.op == kDenseSddmm) return 0;
+    const bool fused = s.op == kDenseFused;
+    const Choice ch = fused ? choose_fused(d, plan, s.M, s.K, s.D, s.N, true, true) : choose_spmm(d, plan, s.M, s.K, s.N, true);
+    int family;
+    switch (family_done(d, s.op, ch, plan != nullptr, s.M, s.K, nnz, !plan || plan->even, true)) {
+        case CSRK_FAMILY_GENERAL_SHARES: family = 0; break;
+        case CSRK_FAMILY_GENERAL_ROWS: family = 1; break;
+        case CSRK_FAMILY_ROWS: family = 2; break;
+        case CSRK_FAMILY_TILED_NARROW:
+        case CSRK_FAMILY_TILED_WIDE: family = 3; break;
+        default: return 0;
+    }
+    if (plan && (!plan->even || family == 3)) return 0;
+    const VectorCost c = costs[!fused ? 0 : s.D <= 64 ? 1 : 2][family][s.N <= 32 ? 0 : s.N <= 128 ? 1 : s.N <= 256 ? 2 : 3];
     return c.call + c.work * 1e-9 * (double)nnz * (s.N + s.D) + c.entries * 1e-6 * (double)nnz + c.cells * 1e-6 * (double)s.M * s.K;
 }
 
@@ -1403,9 +1470,12 @@ constexpr double kOutside = 0.15;
 struct RatioFit {
     double base, dense, vector;
 };
-bool dense_is_faster(const DenseShape &s, const DenseConfig &c, bool planned, double density, double vector) {
+// `us`, `vector`, `family`: the estimates of both sides, the vector kernels' also by family
+bool dense_is_faster(const DenseShape &s, const DenseConfig &c, bool planned, double density, double us, double vector, double family) {
     auto past = [](double x, double lo, double hi) { return std::log(x < lo ? lo / x : x > hi ? x / hi : 1.0); };
     const double outside = past(s.M, 512, 32768) + past(s.K, 512, 16384) + past(density, 0.055, 0.36) + past(s.N, 0, 512);
+    const double line = (planned ? 0.1 : 0.0) + kOutside * outside;
+    if (family > 0 && std::log(family / (us * 1.08)) > line) return true;
     RatioFit f;
     if (s.op == kDenseSpmm && !s.bf16 && s.N > 32)
         f = s.N <= 128 ? RatioFit{0.36, -0.69, 0.62} : s.N <= 256 ? RatioFit{0.55, -0.87, 0.77} : RatioFit{0.58, -0.95, 0.85};
@@ -1416,7 +1486,7 @@ bool dense_is_faster(const DenseShape &s, const DenseConfig &c, bool planned, do
     else
         return false;
     // (a plan is worth a tenth to the vector kernels where the rows are even)
-    return f.base + f.dense * std::log(c.us) + f.vector * std::log(vector) > (planned ? 0.1 : 0.0) + kOutside * outside;
+    return f.base + f.dense * std::log(c.us) + f.vector * std::log(vector) > line;
 }
 
 uintptr_t addresses(std::initializer_list<const void *> pointers) {
@@ -1448,9 +1518,10 @@ bool dense_chosen(const DeviceState &d, const csrk_plan_s *plan, const DenseShap
     if (d.fixed && c->bytes > d.head_floats * sizeof(float)) return false;
     if (mode == 2) return true;
     const double density = (double)nnz / ((double)s.M * (double)s.K);
-    if (!(s.op == kDenseSddmm && sddmm_in_slabs(s)) && wide && dense_is_faster(s, *c, plan != nullptr, density, vector)) return true;
+    const bool slabs = s.op == kDenseSddmm && sddmm_in_slabs(s);
     const double us = dense_us(d, s, *c, density, wide);
-    return us * (s.op == kDenseSddmm && sddmm_in_slabs(s) && s.D > 64 ? 1.0 : 1.1) < vector;
+    if (us * (slabs && s.D > 64 ? 1.0 : 1.1) < vector) return true;
+    return !slabs && wide && dense_is_faster(s, *c, plan != nullptr, density, us, vector, family_us(d, plan, s, nnz));
 }
 
 // The vector kernels need far less scratch, so a call that cannot have what the matrix-core kernels need is theirs: one
@@ -1551,39 +1622,16 @@ csrk_status csrk_explain_choice(int op, int cus, int M, int K, int N, int D, lon
     facts.has_sched = !even && M >= 256 && K >= 2 * kSchedMinSegment && nnz > 0;     // as csrk_plan_create decides
     const csrk_plan_s *plan = planned ? &facts : nullptr;
     Choice ch;
-    bool fused = false;
     switch (op) {
         case CSRK_OP_SPMM: ch = choose_spmm(d, plan, M, K, N, N % 4 == 0); break;
         case CSRK_OP_SDDMM: ch = choose_sddmm(d, plan, M, K, D, D % 4 == 0 && D > 0, false); break;
         case CSRK_OP_FUSEDMM:
             ch = choose_fused(d, plan, M, K, D, N, N % 4 == 0, D % 4 == 0 && D > 0);
-            fused = true;
             break;
         default: return fail(CSRK_INVALID_ARG, "csrk_explain_choice: unknown operation %d", op);
     }
-    bool attempted = false;
-    if (ch.gated) {     // what the row analysis (row_analysis in kernels_ktile.hpp) or the plan's facts would say
-        attempted = true;
-        const bool wide = ch.min_density >= kUnevenOk;
-        const double threshold = wide ? (double)(ch.min_density - kUnevenOk) : (double)ch.min_density;
-        const bool dense = (double)nnz >= threshold * (double)M * (double)K;
-        const bool suits = planned ? even : (even || (wide && (double)longest_row <= 16.0 * mean + 64.0));
-        if (!(ch.min_density < 0.f || (dense && suits))) ch.family = kFamGeneral;
-    }
-    switch (ch.family) {
-        case kFamRows: *family = CSRK_FAMILY_ROWS; break;
-        case kFamNarrow:
-        case kFamNarrowSlabs: *family = CSRK_FAMILY_TILED_NARROW; break;
-        case kFamWide: *family = CSRK_FAMILY_TILED_WIDE; break;
-        case kFamSddmmTile:
-        case kFamSddmmPieces: *family = CSRK_FAMILY_TILED_SDDMM; break;
-        case kFamSchedule: *family = CSRK_FAMILY_SCHEDULE; break;
-        default: {
-            // the general kernels deal out whole rows where they know the rows to be even
-            const bool asked = planned || attempted || (op != CSRK_OP_SDDMM && even_rows_worth_asking(d, M, K, fused));
-            *family = asked && even ? CSRK_FAMILY_GENERAL_ROWS : CSRK_FAMILY_GENERAL_SHARES;
-        }
-    }
+    *family = family_done(d, op == CSRK_OP_FUSEDMM ? kDenseFused : op == CSRK_OP_SPMM ? kDenseSpmm : kDenseSddmm, ch, planned != 0, M, K, nnz, even,
+                          (double)longest_row <= 16.0 * mean + 64.0);
     return CSRK_OK;
 }
 
