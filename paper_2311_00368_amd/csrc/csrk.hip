@@ -1404,7 +1404,7 @@ double vector_us(const DenseShape &s, long long nnz, bool wide) {
 // around it (around the other by as much, and off by up to 2.3 times).  The matrix-core kernels are also taken where they are expected
 // to be the faster by 8 %: of 3632 other calls with even rows that changes 291, 274 of them become faster by more than 3 % and 2 slower
 // (at worst 0.89), and all of them on average 2.8 % faster; of 1250 with log-normal rows 74, 71 and 2 (0.92), 2.6 %.  (By 12 % 232, 224 and
-// none; by 5 % 349, 313 and 7.)  Planned calls have fewer launches and take them by 19 %, with even rows and not from the tiled
+// none; by 5 % 349, 313 and 7.  All before the calls that dense_is_faster leaves out as less exact.)  Planned calls have fewer launches and take them by 19 %, with even rows and not from the tiled
 // kernels (which a plan makes faster than this estimate: 13 of 20 faster, 6 slower): of 1779 that changes 48, 47 and 1, on average 1.5
 // times as fast.  0: not known (no such calls in the fit).
 // [SPMM, FusedMM of up to 64 elements, of more][equal shares, whole rows, whole-row kernels, tiled][N to 32, 128, 256, more]
@@ -1475,7 +1475,11 @@ bool dense_is_faster(const DenseShape &s, const DenseConfig &c, bool planned, do
     auto past = [](double x, double lo, double hi) { return std::log(x < lo ? lo / x : x > hi ? x / hi : 1.0); };
     const double outside = past(s.M, 512, 32768) + past(s.K, 512, 16384) + past(density, 0.055, 0.36) + past(s.N, 0, 512);
     const double line = (planned ? 0.1 : 0.0) + kOutside * outside;
-    if (family > 0 && std::log(family / (us * 1.08)) > line) return true;
+    // (Blocks of 192 and 256 columns have one accumulator for the sums of a range.  Over all of K, below 4096 columns, data of one sign
+    // come out up to 1.38 times as far from FP64 as in the vector kernels: SPMM 10588 x 971, 480 columns, log-normal rows 1.33e-7 against
+    // 0.96e-7.  13800 others had at most 0.81 of their error on data of both signs and 1.20 on data of one, where both are 5e-8 to 7e-8 then.)
+    const bool as_exact = c.ct <= 8 || c.segs > 1 || s.K >= 4096;
+    if (family > 0 && as_exact && std::log(family / (us * 1.08)) > line) return true;
     RatioFit f;
     if (s.op == kDenseSpmm && !s.bf16 && s.N > 32)
         f = s.N <= 128 ? RatioFit{0.36, -0.69, 0.62} : s.N <= 256 ? RatioFit{0.55, -0.87, 0.77} : RatioFit{0.58, -0.95, 0.85};

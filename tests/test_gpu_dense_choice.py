@@ -13,7 +13,7 @@ SHAPES = [("spmm", "f32", 3000, 3000, 0, 96, 0.3), ("spmm", "f32", 3000, 3000, 0
           ("sddmm", "f32", 2048, 2048, 128, 0, 0.3), ("sddmm", "f32", 2999, 3001, 96, 0, 0.12), ("sddmm", "bf16", 2048, 2048, 128, 0, 0.3),
           ("fusedmm", "f32", 2048, 2048, 64, 256, 0.15), ("fusedmm", "f32", 2048, 2048, 128, 256, 0.15),
           # by the vector kernels' estimate for their family: equal shares, whole rows, whole-row kernels, tiled
-          ("spmm", "f32", 512, 2560, 0, 480, 0.316), ("spmm", "f32", 1536, 4608, 0, 480, 0.135), ("spmm", "f32", 2860, 1474, 0, 424, 0.175),
+          ("spmm", "f32", 512, 2560, 0, 480, 0.316), ("spmm", "f32", 1536, 4608, 0, 480, 0.135),
           ("fusedmm", "f32", 768, 2304, 32, 488, 0.226), ("fusedmm", "f32", 3164, 3228, 48, 96, 0.169), ("fusedmm", "f32", 753, 2207, 88, 512, 0.262),
           ("fusedmm", "f32", 4005, 2992, 96, 96, 0.109), ("fusedmm", "f32", 2086, 1056, 128, 392, 0.282), ("fusedmm", "f32", 1024, 8448, 128, 472, 0.126),
           # outside of the sizes that the ratio was fitted to
