@@ -85,3 +85,38 @@ def test_rows_that_stay_behind(csrk, monkeypatch, what, D, bf16):
     rows = np.repeat(np.arange(M), np.diff(rp))
     clean = fine & np.isfinite(A).all(1)[rows] & np.isfinite(B).all(1)[ci]
     check(x[clean], want[clean], terms[clean], "sddmm " + what)
+
+
+@pytest.mark.parametrize("D", [65, 72, 96, 97, 128])
+@pytest.mark.parametrize("mode", ["2", "3"])
+def test_values_beside_halves_of_opposite_signs(csrk, monkeypatch, D, mode):
+    # FP32 dot products of more than 64 elements are the sum of two halves (elements up to 64, the others): a stored value that is infinite,
+    # or so large that it takes one half out of the range of floats, multiplies the sum.  Some halves are zero.
+    monkeypatch.setenv("CSRK_MFMA", mode)
+    M, K = 150, 1100
+    rng = np.random.default_rng(D)
+    rp, ci = rows_of_lengths(rng, K, rng.integers(0, 500, M))
+    A, B = rng.uniform(0.5, 1, (M, D)).astype(np.float32), rng.uniform(0.5, 1, (K, D)).astype(np.float32)
+    B[:, 64:] *= -rng.uniform(0.7, 0.95, (K, 1)) * 64 / (D - 64)
+    B[::2] *= -1
+    B[::7, :64] = 0
+    B[1::7, 64:] = 0
+    v = rng.choice(np.array([1e37, -1e37, 1e38, -1e38, 3e38, np.inf, -np.inf, np.nan, 1, -0.25, 1e-3, 0.5], np.float32), len(ci))
+    v[rp[20]:rp[90]] = rng.uniform(-1, 1, rp[90] - rp[20])
+    P = dev(v)
+    args = M, K, D, dev(rp), dev(ci)
+    got = [csrk.sddmm_csr(*args, dev(v), dev(A), dev(B)).cpu().numpy(), csrk.sddmm_csr(*args, P, dev(A), dev(B), P).cpu().numpy()]
+    score, terms = oracle.sddmm(M, K, D, rp, ci, np.ones_like(v), A, B)
+    v = v.astype(np.float64)
+    with np.errstate(all="ignore"):
+        want = score * v
+    largest = float(np.finfo(np.float32).max)
+    # (near the largest float whether there is an infinity, and near a score of zero which, is a matter of rounding)
+    sure = np.isnan(v) | np.isinf(v) | (np.abs(np.abs(want) - largest) > 1e-5 * terms * np.abs(v))
+    sure &= np.abs(score) > 1e-3 * terms
+    assert sure.mean() > 0.95
+    want[np.abs(want) > largest] = np.copysign(np.inf, want[np.abs(want) > largest])
+    for x in got:
+        fine = sure & np.isfinite(want)
+        np.testing.assert_array_equal(x[sure & ~fine], want[sure & ~fine])
+        check(x[fine], want[fine], (terms * np.abs(v))[fine], "sddmm")
