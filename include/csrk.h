@@ -39,7 +39,10 @@
  *    B and C (2 for bfloat16), lengths rounded up to 32, partial outputs likewise, and
  *    2 bytes for each row, range and block of up to 256 columns; for FP32 outputs of more
  *    than 128 columns over long rows also 640 bytes per column of the output and 4 per row
- *    and column of S.  Three ways to provide it:
+ *    and column of S.  FP32 FusedMM with dot products of 33-64 elements and wide outputs over
+ *    long rows writes its products where it is faster that way and their room, 4 bytes per
+ *    stored entry up to 1 GiB, can be had and is known to be enough (planned calls,
+ *    csrk_call_bounded); csrk_workspace_bytes does not count them.  Three ways to provide it:
  *      * spmm_csr / sddmm_csr / fusedmm_csr (and their planned and bfloat16 forms) use
  *        an area the library keeps per device.  It is allocated (hipMalloc, which
  *        synchronises) the first time it is needed, replaced when it has to grow (after
@@ -205,11 +208,19 @@ csrk_status fusedmm_csr_ws(int M, int K, int D, int N,
  * density of S on the device only, and launch kernels that stand by for it; with nnz known the choice is made here, and
  * the matrix-core kernels (S nearly dense enough to be treated as a dense matrix: see csrc/kernels_dense.hpp) can be part
  * of it, as in planned calls.  nnz decides about speed only: a wrong one gives the same results to rounding.
+ *
+ * csrk_call_bounded: the same by a caller who vouches that S stores at most nnz entries, rowptr[M] <= nnz, as one does who
+ * passes the length of the array colidx.  Scratch may then be given out by nnz, which lets FusedMM keep the products of its SDDMM in
+ * device memory where that is faster (see "Scratch" above); a larger rowptr[M] is undefined behaviour here.
  */
 csrk_status csrk_call(int op, int bf16, long long nnz, int M, int K, int D, int N,
                       const int32_t *rowptr, const int32_t *colidx, const float *vals,
                       const void *A, const void *B, const void *C, float *out,
                       void *workspace, size_t workspace_bytes, hipStream_t stream);
+csrk_status csrk_call_bounded(int op, int bf16, long long nnz, int M, int K, int D, int N,
+                              const int32_t *rowptr, const int32_t *colidx, const float *vals,
+                              const void *A, const void *B, const void *C, float *out,
+                              void *workspace, size_t workspace_bytes, hipStream_t stream);
 
 /*
  * Which kernel family a call would take (the paper chooses NT and nchunks from the

@@ -82,6 +82,7 @@ def load(build_if_missing: bool = True):
     lib.sddmm_csr_ws.argtypes = [i, i, i, p, p, p, p, p, p, p, sz, p]
     lib.fusedmm_csr_ws.argtypes = [i, i, i, i, p, p, p, p, p, p, p, p, sz, p]
     lib.csrk_call.argtypes = [i, i, ctypes.c_longlong, i, i, i, i, p, p, p, p, p, p, p, p, sz, p]
+    lib.csrk_call_bounded.argtypes = lib.csrk_call.argtypes
     lib.csrk_plan_reserve.argtypes = [p, i]
     lib.fusedmm_csr_static.argtypes = [i, i, i, i, p, p, p, p, p, p, p, p]
     lib.csrk_tile_phases.argtypes = [i, i, i, i, i, p, p, p, p, p, p, p, p, ctypes.POINTER(ctypes.c_double),
@@ -97,7 +98,8 @@ def load(build_if_missing: bool = True):
               lib.csrk_plan_info, lib.spmm_csr_plan, lib.sddmm_csr_plan, lib.fusedmm_csr_plan,
               lib.csrk_profile_enable, lib.csrk_profile_collect, lib.csrk_workspace_bytes, lib.spmm_csr_ws,
               lib.sddmm_csr_ws, lib.fusedmm_csr_ws, lib.csrk_plan_reserve, lib.csrk_tile_phases,
-              lib.csrk_debug_row_rotation, lib.fusedmm_csr_static, lib.csrk_microbench, lib.csrk_call, lib.csrk_matrix_core_form):
+              lib.csrk_debug_row_rotation, lib.fusedmm_csr_static, lib.csrk_microbench, lib.csrk_call, lib.csrk_call_bounded,
+              lib.csrk_matrix_core_form):
         f.restype = ctypes.c_int
     lib.csrk_last_error.restype = ctypes.c_char_p
     lib.csrk_version.restype = ctypes.c_char_p
@@ -171,6 +173,10 @@ def csrk_call(op: int, M: int, K: int, D: int, N: int, rowptr, colidx, vals, A, 
     return fns[2 if bf16 else 0](*args)
 
 
+# (S stores at most as many entries as the tensor colidx has elements: the calls vouch for that)
+csrk_call_bounded = csrk_call
+
+
 def spmm_csr(M: int, K: int, N: int, rowptr, colidx, vals, B, O=None) -> torch.Tensor:
     """O = S.B on the current stream; returns O (allocated M x N if not given)."""
     out = _call(CSRK_OP_SPMM, 0, M, K, 0, N, rowptr, colidx, vals, None, None, B, O, None)
@@ -215,7 +221,7 @@ def fusedmm_csr(M: int, K: int, D: int, N: int, rowptr, colidx, vals, A, B, C, O
     if O is None:
         O = torch.empty((M, N), dtype=torch.float32, device=dev)
     with torch.cuda.device(dev):
-        _check(lib.csrk_call(CSRK_OP_FUSEDMM, 0, nnz, M, K, D, N, rp, ci, va,
+        _check(lib.csrk_call_bounded(CSRK_OP_FUSEDMM, 0, nnz, M, K, D, N, rp, ci, va,
                               _dev_ptr(A, "A", torch.float32, (M, D), dev),
                               _dev_ptr(B, "B", torch.float32, (K, D), dev),
                               _dev_ptr(C, "C", torch.float32, (K, N), dev),
@@ -305,7 +311,7 @@ def fusedmm_csr_ws(M: int, K: int, D: int, N: int, rowptr, colidx, vals, A, B, C
         O = torch.empty((M, N), dtype=torch.float32, device=dev)
     ws, ws_bytes = _ws_ptr(workspace, dev)
     with torch.cuda.device(dev):
-        _check(lib.csrk_call(CSRK_OP_FUSEDMM, 0, nnz, M, K, D, N, rp, ci, va,
+        _check(lib.csrk_call_bounded(CSRK_OP_FUSEDMM, 0, nnz, M, K, D, N, rp, ci, va,
                               _dev_ptr(A, "A", torch.float32, (M, D), dev),
                               _dev_ptr(B, "B", torch.float32, (K, D), dev),
                               _dev_ptr(C, "C", torch.float32, (K, N), dev),

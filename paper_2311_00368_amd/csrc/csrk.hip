@@ -1592,11 +1592,12 @@ bool two_passes_wanted(DeviceState &d, const csrk_plan_s *plan, const DenseShape
 }
 
 // FP32 FusedMM on the matrix cores, in one pass or two
-csrk_status dense_fused_call(DeviceState &d, const csrk_plan_s *plan, const DenseShape &s, const DenseConfig &c, long long nnz, const int32_t *rowptr,
-                             const int32_t *colidx, const float *vals, const void *A, const void *B, const void *C, float *out,
+csrk_status dense_fused_call(DeviceState &d, const csrk_plan_s *plan, const DenseShape &s, const DenseConfig &c, long long nnz, bool bound,
+                             const int32_t *rowptr, const int32_t *colidx, const float *vals, const void *A, const void *B, const void *C, float *out,
                              hipStream_t stream) {
     TwoPasses t;
-    if (!two_passes_wanted(d, plan, s, c, vals != nullptr, addresses({A, B}), addresses({C, out}), nnz, stream, &t))
+    // (SDDMM writes rowptr[M] products into room for nnz)
+    if (!bound || !two_passes_wanted(d, plan, s, c, vals != nullptr, addresses({A, B}), addresses({C, out}), nnz, stream, &t))
         return dense_call(d, s, c, rowptr, colidx, vals, A, B, C, out, stream);
     float *const products = d.head;
     char *const rest = reinterpret_cast<char *>(d.head) + t.products;
@@ -1833,7 +1834,8 @@ static csrk_status sddmm_run(const csrk_plan_s *plan, const ScratchSource &scrat
     return CSRK_OK;
 }
 
-static csrk_status fusedmm_run(const csrk_plan_s *plan, const ScratchSource &scratch, long long nnz, int M, int K, int D, int N,
+// `bound`: S has at most nnz entries (otherwise nnz is only what the caller expects)
+static csrk_status fusedmm_run(const csrk_plan_s *plan, const ScratchSource &scratch, long long nnz, bool bound, int M, int K, int D, int N,
                                const int32_t *rowptr, const int32_t *colidx, const float *vals, const float *A,
                                const float *B, const float *C, float *O, hipStream_t stream) {
     if (csrk_status s = check_dims("fusedmm_csr", M, K, D, N)) return s;
@@ -1850,7 +1852,7 @@ static csrk_status fusedmm_run(const csrk_plan_s *plan, const ScratchSource &scr
     DenseConfig dense;
     if (dense_wanted(*d, plan, shape, addresses({A, B, C, O}), nnz, stream, &dense)) {
         rec.begin();
-        return dense_fused_call(*d, plan, shape, dense, nnz, rowptr, colidx, vals, A, B, C, O, stream);
+        return dense_fused_call(*d, plan, shape, dense, nnz, bound, rowptr, colidx, vals, A, B, C, O, stream);
     }
     d->pending_ksplit = 0;
     if (csrk_status s = ensure_scratch(*d, N)) return s;
@@ -1962,7 +1964,7 @@ csrk_status sddmm_csr(int M, int K, int D, const int32_t *rowptr, const int32_t 
 
 csrk_status fusedmm_csr(int M, int K, int D, int N, const int32_t *rowptr, const int32_t *colidx, const float *vals,
                         const float *A, const float *B, const float *C, float *O, hipStream_t stream) {
-    return fusedmm_run(nullptr, ScratchSource{}, -1, M, K, D, N, rowptr, colidx, vals, A, B, C, O, stream);
+    return fusedmm_run(nullptr, ScratchSource{}, -1, false, M, K, D, N, rowptr, colidx, vals, A, B, C, O, stream);
 }
 
 // --- the same calls on a workspace of the caller's: nothing allocated, nothing shared ------------------------
@@ -2045,7 +2047,7 @@ csrk_status fusedmm_csr_ws(int M, int K, int D, int N, const int32_t *rowptr, co
                            const float *A, const float *B, const float *C, float *O, void *workspace,
                            size_t workspace_bytes, hipStream_t stream) {
     if (!workspace) return fail(CSRK_INVALID_ARG, "fusedmm_csr_ws: workspace must not be NULL");
-    return fusedmm_run(nullptr, ScratchSource{workspace, workspace_bytes}, -1, M, K, D, N, rowptr, colidx, vals, A, B, C, O,
+    return fusedmm_run(nullptr, ScratchSource{workspace, workspace_bytes}, -1, false, M, K, D, N, rowptr, colidx, vals, A, B, C, O,
                        stream);
 }
 
@@ -2074,7 +2076,7 @@ csrk_status fusedmm_csr_static(int M, int K, int D, int N, const int32_t *rowptr
                     need, kStaticScratchBytes);
     void *ptr = nullptr;
     if (csrk_status s = static_scratch_ptr(&ptr)) return s;
-    return fusedmm_run(nullptr, ScratchSource{ptr, kStaticScratchBytes}, -1, M, K, D, N, rowptr, colidx, vals, A, B, C, O,
+    return fusedmm_run(nullptr, ScratchSource{ptr, kStaticScratchBytes}, -1, false, M, K, D, N, rowptr, colidx, vals, A, B, C, O,
                        stream);
 }
 
@@ -2241,8 +2243,8 @@ csrk_status sddmm_csr_plan(const csrk_plan *plan, int D, const float *vals, cons
 csrk_status fusedmm_csr_plan(const csrk_plan *plan, int D, int N, const float *vals, const float *A, const float *B,
                              const float *C, float *O, hipStream_t stream) {
     if (csrk_status s = plan_usable("fusedmm_csr_plan", plan)) return s;
-    return fusedmm_run(plan, plan_scratch(plan, CSRK_OP_FUSEDMM, N, D), plan->nnz, plan->M, plan->K, D, N, plan->rowptr, plan->colidx,
-                       vals, A, B, C, O, stream);
+    return fusedmm_run(plan, plan_scratch(plan, CSRK_OP_FUSEDMM, N, D), plan->nnz, true, plan->M, plan->K, D, N, plan->rowptr,
+                       plan->colidx, vals, A, B, C, O, stream);
 }
 
 static csrk_status spmm_bf16_run(long long nnz, int M, int K, int N, const int32_t *rowptr, const int32_t *colidx, const float *vals,
@@ -2433,13 +2435,13 @@ csrk_status fusedmm_csr_bf16(int M, int K, int D, int N, const int32_t *rowptr, 
     return fusedmm_bf16_run(-1, M, K, D, N, rowptr, colidx, vals, A, B, C, O, stream);
 }
 
-csrk_status csrk_call(int op, int bf16, long long nnz, int M, int K, int D, int N, const int32_t *rowptr, const int32_t *colidx,
-                      const float *vals, const void *A, const void *B, const void *C, float *out, void *workspace,
-                      size_t workspace_bytes, hipStream_t stream) {
+static csrk_status counted_call(const char *who, bool bound, int op, int bf16, long long nnz, int M, int K, int D, int N,
+                                const int32_t *rowptr, const int32_t *colidx, const float *vals, const void *A, const void *B,
+                                const void *C, float *out, void *workspace, size_t workspace_bytes, hipStream_t stream) {
     const ScratchSource scratch = workspace ? ScratchSource{workspace, workspace_bytes} : ScratchSource{};
     const auto f32 = [](const void *p) { return static_cast<const float *>(p); };
     const auto b16 = [](const void *p) { return static_cast<const uint16_t *>(p); };
-    if (bf16 && workspace) return fail(CSRK_INVALID_ARG, "csrk_call: bfloat16 calls take no workspace");
+    if (bf16 && workspace) return fail(CSRK_INVALID_ARG, "%s: bfloat16 calls take no workspace", who);
     switch (op) {
         case CSRK_OP_SPMM:
             return bf16 ? spmm_bf16_run(nnz, M, K, N, rowptr, colidx, vals, b16(C), out, stream)
@@ -2449,9 +2451,23 @@ csrk_status csrk_call(int op, int bf16, long long nnz, int M, int K, int D, int 
                         : sddmm_run(nullptr, scratch, nnz, M, K, D, rowptr, colidx, vals, f32(A), f32(B), out, stream);
         case CSRK_OP_FUSEDMM:
             return bf16 ? fusedmm_bf16_run(nnz, M, K, D, N, rowptr, colidx, vals, b16(A), b16(B), b16(C), out, stream)
-                        : fusedmm_run(nullptr, scratch, nnz, M, K, D, N, rowptr, colidx, vals, f32(A), f32(B), f32(C), out, stream);
-        default: return fail(CSRK_INVALID_ARG, "csrk_call: unknown operation %d", op);
+                        : fusedmm_run(nullptr, scratch, nnz, bound, M, K, D, N, rowptr, colidx, vals, f32(A), f32(B), f32(C), out, stream);
+        default: return fail(CSRK_INVALID_ARG, "%s: unknown operation %d", who, op);
     }
+}
+
+csrk_status csrk_call(int op, int bf16, long long nnz, int M, int K, int D, int N, const int32_t *rowptr, const int32_t *colidx,
+                      const float *vals, const void *A, const void *B, const void *C, float *out, void *workspace,
+                      size_t workspace_bytes, hipStream_t stream) {
+    return counted_call("csrk_call", false, op, bf16, nnz, M, K, D, N, rowptr, colidx, vals, A, B, C, out, workspace, workspace_bytes,
+                        stream);
+}
+
+csrk_status csrk_call_bounded(int op, int bf16, long long nnz, int M, int K, int D, int N, const int32_t *rowptr,
+                              const int32_t *colidx, const float *vals, const void *A, const void *B, const void *C, float *out,
+                              void *workspace, size_t workspace_bytes, hipStream_t stream) {
+    return counted_call("csrk_call_bounded", nnz >= 0, op, bf16, nnz, M, K, D, N, rowptr, colidx, vals, A, B, C, out, workspace,
+                        workspace_bytes, stream);
 }
 
 csrk_status csrk_validate_csr(int M, int K, const int32_t *rowptr, const int32_t *colidx, hipStream_t stream,

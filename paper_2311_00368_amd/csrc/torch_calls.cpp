@@ -113,8 +113,8 @@ PyObject *call(PyObject *, PyObject *const *v, Py_ssize_t n) {
         const hipStream_t stream = c10::hip::getCurrentHIPStream(a.device.index()).stream();
         csrk_status status;
         Py_BEGIN_ALLOW_THREADS
-        status = csrk_call(op, bf16, nnz, M, K, D, N, (const int32_t *)rowptr, (const int32_t *)colidx, (const float *)vals, x.A,
-                           x.B, x.C, (float *)out, ws, ws_bytes, stream);
+        status = csrk_call_bounded(op, bf16, nnz, M, K, D, N, (const int32_t *)rowptr, (const int32_t *)colidx, (const float *)vals,
+                                   x.A, x.B, x.C, (float *)out, ws, ws_bytes, stream);
         Py_END_ALLOW_THREADS
         return result(v[12], made, status);
     });

@@ -110,3 +110,37 @@ def test_capture(csrk, monkeypatch, has):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("M,K,D,N", SHAPES)
+def test_a_count_that_is_too_small(csrk, monkeypatch, M, K, D, N):
+    # csrk_call's count is an expectation: nothing may be sized by it.  The call does without products in memory, also where its
+    # scratch has room for them; csrk_call_bounded vouches for the count.
+    s = operands(M, K, D, N, 3)
+    rp, ci, v, A, B, C = s
+    lib, nnz = csrk.load(), len(ci)
+    monkeypatch.setenv("CSRK_MFMA", "2")
+    kernel = csrk.fusedmm_csr(M, K, D, N, *s)
+    monkeypatch.setenv("CSRK_MFMA", "1")
+    out = torch.empty((M, N), device="cuda")
+    ws = torch.empty(csrk.csrk_workspace_bytes(csrk.CSRK_OP_FUSEDMM, M, K, N, D) + 4 * nnz + (1 << 20), dtype=torch.uint8, device="cuda")
+
+    def call(fn, count, workspace=None):
+        out.fill_(7)
+        status = fn(csrk.CSRK_OP_FUSEDMM, 0, count, M, K, D, N, *(t.data_ptr() for t in s), out.data_ptr(),
+                    workspace.data_ptr() if workspace is not None else None, workspace.numel() if workspace is not None else 0,
+                    torch.cuda.current_stream().cuda_stream)
+        assert status == 0, csrk.csrk_last_error()
+        return out.clone()
+
+    for workspace in (None, ws):
+        for count in (nnz, nnz - 1, nnz - nnz // 50, nnz + nnz // 50):
+            assert torch.equal(call(lib.csrk_call, count, workspace), kernel), count
+        for count in (nnz, nnz + nnz // 50):
+            assert torch.equal(call(lib.csrk_call_bounded, count, workspace), two_calls(csrk, M, K, D, N, *s)), count
+    # a count that is far off: another kernel, the same results to rounding
+    for count in (0, nnz // 3, -1):
+        assert (call(lib.csrk_call, count) - kernel).norm() <= 1e-6 * kernel.norm(), count
+    # (the scratch of the one kernel)
+    one = csrk.csrk_workspace_bytes(csrk.CSRK_OP_FUSEDMM, M, K, N, D)
+    assert scratch_of(csrk, lambda: call(lib.csrk_call, nnz)) < one + 2 * nnz
