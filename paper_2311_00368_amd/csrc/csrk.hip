@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -86,6 +87,7 @@ struct LazyScratch {
     int32_t *head_row = nullptr;
     size_t head_floats = 0;
     int flag_set = 0;       // which of the two sets of per-call flag words the next tiled attempt uses (see tile_go)
+    size_t refused = SIZE_MAX;      // bytes that could not be had, where more_scratch was to remember it
 };
 
 // Everything ONE call works with.  It lives on the calling thread's stack, so calls that bring their own scratch
@@ -291,6 +293,36 @@ csrk_status ensure_scratch(DeviceState &d, int width, size_t min_floats = 0) {
         d.head_floats = need;
     }
     return CSRK_OK;
+}
+
+// The same for calls that can do without, in kernels that need less: the new area is allocated before the old one is freed, so a call
+// that cannot have it loses nothing, and neither do HIP graphs captured on the old one.  false: not to be had, or not during a capture.
+// `remember`: do not ask for a size again that could not be had, before csrk_release_workspace.
+// (CSRK_SCRATCH_MB: a test's limit in place of the device's.)
+bool more_scratch(DeviceState &d, size_t bytes, hipStream_t stream, bool remember = false) {
+    if (bytes <= d.head_floats * sizeof(float)) return true;
+    if (d.fixed || (remember && bytes >= d.lazy->refused)) return false;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return false;
+    }
+    LazyScratch &g = *d.lazy;
+    const size_t floats = std::max((bytes + sizeof(float) - 1) / sizeof(float), (size_t)d.workers);
+    float *mem = nullptr;
+    if (bytes >> 20 >= (size_t)env_int("CSRK_SCRATCH_MB", INT_MAX) || hipMalloc((void **)&mem, floats * sizeof(float)) != hipSuccess) {
+        (void)hipGetLastError();
+        if (remember) g.refused = bytes;
+        return false;
+    }
+    if (g.head && (hipDeviceSynchronize() != hipSuccess || hipFree(g.head) != hipSuccess)) {
+        (void)hipFree(mem);
+        (void)hipGetLastError();
+        return false;
+    }
+    g.head = d.head = mem;
+    g.head_floats = d.head_floats = floats;
+    return true;
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -1530,17 +1562,12 @@ bool dense_chosen(const DeviceState &d, const csrk_plan_s *plan, const DenseShap
 
 // The vector kernels need far less scratch, so a call that cannot have what the matrix-core kernels need is theirs: one
 // that would have to allocate it while its stream is captured, and one for which there is no memory left.
+bool dense_scratch(DeviceState &d, const DenseConfig &c, hipStream_t stream) {
+    return env_int("CSRK_MFMA", 1) == 2 || more_scratch(d, c.bytes, stream);
+}
 bool dense_wanted(DeviceState &d, const csrk_plan_s *plan, const DenseShape &s, uintptr_t operands, long long nnz, hipStream_t stream,
                   DenseConfig *c) {
-    if (!dense_chosen(d, plan, s, operands, nnz, c)) return false;
-    if (d.fixed || c->bytes <= d.head_floats * sizeof(float) || env_int("CSRK_MFMA", 1) == 2) return true;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &capture) == hipSuccess) {
-        if (capture != hipStreamCaptureStatusNone) return false;
-        if (ensure_scratch(d, 1, (c->bytes + sizeof(float) - 1) / sizeof(float)) == CSRK_OK) return true;
-    }
-    (void)hipGetLastError();
-    return false;
+    return dense_chosen(d, plan, s, operands, nnz, c) && dense_scratch(d, *c, stream);
 }
 
 csrk_status dense_call(DeviceState &d, const DenseShape &s, const DenseConfig &c, const int32_t *rowptr, const int32_t *colidx,
@@ -1566,8 +1593,8 @@ struct TwoPasses {
     size_t products, bytes;     // of scratch: SDDMM's result, and all
 };
 constexpr size_t kMaxProducts = size_t(1) << 30;
-bool two_passes_wanted(DeviceState &d, const csrk_plan_s *plan, const DenseShape &s, const DenseConfig &fused, bool stored, uintptr_t scores,
-                       uintptr_t product, long long nnz, hipStream_t stream, TwoPasses *t) {
+bool two_passes_chosen(const DeviceState &d, const csrk_plan_s *plan, const DenseShape &s, const DenseConfig &fused, bool stored,
+                       uintptr_t scores, uintptr_t product, long long nnz, TwoPasses *t) {
     if (env_int("CSRK_MFMA", 1) != 1 || !fused.halves || s.D <= 32 || s.D > 64) return false;
     t->products = ((size_t)nnz * sizeof(float) + 255) / 256 * 256;
     if (t->products > kMaxProducts) return false;
@@ -1580,25 +1607,10 @@ bool two_passes_wanted(DeviceState &d, const csrk_plan_s *plan, const DenseShape
     const double us = dense_us(d, t->sddmm, t->scores, density, true) + dense_us(d, t->spmm, t->product, density, true);
     if (us * 1.06 >= dense_us(d, s, fused, density, true)) return false;
     t->bytes = t->products + (t->scores.bytes > t->product.bytes ? t->scores.bytes : t->product.bytes);
-    // (without the scratch, FusedMM's kernel)
-    if (t->bytes <= d.head_floats * sizeof(float)) return true;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (!d.fixed && hipStreamIsCapturing(stream, &capture) == hipSuccess) {
-        if (capture != hipStreamCaptureStatusNone) return false;
-        if (ensure_scratch(d, 1, (t->bytes + sizeof(float) - 1) / sizeof(float)) == CSRK_OK) return true;
-    }
-    (void)hipGetLastError();
-    return false;
+    return true;
 }
-
-// FP32 FusedMM on the matrix cores, in one pass or two
-csrk_status dense_fused_call(DeviceState &d, const csrk_plan_s *plan, const DenseShape &s, const DenseConfig &c, long long nnz, bool bound,
-                             const int32_t *rowptr, const int32_t *colidx, const float *vals, const void *A, const void *B, const void *C, float *out,
-                             hipStream_t stream) {
-    TwoPasses t;
-    // (SDDMM writes rowptr[M] products into room for nnz)
-    if (!bound || !two_passes_wanted(d, plan, s, c, vals != nullptr, addresses({A, B}), addresses({C, out}), nnz, stream, &t))
-        return dense_call(d, s, c, rowptr, colidx, vals, A, B, C, out, stream);
+csrk_status two_passes_call(DeviceState &d, const TwoPasses &t, const int32_t *rowptr, const int32_t *colidx, const float *vals, const void *A,
+                            const void *B, const void *C, float *out, hipStream_t stream) {
     float *const products = d.head;
     char *const rest = reinterpret_cast<char *>(d.head) + t.products;
     CSRK_HIP(dense_run(t.sddmm, t.scores, rowptr, colidx, vals, A, B, nullptr, products, rest, stream));
@@ -1850,9 +1862,19 @@ static csrk_status fusedmm_run(const csrk_plan_s *plan, const ScratchSource &scr
     CallRecord rec(3, stream);
     const DenseShape shape{kDenseFused, false, M, K, N, D};
     DenseConfig dense;
-    if (dense_wanted(*d, plan, shape, addresses({A, B, C, O}), nnz, stream, &dense)) {
-        rec.begin();
-        return dense_fused_call(*d, plan, shape, dense, nnz, bound, rowptr, colidx, vals, A, B, C, O, stream);
+    if (dense_chosen(*d, plan, shape, addresses({A, B, C, O}), nnz, &dense)) {
+        // (SDDMM writes rowptr[M] products into room for nnz.  Their scratch is asked for before the one kernel's, which a call without it
+        // falls back to; not again where it could not be had: the one kernel takes 1.15 times as long, a failing allocation may take longer)
+        TwoPasses two;
+        if (bound && two_passes_chosen(*d, plan, shape, dense, vals != nullptr, addresses({A, B}), addresses({C, O}), nnz, &two) &&
+            more_scratch(*d, two.bytes, stream, true)) {
+            rec.begin();
+            return two_passes_call(*d, two, rowptr, colidx, vals, A, B, C, O, stream);
+        }
+        if (dense_scratch(*d, dense, stream)) {
+            rec.begin();
+            return dense_call(*d, shape, dense, rowptr, colidx, vals, A, B, C, O, stream);
+        }
     }
     d->pending_ksplit = 0;
     if (csrk_status s = ensure_scratch(*d, N)) return s;
@@ -2630,6 +2652,7 @@ csrk_status csrk_release_workspace(void) {
     g.head = nullptr;
     g.head_row = nullptr;
     g.head_floats = 0;
+    g.refused = SIZE_MAX;
     return CSRK_OK;
 }
 

@@ -144,3 +144,39 @@ def test_a_count_that_is_too_small(csrk, monkeypatch, M, K, D, N):
     # (the scratch of the one kernel)
     one = csrk.csrk_workspace_bytes(csrk.CSRK_OP_FUSEDMM, M, K, N, D)
     assert scratch_of(csrk, lambda: call(lib.csrk_call, nnz)) < one + 2 * nnz
+
+
+def test_scratch_that_cannot_be_had(csrk, monkeypatch):
+    # A call that cannot have room for its products keeps the area there is, and with it the graphs captured on it, and does not ask
+    # again before the area is released.  (CSRK_SCRATCH_MB stands in for a device without memory.)
+    M, K, D, N = SHAPES[0]
+    s = operands(M, K, D, N, 4)
+    one = csrk.csrk_workspace_bytes(csrk.CSRK_OP_FUSEDMM, M, K, N, D)
+    csrk.csrk_release_workspace()
+    monkeypatch.setenv("CSRK_MFMA", "2")
+    kernel = csrk.fusedmm_csr(M, K, D, N, *s)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        captured = csrk.fusedmm_csr(M, K, D, N, *s)
+    monkeypatch.setenv("CSRK_MFMA", "1")
+    monkeypatch.setenv("CSRK_SCRATCH_MB", "1")
+    before = torch.cuda.mem_get_info()[0]
+    for _ in range(2):
+        out = csrk.fusedmm_csr(M, K, D, N, *s)
+        captured.fill_(7)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, kernel) and torch.equal(captured, kernel)
+    monkeypatch.delenv("CSRK_SCRATCH_MB")
+    assert torch.equal(csrk.fusedmm_csr(M, K, D, N, *s), kernel)
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] > before - one // 2
+    csrk.csrk_release_workspace()
+    assert torch.equal(csrk.fusedmm_csr(M, K, D, N, *s), two_calls(csrk, M, K, D, N, *s))
+    # nothing at all to be had for the matrix cores
+    csrk.csrk_release_workspace()
+    monkeypatch.setenv("CSRK_SCRATCH_MB", "1")
+    out = csrk.fusedmm_csr(M, K, D, N, *s)
+    monkeypatch.setenv("CSRK_MFMA", "3")
+    assert torch.equal(out, csrk.fusedmm_csr(M, K, D, N, *s))
