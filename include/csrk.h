@@ -42,7 +42,9 @@
  *    and column of S.  FP32 FusedMM with dot products of 33-64 elements and wide outputs over
  *    long rows writes its products where it is faster that way and their room, 4 bytes per
  *    stored entry up to 1 GiB, can be had and is known to be enough (planned calls,
- *    csrk_call_bounded); csrk_workspace_bytes does not count them.  Three ways to provide it:
+ *    csrk_call_bounded).  csrk_workspace_bytes, which does not know the entries, leaves them out:
+ *    a workspace that is larger by that room (4 * nnz rounded up to 256 bytes) has it.  Three
+ *    ways to provide scratch:
  *      * spmm_csr / sddmm_csr / fusedmm_csr (and their planned and bfloat16 forms) use
  *        an area the library keeps per device.  It is allocated (hipMalloc, which
  *        synchronises) the first time it is needed, replaced when it has to grow (after
@@ -285,7 +287,8 @@ csrk_status csrk_plan_create(int M, int K, const int32_t *rowptr, const int32_t 
  * Gives the plan a workspace of its own, large enough for spmm_csr_plan and fusedmm_csr_plan
  * with outputs of up to max_N columns (and for sddmm_csr_plan), whichever kernels they take
  * and with dot products of up to 128 elements (16384 x 16384, 512 columns: some 0.1 GB, most of
- * it for the matrix-core kernels' operands in pieces): allocates it here
+ * it for the matrix-core kernels' operands in pieces, or 0.3 GB with 20 % stored, where FusedMM's
+ * products take 4 bytes per entry, see "Scratch"): allocates it here
  * (hipMalloc; if the plan already had a smaller one, the device is synchronised and that one
  * freed), freed by csrk_plan_destroy.  Planned calls that fit into it use it instead of the
  * library's per-device area and then allocate nothing, never synchronise, take no lock and

@@ -1593,22 +1593,25 @@ struct TwoPasses {
     size_t products, bytes;     // of scratch: SDDMM's result, and all
 };
 constexpr size_t kMaxProducts = size_t(1) << 30;
-bool two_passes_chosen(const DeviceState &d, const csrk_plan_s *plan, const DenseShape &s, const DenseConfig &fused, bool stored,
-                       uintptr_t scores, uintptr_t product, long long nnz, TwoPasses *t) {
-    if (env_int("CSRK_MFMA", 1) != 1 || !fused.halves || s.D <= 32 || s.D > 64) return false;
+// What the forms and the estimates say; `stored`: S has values.
+bool two_passes_pay(const DeviceState &d, const DenseShape &s, const DenseConfig &fused, bool stored, long long nnz, TwoPasses *t) {
+    if (!fused.halves || s.D <= 32 || s.D > 64) return false;
     t->products = ((size_t)nnz * sizeof(float) + 255) / 256 * 256;
     if (t->products > kMaxProducts) return false;
     t->sddmm = DenseShape{kDenseSddmm, false, s.M, s.K, 0, s.D, !stored};
     t->spmm = DenseShape{kDenseSpmm, false, s.M, s.K, s.N, 0};
-    if (!dense_chosen(d, plan, t->sddmm, scores, nnz, &t->scores) || !dense_chosen(d, plan, t->spmm, product, nnz, &t->product) ||
-        !t->product.halves)
-        return false;
+    if (!dense_config(t->sddmm, d.cus, &t->scores) || !dense_config(t->spmm, d.cus, &t->product) || !t->product.halves) return false;
     const double density = (double)nnz / ((double)s.M * (double)s.K);
     const double us = dense_us(d, t->sddmm, t->scores, density, true) + dense_us(d, t->spmm, t->product, density, true);
-    if (us * 1.06 >= dense_us(d, s, fused, density, true)) return false;
     t->bytes = t->products + (t->scores.bytes > t->product.bytes ? t->scores.bytes : t->product.bytes);
-    return true;
+    return us * 1.06 < dense_us(d, s, fused, density, true);
 }
+bool two_passes_chosen(const DeviceState &d, const csrk_plan_s *plan, const DenseShape &s, const DenseConfig &fused, bool stored,
+                       uintptr_t scores, uintptr_t product, long long nnz, TwoPasses *t) {
+    return env_int("CSRK_MFMA", 1) == 1 && two_passes_pay(d, s, fused, stored, nnz, t) &&
+           dense_chosen(d, plan, t->sddmm, scores, nnz, &t->scores) && dense_chosen(d, plan, t->spmm, product, nnz, &t->product);
+}
+
 csrk_status two_passes_call(DeviceState &d, const TwoPasses &t, const int32_t *rowptr, const int32_t *colidx, const float *vals, const void *A,
                             const void *B, const void *C, float *out, hipStream_t stream) {
     float *const products = d.head;
@@ -2119,6 +2122,8 @@ csrk_status csrk_plan_reserve(csrk_plan *plan, int max_N) {
     if (csrk_status s = plan_usable("csrk_plan_reserve", plan)) return s;
     if (max_N < 0 || max_N >= (1 << 24)) return fail(CSRK_INVALID_ARG, "csrk_plan_reserve: width out of range");
     size_t bytes = 0;
+    const DeviceInfo *info = nullptr;
+    if (csrk_status s = device_info(&info)) return s;
     // (a narrower output may need more: its K is cut into more ranges.  The matrix-core kernels take widths in pieces of 16)
     for (int op : {CSRK_OP_SPMM, CSRK_OP_FUSEDMM, CSRK_OP_SDDMM})
         for (int n = max_N; n >= 0; n = n > 2048 ? 2048 : n % 16 ? n / 16 * 16 : n - 16) {
@@ -2126,10 +2131,17 @@ csrk_status csrk_plan_reserve(csrk_plan *plan, int max_N) {
             if (csrk_status s = csrk_workspace_bytes(op, plan->M, plan->K, n, 0, &need)) return s;
             bytes = need > bytes ? need : bytes;
             if (op == CSRK_OP_SDDMM) break;
+            // FusedMM in two passes: all dot products of 33-64 elements have the form of those of 64
+            DeviceState d;
+            d.cus = info->cus;
+            DenseConfig fused;
+            TwoPasses two;
+            const DenseShape shape{kDenseFused, false, plan->M, plan->K, n, 64};
+            if (op == CSRK_OP_FUSEDMM && plan->sorted && dense_config(shape, info->cus, &fused) &&
+                two_passes_pay(d, shape, fused, true, plan->nnz, &two))
+                bytes = std::max(bytes, scratch_int_bytes(info->workers) + (two.bytes + 255) / 256 * 256);
         }
     if (plan->has_sched) {      // the partial rows of the plan's schedule for uneven rows
-        const DeviceInfo *info = nullptr;
-        if (csrk_status s = device_info(&info)) return s;
         const size_t with_sched = scratch_int_bytes(info->workers) + sched_partial_floats(plan, max_N) * sizeof(float);
         bytes = with_sched > bytes ? with_sched : bytes;
     }

@@ -123,7 +123,9 @@ def test_a_count_that_is_too_small(csrk, monkeypatch, M, K, D, N):
     kernel = csrk.fusedmm_csr(M, K, D, N, *s)
     monkeypatch.setenv("CSRK_MFMA", "1")
     out = torch.empty((M, N), device="cuda")
-    ws = torch.empty(csrk.csrk_workspace_bytes(csrk.CSRK_OP_FUSEDMM, M, K, N, D) + 4 * nnz + (1 << 20), dtype=torch.uint8, device="cuda")
+    # (what the header says is enough for the products)
+    ws = torch.empty(csrk.csrk_workspace_bytes(csrk.CSRK_OP_FUSEDMM, M, K, N, D) + (4 * (nnz + nnz // 50) + 255) // 256 * 256,
+                     dtype=torch.uint8, device="cuda")
 
     def call(fn, count, workspace=None):
         out.fill_(7)
@@ -180,3 +182,26 @@ def test_scratch_that_cannot_be_had(csrk, monkeypatch):
     out = csrk.fusedmm_csr(M, K, D, N, *s)
     monkeypatch.setenv("CSRK_MFMA", "3")
     assert torch.equal(out, csrk.fusedmm_csr(M, K, D, N, *s))
+
+
+@pytest.mark.parametrize("M,K,D,N", SHAPES)
+@pytest.mark.parametrize("wider", [0, 3])
+def test_reserved_plan(csrk, M, K, D, N, wider):
+    # a plan's own scratch has room for the products: the same kernels, and so the same bits, as without it, and in a capture
+    # (so many entries that their products do not fit into the room for the other kernels by chance)
+    s = operands(M, K, D, N, 5, density=0.13)
+    rp, ci, v, A, B, C = s
+    want = two_calls(csrk, M, K, D, N, *s)
+    csrk.csrk_release_workspace()
+    plan = csrk.csrk_plan_create(M, K, rp, ci)
+    csrk.csrk_plan_reserve(plan, N + wider)
+    assert torch.equal(csrk.fusedmm_csr_plan(plan, D, N, v, A, B, C), want)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = csrk.fusedmm_csr_plan(plan, D, N, v, A, B, C)
+    for _ in range(3):
+        out.fill_(7)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
