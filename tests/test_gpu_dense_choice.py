@@ -65,3 +65,46 @@ def test_capture_without_the_scratch(csrk, monkeypatch, shape):
     assert not torch.equal(dense, vector)
     csrk.csrk_release_workspace()
     assert torch.equal(call(), dense)
+
+
+# op, M, K, D, N, density, rows, planned
+NO_LESS_EXACT = [("fusedmm", 29184, 3840, 84, 32, 0.07, "even", False), ("spmm", 30424, 574, 0, 32, 0.21, "even", False),
+                 ("spmm", 16384, 512, 0, 64, 0.157, "lognormal", False), ("fusedmm", 16760, 578, 64, 36, 0.214, "lognormal", False),
+                 ("fusedmm", 12764, 3172, 104, 456, 0.1129, "even", False), ("spmm", 6656, 5120, 0, 336, 0.0792, "lognormal", False),
+                 ("spmm", 7258, 2725, 0, 352, 0.0729, "lognormal", False),
+                 ("spmm", 12288, 768, 0, 480, 0.1008, "lognormal", False),
+                 # (these are taken)
+                 ("spmm", 512, 2560, 0, 480, 0.316, "even", False), ("spmm", 1536, 4608, 0, 480, 0.135, "lognormal", False),
+                 ("fusedmm", 1024, 8448, 128, 472, 0.126, "even", False), ("fusedmm", 753, 2207, 88, 512, 0.262, "lognormal", False),
+                 ("spmm", 512, 2560, 0, 480, 0.316, "even", True)]
+
+
+@pytest.mark.parametrize("shape", NO_LESS_EXACT, ids=lambda s: "-".join(map(str, s)))
+def test_no_less_exact_on_data_of_one_sign(csrk, monkeypatch, shape):
+    # whatever is chosen by the family that would do the call: no further from FP64 than the vector kernels, in the 2-norm.  (Sums of one
+    # sign, where the matrix cores' truncation shows most; the same inputs every time, on which the ratio lies below 0.95 or is 1)
+    op, M, K, D, N, density, rows, planned = shape
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    p = torch.full((M,), density, device="cuda")
+    if rows == "lognormal":
+        p = (density * torch.exp(torch.randn(M, device="cuda", generator=g) - 0.5)).clamp(1 / K, 1)
+    keep = torch.rand((M, K), device="cuda", generator=g) < p[:, None]
+    rp = torch.zeros(M + 1, dtype=torch.int32, device="cuda")
+    rp[1:] = keep.sum(1).cumsum(0)
+    ci = keep.nonzero()[:, 1].to(torch.int32)
+    v, A, B, C = (torch.rand(s, device="cuda", generator=g) for s in (len(ci), (M, D), (K, D), (K, N)))
+    S = torch.zeros((M, K), dtype=torch.float64, device="cuda")
+    S[keep] = v.double()
+    if op == "fusedmm":
+        S *= A.double() @ B.double().T
+    want = S @ C.double()
+    plan = csrk.csrk_plan_create(M, K, rp, ci) if planned else None
+    error = {}
+    for mode in "13":
+        monkeypatch.setenv("CSRK_MFMA", mode)
+        if op == "spmm":
+            out = csrk.spmm_csr_plan(plan, N, v, C) if planned else csrk.spmm_csr(M, K, N, rp, ci, v, C)
+        else:
+            out = csrk.fusedmm_csr(M, K, D, N, rp, ci, v, A, B, C)
+        error[mode] = ((out.double() - want).norm() / want.norm()).item()
+    assert error["1"] <= error["3"], error
