@@ -1478,7 +1478,11 @@ double family_us(const DeviceState &d, const csrk_plan_s *plan, const DenseShape
 // these ranges, times as fast as the vector kernels on average (always the better of the two): FP32 of up to 32 elements 1.11 (1.17),
 // 33-64 1.14 (1.23), 65-96 1.32 (1.34), 97-128 1.34 (1.38); bfloat16 1.19 times as fast as the choice before (1.26).  Of 1800 FP32
 // calls with even rows and up to 64 elements 5 are slower by more than 3 %, at worst 0.89 times as fast; of those with log-normal
-// rows, which the host cannot tell, a twentieth, at worst 0.78 times.
+// rows, which the host cannot tell without a plan, a twentieth, at worst 0.78 times.  With uneven rows the estimate for up to 32 elements
+// is 1.16 times too low (120 planned calls with log-normal rows; of more elements level), so where a plan says so that much more is asked
+// for: of the 120 a tenth took 13 that are slower by more than 3 % (at worst 0.74 times as fast) and this takes 2 of 81 (0.83).  Outside of the
+// ranges of the fit nothing more is asked for: of 354 calls there with even rows (M 64-200000, K 64-65536, 0.8-95 %, D from 4) that are
+// taken one is slower by more than 3 % (0.84), of 146 with log-normal rows 4, and all of them are 2.9 times as fast on average.
 
 // The two estimates above err in ways that depend on the class of the call: the kernels of both sides have changed since
 // they were fitted, and a call of 30 us is not a call of 300 us made ten times.  So for the classes where that loses most
@@ -1558,7 +1562,8 @@ bool dense_chosen(const DeviceState &d, const csrk_plan_s *plan, const DenseShap
     const double density = (double)nnz / ((double)s.M * (double)s.K);
     const bool slabs = s.op == kDenseSddmm && sddmm_in_slabs(s);
     const double us = dense_us(d, s, *c, density, wide);
-    if (us * (slabs && s.D > 64 ? 1.0 : 1.1) < vector) return true;
+    const double margin = slabs && s.D > 64 ? 1.0 : slabs && s.D <= 32 && plan && !plan->even ? 1.1 * 1.16 : 1.1;
+    if (us * margin < vector) return true;
     return !slabs && wide && dense_is_faster(s, *c, plan != nullptr, density, us, vector, family_us(d, plan, s, nnz));
 }
 

@@ -108,3 +108,26 @@ def test_no_less_exact_on_data_of_one_sign(csrk, monkeypatch, shape):
             out = csrk.fusedmm_csr(M, K, D, N, rp, ci, v, A, B, C)
         error[mode] = ((out.double() - want).norm() / want.norm()).item()
     assert error["1"] <= error["3"], error
+
+
+@pytest.mark.parametrize("even", [False, True])
+@pytest.mark.parametrize("M,K,D,density", [(8170, 10048, 32, 0.0618), (3966, 10910, 32, 0.0946)])
+def test_planned_sddmm_of_uneven_rows(csrk, monkeypatch, even, M, K, D, density):
+    # near the line, where slabs of scores lose what uneven rows cost them: only a plan can tell
+    g = torch.Generator(device="cuda").manual_seed(K)
+    z = torch.zeros(M, device="cuda") if even else torch.randn(M, device="cuda", generator=g) - 0.5
+    p = (density * torch.exp(z)).clamp(1 / K, 1)
+    keep = torch.rand((M, K), device="cuda", generator=g) < p[:, None]
+    rp = torch.zeros(M + 1, dtype=torch.int32, device="cuda")
+    rp[1:] = keep.sum(1).cumsum(0)
+    ci = keep.nonzero()[:, 1].to(torch.int32)
+    v, A, B = (torch.rand(s, device="cuda", generator=g) for s in (len(ci), (M, D), (K, D)))
+    plan = csrk.csrk_plan_create(M, K, rp, ci)
+    assert csrk.csrk_plan_info(plan)[2] == even
+    planned, plain = {}, {}
+    for mode in "123":
+        monkeypatch.setenv("CSRK_MFMA", mode)
+        planned[mode] = csrk.sddmm_csr_plan(plan, D, v, A, B)
+        plain[mode] = csrk.sddmm_csr(M, K, D, rp, ci, v, A, B)
+    assert torch.equal(planned["1"], planned["2" if even else "3"])
+    assert torch.equal(plain["1"], plain["2"]) and not torch.equal(plain["1"], plain["3"])
