@@ -119,6 +119,20 @@ __global__ __launch_bounds__(finish_waves(HALVES, FUSED) * kWave) void dense_fin
         int s0 = begin, s1 = end;
         if (share) row_part(begin, end, wave, kWaves, s0, s1);
         float *const orow = a.O + (size_t)row * N;
+        if constexpr (HALVES && !FUSED) {
+            // A NaN among the row's values is one in all of its results, whatever C holds, and the matrix cores have left one.  (As in FusedMM's
+            // products, where a NaN in B leaves one in every row that stores its column: 16384^2, 20 %, 512/64 4.6 -> 2.6 ms with one
+            // such row of B, 12.9 -> 3.2 with ten.)
+            if (a.vals && orow[0] != orow[0]) {
+                bool nan = false;
+#pragma unroll 4
+                for (int j = s0 + lane; j < s1; j += kWave) nan |= a.vals[j] != a.vals[j];
+                if (share ? __syncthreads_or(nan) : __any(nan)) {
+                    for (int n = share ? (int)threadIdx.x : lane; n < N; n += share ? kThreads : kWave) orow[n] = __builtin_nanf("");
+                    return;
+                }
+            }
+        }
         auto columns = [&](auto lanes, auto tiles, auto &parts, int n) CSRK_INLINE {
             constexpr int LN = decltype(lanes)::value, TN = decltype(tiles)::value;
             float acc[TN][VEC] = {};
