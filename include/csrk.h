@@ -111,7 +111,8 @@ csrk_status sddmm_csr(int M, int K, int D,
 
 /*
  * FusedMM, paper eq. (3) / Algorithm 3: SDDMM followed by SPMM with the sampled
- * scores kept on chip (never written to device memory):
+ * scores kept on chip (this call never writes them to device memory; planned calls and
+ * csrk_call_bounded do so where it is the faster way, see "Scratch"):
  *   O[i, :] = sum_j ( vals[j] * <A[i, :], B[colidx[j], :]> ) * C[colidx[j], :]
  * A is M x D, B is K x D, C is K x N, O is M x N (overwritten).  The paper has
  * D == N; here the dot length D and the output width N are independent.

@@ -1594,6 +1594,9 @@ csrk_status dense_call(DeviceState &d, const DenseShape &s, const DenseConfig &c
 // 1.00).  Of up to 32 elements the scores are too cheap.  Of more than 64 the one kernel has blocks of up to 128 columns, whose sums
 // are added up on the way, and SPMM in wider ones is up to 4 times as far off; in such blocks it is no faster on average, and up to
 // 1.25 times as far off.
+// What it is slower at, one kernel / two passes at 16384^2, 20 %, 512/64: rows of B of very different sizes, which the one kernel scales one
+// by one (10^-3 ... 10^3 1330 / 1640 us, with C's rows the inverse 1160 / 2210; 10^-1 ... 10^1 1190 / 1040), and rows of B with a
+// NaN (one 1.7 / 2.6 ms, ten 1.8 / 3.2) or an infinity (1.7 / 4.6 ms), which it leaves out and adds behind.
 struct TwoPasses {
     DenseShape sddmm, spmm;
     DenseConfig scores, product;

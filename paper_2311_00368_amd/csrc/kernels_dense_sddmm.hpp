@@ -25,13 +25,16 @@
 // FP64 in the 2-norm at D = 32 / 64 4.4e-8 / 4.8e-8 (vector kernels 1.06e-7 / 1.47e-7).
 // FP32 dot products of more than 64 elements need more registers for A than a scorer has: two scorers have one half of the steps each
 // and two the other, in slabs of 128 columns, and the handlers add the halves' products with the entry's value.  Kernel of 16 lanes per
-// row / this: 4096^2, 30 %, D = 128 46 / 37 us; 16384^2, 20 %, D = 128 480 / 367; 8192^2, 15 %, D = 72 98 / 86; log-normal rows, 10 %, D = 128
+// row / this: 4096^2, 30 %, D = 128 40.3 / 34.5 us; 16384^2, 20 %, D = 128 480 / 367; 8192^2, 15 %, D = 72 98 / 86; log-normal rows, 10 %, D = 128
 // 136 / 95.  Error against FP64 5.3e-8 / 5.1e-8, of data of one sign 4.7e-8 / 3.8e-8 (the halves' sum in one accumulator after the
 // other: 9.9e-8; added before the multiplication 5.5e-8).
 // What bounds it: at 10 % and D = 32 neither kind alone (scorers 88 us, handlers 89, of which 19 for the call and each workgroup's
-// first loads) but both on one SIMD, whose matrix cores are busy for 40 % of the cycles; from 20 % on the handlers, at the rate of
+// first loads) but both on one SIMD, whose matrix cores are busy for 42 % of the cycles; from 20 % on the handlers, at the rate of
 // memory (150 us without the scores at 20 %).  With D = 64 B does not fit an L2 and its fragments are late (151 us without them): the
 // rows of A leave registers for two tiles of them.
+// Registers: FP32 kernels of more than 32 elements are at the 168 that 12 wavefronts leave, and spill 2 (up to 64 elements), 1 (up to 96)
+// and 6 (more).  In their loops the first read one word per slab back from memory, half of the scorers of the last four words of
+// A; at 4096^2, 30 %, D = 128 the matrix cores are busy for 39 % of the cycles.
 #pragma once
 #include "kernels_dense.hpp"
 
