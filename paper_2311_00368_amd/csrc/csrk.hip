@@ -1434,25 +1434,25 @@ double vector_us(const DenseShape &s, long long nnz, bool wide) {
 // The same for FP32 SPMM and FusedMM by the family that does the call if its rows are even, which is most of what the estimate above
 // does not know: fitted by least squares of the relative error to 9100 calls of the same ranges, those of a family scatter by 4-25 %
 // around it (around the other by as much, and off by up to 2.3 times).  The matrix-core kernels are also taken where they are expected
-// to be the faster by 8 %: with outputs of more than 64 columns, and where dense_is_faster finds them exact enough (it has what that gives).
+// to be the faster by 8 %, where dense_is_faster finds them exact enough (it has what that gives).
 // Planned calls have fewer launches and take them by 19 %, with even rows and not from the tiled kernels (which a plan makes faster than
-// this estimate: 13 of 20 faster, 6 slower).  0: not known (no such calls in the fit, or narrow ones).
-// [SPMM, FusedMM of up to 64 elements, of more][equal shares, whole rows, whole-row kernels, tiled][N to 128, 256, more]
+// this estimate: 13 of 20 faster, 6 slower).  0: not known (no such calls in the fit).
+// [SPMM, FusedMM of up to 64 elements, of more][equal shares, whole rows, whole-row kernels, tiled][N to 32, 128, 256, more]
 double family_us(const DeviceState &d, const csrk_plan_s *plan, const DenseShape &s, long long nnz) {
-    static constexpr VectorCost costs[3][4][3] = {
-        {{{11, 144, 3.11, 0}, {10.5, 92.4, 19.7, 0.389}, {5.37, 272, 0, 0.978}},
-         {{10.7, 138, 3.04, 0.00749}, {11.2, 33, 28.4, 0.119}, {28, 31.8, 48.5, 0}},
-         {{4.43, 138, 3.17, 0.0361}, {6.46, 16.1, 28.3, 0.0652}, {7.15, 14.5, 57.7, 0.113}},
-         {{16.8, 78.9, 0, 0.496}, {20.1, 0, 13.5, 0.983}, {27.3, 7.86, 18.9, 1.84}}},
-        {{{8.99, 177, 2.75, 0.356}, {7.2, 183, 8.7, 0.288}, {0, 307, 11.8, 0.054}},
-         {{13, 121, 5.99, 0}, {9.45, 76.9, 18.2, 0.554}, {0, 0, 0, 0}},
-         {{6.4, 145, 0, 0.236}, {5.74, 34.1, 28.3, 0.407}, {6.12, 30.8, 54.4, 0.815}},
-         {{20.5, 51.1, 2.83, 1.56}, {24.9, 8.74, 17.2, 1.92}, {31.6, 11.4, 21.8, 2.88}}},
-        {{{6.59, 161, 12.6, 0.567}, {2.03, 115, 35.1, 1.54}, {4.36, 266, 0, 3.54}},
-         {{12.2, 67.8, 21.6, 0.145}, {6.85, 61.8, 33, 1.02}, {29.2, 73.1, 34, 2.22}},
-         {{6.33, 65.2, 21.8, 0}, {7.05, 5.71, 48, 0.0242}, {8.73, 9.79, 75.2, 0.589}},
-         {{22.5, 33.7, 4.7, 2.42}, {55.5, 0, 26.2, 4.12}, {79, 92.3, 0, 7.15}}}};
-    if (s.bf16 || s.op == kDenseSddmm || s.N <= 64) return 0;
+    static constexpr VectorCost costs[3][4][4] = {
+        {{{11.6, 1.59, 5.21, 0}, {11, 144, 3.11, 0}, {10.5, 92.4, 19.7, 0.389}, {5.37, 272, 0, 0.978}},
+         {{10, 0, 5.49, 0.0428}, {10.7, 138, 3.04, 0.00749}, {11.2, 33, 28.4, 0.119}, {28, 31.8, 48.5, 0}},
+         {{4.11, 9.68, 4.98, 0.103}, {4.43, 138, 3.17, 0.0361}, {6.46, 16.1, 28.3, 0.0652}, {7.15, 14.5, 57.7, 0.113}},
+         {{14, 0, 2.82, 0.429}, {16.8, 78.9, 0, 0.496}, {20.1, 0, 13.5, 0.983}, {27.3, 7.86, 18.9, 1.84}}},
+        {{{11.5, 192, 0.55, 0.0155}, {8.99, 177, 2.75, 0.356}, {7.2, 183, 8.7, 0.288}, {0, 307, 11.8, 0.054}},
+         {{9.27, 131, 3.54, 0}, {13, 121, 5.99, 0}, {9.45, 76.9, 18.2, 0.554}, {0, 0, 0, 0}},
+         {{4.82, 117, 3.96, 0.193}, {6.4, 145, 0, 0.236}, {5.74, 34.1, 28.3, 0.407}, {6.12, 30.8, 54.4, 0.815}},
+         {{0, 0, 0, 0}, {20.5, 51.1, 2.83, 1.56}, {24.9, 8.74, 17.2, 1.92}, {31.6, 11.4, 21.8, 2.88}}},
+        {{{9.89, 128, 15.8, 0.03}, {6.59, 161, 12.6, 0.567}, {2.03, 115, 35.1, 1.54}, {4.36, 266, 0, 3.54}},
+         {{11.6, 9.9, 26.2, 0.0396}, {12.2, 67.8, 21.6, 0.145}, {6.85, 61.8, 33, 1.02}, {29.2, 73.1, 34, 2.22}},
+         {{6.98, 1.38, 26.2, 0.0219}, {6.33, 65.2, 21.8, 0}, {7.05, 5.71, 48, 0.0242}, {8.73, 9.79, 75.2, 0.589}},
+         {{0, 0, 0, 0}, {22.5, 33.7, 4.7, 2.42}, {55.5, 0, 26.2, 4.12}, {79, 92.3, 0, 7.15}}}};
+    if (s.bf16 || s.op == kDenseSddmm) return 0;
     const bool fused = s.op == kDenseFused;
     const Choice ch = fused ? choose_fused(d, plan, s.M, s.K, s.D, s.N, true, true) : choose_spmm(d, plan, s.M, s.K, s.N, true);
     int family;
@@ -1465,7 +1465,7 @@ double family_us(const DeviceState &d, const csrk_plan_s *plan, const DenseShape
         default: return 0;
     }
     if (plan && (!plan->even || family == 3)) return 0;
-    const VectorCost c = costs[!fused ? 0 : s.D <= 64 ? 1 : 2][family][s.N <= 128 ? 0 : s.N <= 256 ? 1 : 2];
+    const VectorCost c = costs[!fused ? 0 : s.D <= 64 ? 1 : 2][family][s.N <= 32 ? 0 : s.N <= 128 ? 1 : s.N <= 256 ? 2 : 3];
     return c.call + c.work * 1e-9 * (double)nnz * (s.N + s.D) + c.entries * 1e-6 * (double)nnz + c.cells * 1e-6 * (double)s.M * s.K;
 }
 
@@ -1510,13 +1510,20 @@ bool dense_is_faster(const DenseShape &s, const DenseConfig &c, bool planned, do
     const double outside = past(s.M, 512, 32768) + past(s.K, 512, 16384) + past(density, 0.055, 0.36) + past(s.N, 0, 512);
     const double line = (planned ? 0.1 : 0.0) + kOutside * outside;
     // The family's estimate counts only where the results are no further from FP64 than the vector kernels'.  Of data of both signs they
-    // are at 0.76 of that error at most wherever it would be asked.  Of data of one sign, where both are 4e-8 to 1.6e-7, they are further
-    // off in three places: outputs of up to 64 columns, which family_us leaves out (FusedMM 29184 x 3840, 32/84: 6.9e-8 against 4.9e-8); all of
-    // a K above 2048 in one range (FusedMM 12764 x 3172, 456/104: 7.0e-8 and 5.4e-8); blocks of 192 and 256 columns, which do not put sums away
-    // within a range, over all of K or over ranges of more than 768 columns of uneven rows (SPMM 12288 x 768, 480 columns, log-normal:
-    // 1.21e-7 and 0.99e-7).  Over 5875 random calls that are left and taken: at most 0.98 on data of one sign and 0.67 on data of both;
-    // 1.58 times as fast on average, 60 of them slower by more than 3 % (at worst 0.68).
-    const bool as_exact = c.ct <= 8 ? c.segs > 1 || s.K <= 2048 : c.segs > 1 && (planned || c.seg_k <= 768);
+    // are at 0.78 of that error at most wherever it would be asked.  Of data of one sign, where both are 4e-8 to 1.6e-7, they are further
+    // off where few ranges' sums are added up, or rows are short, so that the vector kernels' own sums are: outputs of up to 64 columns in
+    // one range (713 of 10300 calls that are left out here, by up to 1.66: FusedMM 29184 x 3840, 32/84 6.9e-8 against 4.9e-8) or in two or
+    // three; all of a K above 2048 in one range (FusedMM 12764 x 3172, 456/104: 7.0e-8 and 5.4e-8); blocks of 192 and 256 columns, which do
+    // not put sums away within a range, over all of K or in two or three ranges of more than 768 columns of uneven rows (SPMM 12288 x 768,
+    // 480 columns, log-normal: 1.21e-7 and 0.99e-7).  From four ranges on none is, but for up to 32 columns over K below 2560.
+    // Over 5951 random calls that are taken: at most 0.99 on data of one sign and 0.75 on data of both; 1.52 times as fast on average,
+    // 52 of them slower by more than 3 % (at worst 0.84).  Over 3820 planned ones from four ranges on (all that the matrix cores do of up to
+    // 64 columns): at most 0.97.
+    const bool few = c.segs < 4, some = c.segs > 1;
+    const bool as_exact = s.N <= 32   ? !few && s.K >= 3072
+                          : s.N <= 64 ? !few || (some && !planned && s.K >= 1536)
+                          : c.ct <= 8 ? some || s.K <= 2048
+                                      : !few || (some && (planned || c.seg_k <= 768));
     if (family > 0 && as_exact && std::log(family / (us * 1.08)) > line) return true;
     RatioFit f;
     if (s.op == kDenseSpmm && !s.bf16 && s.N > 32)

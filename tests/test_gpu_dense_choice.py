@@ -73,7 +73,11 @@ NO_LESS_EXACT = [("fusedmm", 29184, 3840, 84, 32, 0.07, "even", False), ("spmm",
                  ("fusedmm", 12764, 3172, 104, 456, 0.1129, "even", False), ("spmm", 6656, 5120, 0, 336, 0.0792, "lognormal", False),
                  ("spmm", 7258, 2725, 0, 352, 0.0729, "lognormal", False),
                  ("spmm", 12288, 768, 0, 480, 0.1008, "lognormal", False),
+                 ("spmm", 16384, 1024, 0, 32, 0.208, "lognormal", False), ("fusedmm", 12032, 512, 88, 32, 0.187, "lognormal", False),
+                 ("fusedmm", 15532, 558, 48, 64, 0.153, "lognormal", False), ("spmm", 5632, 1792, 0, 328, 0.102, "lognormal", False),
                  # (these are taken)
+                 ("fusedmm", 2917, 3143, 72, 20, 0.138, "even", False), ("spmm", 2406, 3083, 0, 64, 0.25, "even", False),
+                 ("fusedmm", 9370, 1605, 104, 44, 0.1, "lognormal", False),
                  ("spmm", 512, 2560, 0, 480, 0.316, "even", False), ("spmm", 1536, 4608, 0, 480, 0.135, "lognormal", False),
                  ("fusedmm", 1024, 8448, 128, 472, 0.126, "even", False), ("fusedmm", 753, 2207, 88, 512, 0.262, "lognormal", False),
                  ("spmm", 512, 2560, 0, 480, 0.316, "even", True)]
