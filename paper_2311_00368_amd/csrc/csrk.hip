@@ -1512,13 +1512,13 @@ bool dense_is_faster(const DenseShape &s, const DenseConfig &c, bool planned, do
     // The family's estimate counts only where the results are no further from FP64 than the vector kernels'.  Of data of both signs they
     // are at 0.78 of that error at most wherever it would be asked.  Of data of one sign, where both are 4e-8 to 1.6e-7, they are further
     // off where few ranges' sums are added up, or rows are short, so that the vector kernels' own sums are: outputs of up to 64 columns in
-    // one range (530 of 886 random calls, by up to 1.66: FusedMM 29184 x 3840, 32/84 6.9e-8 against 4.9e-8) or in two or
-    // three (160 of 1900, by up to 1.12); all of a K above 2048 in one range (FusedMM 12764 x 3172, 456/104: 7.0e-8 and 5.4e-8); blocks of 192 and 256 columns, which do
-    // not put sums away within a range, over all of K or in two or three ranges of more than 768 columns of uneven rows (SPMM 12288 x 768,
-    // 480 columns, log-normal: 1.21e-7 and 0.99e-7).  From four ranges on none is, but for up to 32 columns over K below 2560.
+    // one range (530 of 886 random calls, by up to 1.66: FusedMM 29184 x 3840, 32/84 6.9e-8 against 4.9e-8) or in two or three (151 of
+    // 1269, 1.12); all of a K above 2048 in one range (FusedMM 12764 x 3172, 456/104: 7.0e-8 and 5.4e-8); blocks of 192 and 256 columns, which
+    // do not put sums away within a range, over all of K or in two or three ranges of more than 768 columns of uneven rows (SPMM 12288 x
+    // 768, 480 columns, log-normal: 1.21e-7 and 0.99e-7).  From four ranges on 18 of 7454, up to 32 columns wide and over a K below 2560.
     // Over 5951 random calls that are taken: at most 0.99 on data of one sign and 0.75 on data of both; 1.52 times as fast on average,
-    // 52 of them slower by more than 3 % (at worst 0.84).  Over 3820 planned ones from four ranges on (all that the matrix cores do of up to
-    // 64 columns): at most 0.97.
+    // 52 of them slower by more than 3 % (at worst 0.84).  Over 3334 planned ones of up to 64 columns that the matrix cores do in four
+    // ranges or more, by whatever rule, at most 0.96.
     const bool few = c.segs < 4, some = c.segs > 1;
     const bool as_exact = s.N <= 32   ? !few && s.K >= 3072
                           : s.N <= 64 ? !few || (some && !planned && s.K >= 1536)
